@@ -1,0 +1,713 @@
+"""Performance cases: the work a user of the library has it do, through the
+binding's public entry points.
+
+listed() / draw(rng)  the cases: dicts of plain values (see _case)
+prepare(case, seed)   what the program holds before the call: a grid handle
+                      with its properties (or a batch), and the state
+run(state)            one pass: a time step, a rollout with its gradient, a
+                      batched step, or a stand-alone pressure solve
+work(case)            the bytes and operations one pass cannot do without
+exact(case, seed)     the result of the first pass in plain torch, float64
+
+A step is run on the state in place, as a program's time loop does: the next
+pass on the same state is the next step.
+"""
+from __future__ import annotations
+
+import math
+from types import SimpleNamespace
+
+import numpy as np
+import torch
+
+import paper_2009_06628_amd as chns
+from paper_2009_06628_amd.adjoint import rollout
+
+F64 = torch.float64
+# solver tolerances (CH, momentum, pressure) of the two arithmetic forms
+TOLERANCES = {"fp64": (1e-15, 1e-13, 1e-12), "fp32": (1e-10, 1e-9, 1e-8)}
+PRECISION = {"fp64": chns.CHNS_FP64, "fp32": chns.CHNS_FP32_REFINE}
+ENSEMBLE_SIZES = (64, 96, 128, 192, 256)
+
+
+def _case(path, physics, n, precision="fp64", walls="", **more):
+    """path: step, cn (Crank-Nicolson step), rollout (forward and backward),
+    batch or pressure; physics: the parameter set of _problem; n: cells per
+    axis; walls: the walled axes, the others are periodic."""
+    c = {"path": path, "physics": physics, "nx": n[0], "ny": n[1], "nz": n[2] if len(n) > 2 else 0,
+         "precision": precision, "walls": walls}
+    c.update(more)
+    return c
+
+
+def listed():
+    return [
+        # the smallest ordinary call, a 2D drop on a coarse grid: launch latency
+        dict(_case("step", "drop", (64, 64)), name="static_drop_64"),
+        # ragged axes (no power of two), walls, the precision form: a reduced bubble
+        dict(_case("step", "bubble", (80, 176), "fp32", "y"), name="bubble_80x176_fp32"),
+        # the rising-bubble configuration: density ratio 1000, walls, gravity
+        dict(_case("step", "bubble", (256, 512), walls="y"), name="bubble_256x512"),
+        # a large 2D step, walls on every side, an axis of no power of two
+        dict(_case("step", "drop", (768, 768), walls="xy"), name="drop_walls_768"),
+        # two phases in 3D on an axis that is no power of two
+        dict(_case("step", "drops3d", (96, 96, 96)), name="drops3d_96"),
+        # the three-phase headline configuration in both arithmetic forms
+        dict(_case("step", "ternary", (128, 128, 128), "fp32"), name="ternary_128_fp32"),
+        dict(_case("step", "ternary", (128, 128, 128)), name="ternary_128"),
+        # walls on every side in 3D with a moving lid
+        dict(_case("step", "cavity", (64, 64, 64), walls="xyz"), name="cavity_64"),
+        # the second-order time scheme (three Picard iterations a step)
+        dict(_case("cn", "bubble", (128, 256), walls="y"), name="crank_nicolson_128x256"),
+        # the differentiable rollout, forward and backward: parameter fitting
+        dict(_case("rollout", "oscillating", (128, 128), steps=10, every=5), name="rollout_128"),
+        # the ensemble configuration: 512 drops of 64^2 .. 256^2, one batched step
+        dict(_case("batch", "ensemble", (0, 0), "fp32", count=512), name="ensemble_512"),
+        # the largest: one pressure solve far above the last-level cache
+        dict(_case("pressure", "drops3d", (512, 512, 512)), name="pressure_512"),
+    ]
+
+
+def _axis(rng, lo, hi, k):
+    """An axis length m 2^k between lo and hi, spread over the logarithm."""
+    t = math.exp(rng.uniform(math.log(lo), math.log(hi)))
+    return max(1, round(t / 2 ** k)) << k
+
+
+def draw(rng):
+    kind = rng.choice(["step2", "step2", "step3", "ternary", "cavity", "cn", "rollout", "batch", "pressure2",
+                       "pressure3"])
+    prec = rng.choice(["fp64", "fp64", "fp32"])
+    if kind in ("step2", "cn"):
+        # the coarsest grid of the hierarchy keeps at most 512 cells
+        k = rng.choice([4, 5, 6])
+        n = (_axis(rng, 48, 20 << k, k), _axis(rng, 48, 20 << k, k))
+        if kind == "cn":
+            n = (min(n[0], 384), min(n[1], 384))
+            return _case("cn", rng.choice(["drop", "bubble"]), n, walls=rng.choice(["", "y"]))
+        return _case("step", rng.choice(["drop", "bubble"]), n, prec, rng.choice(["", "y", "xy"]))
+    if kind in ("step3", "ternary", "cavity"):
+        k = rng.choice([3, 4])
+        top = 136 if kind != "cavity" else 104
+        n = tuple(_axis(rng, 32, min(top, 8 << k), k) for _ in range(3))
+        if kind == "cavity":
+            return _case("step", "cavity", n, walls="xyz")
+        return _case("step", "drops3d" if kind == "step3" else "ternary", n, prec)
+    if kind == "rollout":
+        m = _axis(rng, 32, 160, 4)
+        return _case("rollout", "oscillating", (m, m), steps=rng.randint(2, 10), every=rng.choice([2, 5]))
+    if kind == "batch":
+        return _case("batch", "ensemble", (0, 0), "fp32", count=int(math.exp(rng.uniform(math.log(8), math.log(400)))))
+    if kind == "pressure2":
+        return _case("pressure", "drop", (_axis(rng, 256, 4096, 8), _axis(rng, 256, 4096, 8)), walls=rng.choice(["", "y"]))
+    k = rng.choice([5, 6])
+    return _case("pressure", "drops3d", tuple(_axis(rng, 64, 7 << k, k) for _ in range(3)), prec)
+
+
+# ---------------------------------------------------------------------------
+# problems and inputs
+# ---------------------------------------------------------------------------
+
+class _Props(SimpleNamespace):
+    def copy(self, **kw):
+        return _Props(**{**vars(self), **kw})
+
+
+def _problem(case, seed):
+    """Grid and properties (the repository's configurations at the case's
+    size); the time step stays below the capillary bound."""
+    n = tuple(v for v in (case["nx"], case["ny"], case["nz"]) if v)
+    ph = case["physics"]
+    L = 2.0 if ph == "bubble" else 1.0
+    h = L / n[0]
+    Cn = 1.5 * h
+    rtol = TOLERANCES[case["precision"]]
+    pr = _Props(rho_minus=0.1, eta_minus=0.1, Re=10.0, We=1.0, Cn=Cn, Pe=1000.0, inv_Fr=0.0, dt=1e-4, S=2.0,
+                rtol_ch=rtol[0], rtol_mom=rtol[1], rtol_p=rtol[2], max_iter=300, nphases=2,
+                rho3=(1.0,) * 3, eta3=(1.0,) * 3, sigma3=(1.0,) * 3)
+    if ph == "bubble":
+        pr.__dict__.update(rho_minus=1e-3, eta_minus=1e-2, Re=35.0, We=10.0, Pe=1.0 / (3.0 * Cn * Cn), inv_Fr=1.0,
+                           dt=2.5e-4)
+    elif ph == "drops3d":
+        pr.__dict__.update(rho_minus=0.01, eta_minus=0.01, Pe=1.0 / (3.0 * Cn * Cn))
+    elif ph == "ternary":
+        pr.__dict__.update(Re=1.0, Pe=1.0 / (3.0 * Cn * Cn), nphases=3, rho3=(100.0, 10.0, 1.0),
+                           eta3=(1e-2, 1e-2, 1e-2), sigma3=(0.586, 0.737, 1.301))
+    elif ph == "cavity":
+        pr.__dict__.update(rho_minus=1.0, eta_minus=1.0, Re=100.0, We=100.0, Pe=1.0 / (3.0 * Cn * Cn), dt=1e-3)
+    pr.dt = min(pr.dt, _capillary(pr.rho_minus, h, 1.0 / pr.We))
+    bc = tuple("wall" if "xyz"[a] in case["walls"] else "periodic" for a in range(len(n)))
+    return SimpleNamespace(n=n, h=h, bc=bc, props=pr, shape=tuple(reversed(n)), dim=len(n),
+                           per=tuple(b == "periodic" for b in bc))
+
+
+def _capillary(rho_minus, h, sigma):
+    return 0.5 * math.sqrt((1.0 + rho_minus) * h ** 3 / (2.0 * math.pi * sigma))
+
+
+def _coords(p, centred=(True, True, True)):
+    """Coordinate of every axis, shaped to broadcast over the grid."""
+    out = []
+    for a in range(p.dim):
+        x = (torch.arange(p.n[a], dtype=F64, device="cuda") + (0.5 if centred[a] else 0.0)) * p.h
+        sh = [1] * p.dim
+        sh[p.dim - 1 - a] = p.n[a]
+        out.append(x.view(sh))
+    return out
+
+
+def _distance(p, centres, radii):
+    """Signed distance to the nearest drop (negative inside)."""
+    X = _coords(p)
+    best = torch.full(p.shape, float("inf"), dtype=F64, device="cuda")
+    for c, r in zip(centres, radii):
+        r2 = 0.0
+        for a in range(p.dim):
+            d = X[a] - c[a]
+            L = p.n[a] * p.h
+            r2 = r2 + (d - L * torch.round(d / L) if p.per[a] else d) ** 2
+        best = torch.minimum(best, torch.sqrt(r2) - r)
+    return best
+
+
+def _drops(p, rng, count):
+    """Seeded drops in the box, surfaces some cells apart."""
+    L = [m * p.h for m in p.n]
+    s = min(L)
+    centres, radii = [], []
+    for _ in range(20000):
+        r = rng.uniform(0.05, 0.12) * s
+        c = [rng.uniform(0, l) if per else rng.uniform(1.5 * r, l - 1.5 * r) for l, per in zip(L, p.per)]
+        far = True
+        for c2, r2 in zip(centres, radii):
+            d = [abs(x - y) for x, y in zip(c, c2)]
+            d = [min(x, l - x) if per else x for x, l, per in zip(d, L, p.per)]
+            far = far and math.sqrt(sum(x * x for x in d)) > r + r2 + 0.07 * s
+        if far:
+            centres.append(c)
+            radii.append(r)
+            if len(radii) == count:
+                break
+    return centres, radii
+
+
+def _profile(d, Cn):
+    return torch.tanh(d / (math.sqrt(2.0) * Cn))
+
+
+def _velocity(p, rng, amp):
+    """Divergence-free face velocity: the discrete curl of a seeded potential
+    of a few long waves, damped to zero at walls."""
+    def potential(centred):
+        X = _coords(p, centred)
+        A = torch.zeros(p.shape, dtype=F64, device="cuda")
+        for _ in range(8):
+            k = [int(v) for v in rng.integers(-2, 3, size=p.dim)]
+            arg = sum(2.0 * math.pi * k[a] * X[a] / (p.n[a] * p.h) for a in range(p.dim))
+            A = A + float(rng.normal()) * torch.cos(arg + float(rng.uniform(0, 2 * math.pi)))
+        for a in range(p.dim):
+            if not p.per[a]:
+                A = A * torch.sin(math.pi * X[a] / (p.n[a] * p.h)) ** 2
+        return A
+
+    def dplus(q, a):
+        return (torch.roll(q, -1, dims=p.dim - 1 - a) - q) / p.h
+
+    if p.dim == 2:
+        A = potential((False, False))
+        u = [dplus(A, 1), -dplus(A, 0)]
+    else:
+        A = [potential(tuple(b == a for b in range(3))) for a in range(3)]
+        u = [dplus(A[2], 1) - dplus(A[1], 2), dplus(A[0], 2) - dplus(A[2], 0), dplus(A[1], 0) - dplus(A[0], 1)]
+    m = max(float(x.abs().max()) for x in u)
+    return [(x * (amp / m)).contiguous() for x in u]
+
+
+def _inputs(case, seed):
+    """The problem and its initial state (device tensors), from the seed."""
+    p = _problem(case, seed)
+    rng = np.random.default_rng(seed)
+    L = [m * p.h for m in p.n]
+    pr, ph = p.props, case["physics"]
+    if ph == "ternary":
+        c, r = _drops(p, rng, 16)
+        phi = [-_profile(_distance(p, c[i::2], r[i::2]), pr.Cn) for i in range(2)]
+    elif ph == "cavity":
+        phi = (_profile(rng.uniform(0.45, 0.55) * L[1] - _coords(p)[1], pr.Cn)).expand(p.shape).contiguous()
+    elif ph == "drops3d":
+        phi = _profile(_distance(p, *_drops(p, rng, 16)), pr.Cn)
+    elif ph == "oscillating":
+        X = _coords(p)
+        s = [0.3 + 0.01 * rng.uniform(-1, 1), 0.2 + 0.01 * rng.uniform(-1, 1)]
+        phi = _ellipse(p, X, s) * (1.0 - 1e-4)
+    else:
+        r = rng.uniform(0.22, 0.27) * min(L)
+        c = [l * rng.uniform(0.45, 0.55) for l in L]
+        if ph == "bubble":
+            c[1] = max(1.1 * r, L[1] * 0.25)
+        phi = _profile(_distance(p, [c], [r]), pr.Cn)
+    if ph in ("cavity", "oscillating"):
+        u = [torch.zeros(p.shape, dtype=F64, device="cuda") for _ in range(p.dim)]
+    else:
+        u = _velocity(p, rng, 1e-2)
+    p.lid = None
+    if ph == "cavity":
+        # the lid's speed at the x faces, zero at its edges
+        X = _coords(p)
+        x, z = X[0] - 0.5 * p.h, X[2]
+        p.lid = (float(rng.uniform(0.9, 1.1)) * 16.0 / L[2] ** 2 * x * (1.0 - x) * z * (L[2] - z)).expand(p.shape).contiguous()
+    return p, {"phi": phi, "u": u}
+
+
+def _ellipse(p, X, s):
+    q = sum(((X[a] - 0.5 * p.n[a] * p.h) / s[a]) ** 2 for a in range(2))
+    g = sum(((X[a] - 0.5 * p.n[a] * p.h) / s[a] ** 2) ** 2 for a in range(2))
+    rad = torch.sqrt(q)
+    return _profile((rad - 1.0) * rad / torch.sqrt(g).clamp_min(1e-300), p.props.Cn)
+
+
+def _members(case, seed):
+    """Problems and semi-axes of an ensemble of oscillating drops."""
+    rng = np.random.default_rng(seed)
+    sizes = np.random.default_rng(4).choice(ENSEMBLE_SIZES, size=case["count"])  # the sizes are the case's, not the seed's
+    out = []
+    for n in sizes:
+        n, h = int(n), 1.0 / int(n)
+        s = [float(v) for v in rng.uniform(0.2, 0.3, size=2)]
+        rm = math.exp(-rng.uniform(0.0, math.log(1000.0)))
+        em = math.exp(-rng.uniform(0.0, math.log(100.0)))
+        p = _problem(dict(case, physics="oscillating", nx=n, ny=n), seed)
+        p.props.rho_minus, p.props.eta_minus, p.props.dt = rm, em, min(1e-4, _capillary(rm, h, 1.0))
+        out.append((p, s))
+    return out
+
+
+def _rhs(p, phi, seed):
+    """A pressure right-hand side as a projection has it: sources at the
+    interfaces on top of a smooth field."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    q = torch.randn(p.shape, dtype=F64, device="cuda", generator=gen) * (1.0 - phi * phi)
+    X = _coords(p)
+    smooth = 1.0
+    for a in range(p.dim):
+        smooth = smooth * torch.cos(2.0 * math.pi * X[a] / (p.n[a] * p.h) + 0.3 * (a + 1) + seed % 7)
+    q = q * 10.0 + smooth
+    return q - q.mean()
+
+
+def _density(p, phi):
+    rm = p.props.rho_minus
+    return 0.5 * (1.0 - rm) * phi.clamp(-1.0, 1.0) + 0.5 * (1.0 + rm)
+
+
+def prepare(case, seed):
+    if case["path"] == "batch":
+        members = _members(case, seed)
+        b = chns.create_batch([p for p, _ in members], precision=PRECISION[case["precision"]])
+        b.set_tiled(1024)
+        st = b.new_state()
+        for i, (p, s) in enumerate(members):
+            b.view(st, i)["phi"].copy_(_ellipse(p, _coords(p), s))
+        return {"path": "batch", "batch": b, "st": st}
+    p, ini = _inputs(case, seed)
+    g = chns.create_grid(p.n, p.h, p.bc, precision=PRECISION[case["precision"]], nphases=p.props.nphases)
+    if case["path"] == "pressure":
+        return {"path": "pressure", "grid": g, "rho": _density(p, ini["phi"]), "rhs": _rhs(p, ini["phi"], seed),
+                "p": torch.zeros(p.shape, dtype=F64, device="cuda"), "rtol": p.props.rtol_p}
+    if case["path"] == "rollout":
+        target = torch.roll(ini["phi"], 1, dims=1)
+        return {"path": "rollout", "grid": g, "props": p.props, "phi": ini["phi"], "u": ini["u"], "target": target,
+                "h": p.h, "steps": case["steps"], "every": case["every"]}
+    if p.lid is not None:
+        g.set_wall_velocity(1, 1, 0, p.lid)
+    g.set_properties(p.props)
+    if case["path"] == "cn":
+        g.set_option(chns.CHNS_OPT_TIME_SCHEME, chns.CHNS_SCHEME_CN)
+    st = g.new_state()
+    for k, v in (("phi", ini["phi"]), ("u", ini["u"])):
+        for to, x in zip(st[k] if isinstance(st[k], list) else [st[k]], v if isinstance(v, list) else [v]):
+            to.copy_(x)
+    return {"path": "step", "grid": g, "st": st}
+
+
+def run(state):
+    if state["path"] == "step":
+        state["grid"].step(state["st"], 1, stats=False)
+        return state["st"]
+    if state["path"] == "batch":
+        state["batch"].step(state["st"], 1, stats=False)
+        return state["st"]
+    if state["path"] == "pressure":
+        state["p"].zero_()
+        state["grid"].solve_pressure(state["rho"], state["rhs"], state["p"], rtol=state["rtol"])
+        return state["p"]
+    # a fit's loss and gradient: initial fields, surface tension and mobility
+    phi0 = state["phi"].detach().requires_grad_()
+    u0 = [x.detach().requires_grad_() for x in state["u"]]
+    sigma = torch.tensor(1.1, dtype=F64, requires_grad=True)
+    mobility = torch.tensor(1.2e-3, dtype=F64, requires_grad=True)
+    out = rollout(state["grid"], state["props"], phi0, u0, sigma, mobility, state["steps"], state["every"])
+    loss = 0.5 * state["h"] ** 2 * ((out[0] - state["target"]) ** 2).sum()
+    loss.backward()
+    return {"phi": out[0].detach(), "u": [x.detach() for x in out[1:]], "loss": loss.detach(), "dphi": phi0.grad,
+            "du": [x.grad for x in u0], "dsigma": sigma.grad, "dmobility": mobility.grad}
+
+
+def work(case):
+    """Each field read once and written once, and one evaluation of every
+    term of the step (a solve at least applies its operator once)."""
+    if case["path"] == "batch":
+        sizes = np.random.default_rng(4).choice(ENSEMBLE_SIZES, size=case["count"])
+        cells, d = int((sizes.astype(np.int64) ** 2).sum()), 2
+    else:
+        n = [v for v in (case["nx"], case["ny"], case["nz"]) if v]
+        cells, d = math.prod(n), len(n)
+    if case["path"] == "pressure":
+        return {"bytes": 24.0 * cells, "flops": (6.0 * d + 2) * cells}
+    ph = 2 if case["physics"] == "ternary" else 1
+    arrays = (ph + d + 1) + (2 * ph + d + 1)      # phi, u, p in; phi, u, p, mu out
+    flops = 80.0 * ph + 60.0 * d * d
+    times = {"cn": 3, "rollout": 3 * case.get("steps", 1)}.get(case["path"], 1)
+    if case["path"] == "rollout":
+        arrays = 2 * (1 + d) + 1 + (1 + d)        # phi, u, target in; phi, u and the gradients out
+    return {"bytes": 8.0 * arrays * cells, "flops": flops * times * cells}
+
+
+# ---------------------------------------------------------------------------
+# the same results in plain torch, float64
+# ---------------------------------------------------------------------------
+
+class _Ops:
+    """Difference operators on arrays of shape (batch, nz, ny, nx): cells and
+    faces as the library lays them out, walls where not periodic."""
+
+    def __init__(self, n, h, per):
+        self.n, self.h, self.per, self.d = n, h, per, len(n)
+        self.dims = tuple(range(1, self.d + 1))
+        self.lo, self.hi = [], []
+        for a in range(self.d):
+            i = torch.arange(n[a], device="cuda")
+            sh = [1] * (self.d + 1)
+            sh[self.dim(a)] = n[a]
+            wall = 0.0 if per[a] else 1.0
+            self.lo.append((i == 0).to(F64).view(sh) * wall)
+            self.hi.append((i == n[a] - 1).to(F64).view(sh) * wall)
+
+    def dim(self, a):
+        return self.d - a
+
+    def at(self, q, a, s):
+        """q[c + s e_a], zero outside a wall."""
+        r = torch.roll(q, -s, dims=self.dim(a))
+        return r if self.per[a] else r * (1.0 - (self.hi[a] if s > 0 else self.lo[a]))
+
+    def grad(self, q, a):
+        return (q - self.at(q, a, -1)) / self.h * (1.0 - self.lo[a])
+
+    def div(self, F):
+        out = 0.0
+        for a in range(self.d):
+            f = F[a] * (1.0 - self.lo[a])
+            out = out + (self.at(f, a, 1) - f) / self.h
+        return out
+
+    def avg(self, q, a):
+        return 0.5 * (q + self.at(q, a, -1) + self.lo[a] * q)
+
+    def lap(self, q):
+        return self.div([self.grad(q, a) for a in range(self.d)])
+
+    def function_of_laplacian(self, r, f):
+        """f(L) r: walled axes are extended evenly, then a Fourier transform."""
+        for a in range(self.d):
+            if not self.per[a]:
+                r = torch.cat([r, r.flip(self.dim(a))], dim=self.dim(a))
+        m = [r.shape[k] for k in self.dims]
+        lam = 0.0
+        for j, k in enumerate(self.dims):
+            freq = torch.arange(m[j] // 2 + 1 if j == self.d - 1 else m[j], dtype=F64, device="cuda")
+            sh = [1] * (self.d + 1)
+            sh[k] = freq.numel()
+            lam = lam - (4.0 / self.h ** 2) * torch.sin(math.pi * freq / m[j]).view(sh) ** 2
+        x = torch.fft.irfftn(torch.fft.rfftn(r, dim=self.dims) * f(lam), s=m, dim=self.dims)
+        for a in range(self.d):
+            x = x.narrow(self.dim(a), 0, self.n[a])
+        return x
+
+
+class _Pressure:
+    """-D(c_a G p), c_a per face, on mean-free fields."""
+
+    def __init__(self, o):
+        self.o = o
+
+    def apply(self, x, *c):
+        return -self.o.div([c[a] * self.o.grad(x, a) for a in range(self.o.d)])
+
+    def project(self, x):
+        return x - x.mean(self.o.dims, keepdim=True)
+
+    def precondition(self, r, c):
+        return self.o.function_of_laplacian(r, lambda lam: torch.where(lam < 0, -1.0 / lam, torch.zeros_like(lam)))
+
+
+class _Momentum:
+    """shift u - div(k grad u) for component a; k per direction and side."""
+
+    def __init__(self, o, a):
+        self.o, self.a = o, a
+        self.unknown = 1.0 - o.lo[a]
+
+    def coefficients(self, eta, Re):
+        o, a, out = self.o, self.a, []
+        scale = 1.0 / (Re * o.h * o.h)
+        em = o.at(eta, a, -1)
+        for b in range(o.d):
+            for s in (1, -1):
+                if b == a:
+                    out.append((eta if s > 0 else em) * scale)
+                else:
+                    wall = o.hi[b] if s > 0 else o.lo[b]
+                    k = 0.25 * (eta + em + o.at(eta, b, s) + o.at(em, b, s))
+                    out.append((k + wall * 0.25 * (eta + em)) * scale)
+        return out
+
+    def apply(self, x, shift, *k):
+        o = self.o
+        x = x * self.unknown
+        y, j = shift * x, 0
+        for b in range(o.d):
+            for s in (1, -1):
+                up = o.at(x, b, s)
+                if b != self.a:
+                    up = up - (o.hi[b] if s > 0 else o.lo[b]) * x
+                y = y + k[j] * (x - up)
+                j += 1
+        return y * self.unknown
+
+    def project(self, x):
+        return x * self.unknown
+
+    def precondition(self, r, c):
+        o, diag = self.o, c[0] + sum(c[1:])
+        j = 1
+        for b in range(o.d):
+            for s in (1, -1):
+                if b != self.a:
+                    diag = diag + (o.hi[b] if s > 0 else o.lo[b]) * c[j]
+                j += 1
+        return r / diag
+
+
+def _cg(op, b, c):
+    """Preconditioned conjugate gradients to rounding, restarted on the true residual."""
+    dot = lambda x, y: (x * y).sum(op.o.dims, keepdim=True)  # noqa: E731
+    b = op.project(b)
+    x, bb = torch.zeros_like(b), dot(b, b).clamp_min(1e-300)
+    for _ in range(3):
+        r = op.project(b - op.apply(x, *c))
+        p, rz = None, None
+        for it in range(1500):
+            z = op.project(op.precondition(r, c))
+            new = dot(r, z)
+            p = z if p is None else z + torch.where(rz > 0, new / rz, torch.zeros_like(rz)) * p
+            rz = new
+            q = op.apply(p, *c)
+            pq = dot(p, q)
+            alpha = torch.where(pq > 0, rz / pq, torch.zeros_like(pq))
+            x, r = x + alpha * p, r - alpha * q
+            if it % 20 == 19 and float((dot(r, r) / bb).max()) < 1e-29:
+                break
+    return op.project(x)
+
+
+class _Solve(torch.autograd.Function):
+    @staticmethod
+    def forward(ctx, op, b, *c):
+        x = _cg(op, b, c)
+        ctx.op = op
+        ctx.save_for_backward(x, *c)
+        return x
+
+    @staticmethod
+    def backward(ctx, g):
+        x, *c = ctx.saved_tensors
+        lam = _cg(ctx.op, g, c)
+        with torch.enable_grad():
+            cc = [t.detach().requires_grad_() for t in c]
+            gc = torch.autograd.grad(ctx.op.apply(x, *cc), cc, -lam, allow_unused=True)
+        return (None, lam, *gc)
+
+
+def _advection(o, m, u, a, skew):
+    """m . grad u_a, or the half sum of it and div(m u_a)."""
+    adv, dv = 0.0, 0.0
+    for b in range(o.d):
+        f = m[b] if b == a else o.at(m[b], a, -1)
+        up, um = o.at(u, b, 1), o.at(u, b, -1)
+        if b == a:
+            mp, mm = 0.5 * (m[a] + o.at(m[a], a, 1)), 0.5 * (o.at(m[a], a, -1) + m[a])
+        else:
+            mp, mm = 0.5 * (o.at(m[b], b, 1) + o.at(f, b, 1)), 0.5 * (m[b] + f)
+            up, um = up - o.hi[b] * u, um - o.lo[b] * u
+        adv = adv + 0.5 * (mp * (up - u) + mm * (u - um)) / o.h
+        dv = dv + 0.5 * (mp * (u + up) - mm * (u + um)) / o.h
+    return 0.5 * (adv + dv) if skew else adv
+
+
+def _dpsi(q):
+    return q ** 3 - q
+
+
+def _pull(q):
+    return torch.where(q.abs() < 1.0, q, torch.sign(q).detach())
+
+
+def _ch(o, r, a, b):
+    return o.function_of_laplacian(r, lambda lam: 1.0 / (1.0 - a * lam + b * lam * lam))
+
+
+def _momentum(o, a, shift, eta, Re, rhs, lid):
+    op = _Momentum(o, a)
+    k = op.coefficients(eta, Re)
+    if lid is not None and a == 0:
+        # the top wall moves along x: 2 k U on the rows next to it
+        kw = 0.5 * (eta + o.at(eta, 0, -1)) / (Re * o.h ** 2)
+        rhs = rhs + o.hi[1] * 2.0 * kw * lid
+    return _Solve.apply(op, rhs * op.unknown, shift, *k)
+
+
+def _step(o, pr, phis, u, lid=None):
+    """One split step; phis: the stored phases (one for two phases, two for
+    three).  pr: numbers, or tensors that broadcast over the batch."""
+    d, dt, Cn, S = o.d, pr.dt, pr.Cn, pr.S
+    kM = 1.0 / (pr.Pe * Cn)
+    three = len(phis) == 2
+    if three:
+        s12, s13, s23 = pr.sigma3
+        Sg = (s12 + s13 - s23, s12 + s23 - s13, s13 + s23 - s12)
+        w = [(1.0 / s) / sum(1.0 / t for t in Sg) for s in Sg]
+        lam = _dpsi(phis[0]) + _dpsi(phis[1]) + _dpsi(-1.0 - phis[0] - phis[1])
+    else:
+        w, lam = [0.0], 0.0
+    mus, Gmu, new, Fs = [], [], [], []
+    for i, q in enumerate(phis):
+        F = [u[a] * o.avg(q, a) for a in range(d)]
+        r = q - dt * o.div(F) + dt * kM * o.lap(_dpsi(q) - S * q - w[i] * lam)
+        hat = _ch(o, r, dt * kM * S, dt * kM * Cn * Cn)
+        mu = _dpsi(q) + S * (hat - q) - Cn * Cn * o.lap(hat) - w[i] * lam
+        G = [o.grad(mu, a) for a in range(d)]
+        new.append(q - dt * o.div([F[a] - kM * G[a] for a in range(d)]))
+        mus.append(mu)
+        Gmu.append(G)
+    if three:
+        full = lambda p: [p[0], p[1], -1.0 - p[0] - p[1]]  # noqa: E731
+        mix = lambda v, p, f: sum(v[i] * f(0.5 * (1.0 + full(p)[i])) for i in range(3))  # noqa: E731
+        clip = lambda c: c.clamp(0.0, 1.0)  # noqa: E731
+        lin = mix(pr.rho3, phis, lambda c: c)
+        J = [-0.5 * kM * sum((pr.rho3[i] - pr.rho3[2]) * Gmu[i][a] for i in range(2)) for a in range(d)]
+        rho0, rho1, eta1 = mix(pr.rho3, phis, clip), mix(pr.rho3, new, clip), mix(pr.eta3, new, clip)
+        G3 = Gmu + [[-Gmu[0][a] - Gmu[1][a] for a in range(d)]]
+        force = [-(0.5 / Cn) * sum(Sg[i] * o.avg(full(phis)[i], a) * G3[i][a] for i in range(3)) for a in range(d)]
+    else:
+        al, be, ga, xi = 0.5 * (1 - pr.rho_minus), 0.5 * (1 + pr.rho_minus), 0.5 * (1 - pr.eta_minus), 0.5 * (1 + pr.eta_minus)
+        lin = al * phis[0] + be
+        J = [-(al * kM) * Gmu[0][a] for a in range(d)]
+        rho0, rho1, eta1 = al * _pull(phis[0]) + be, al * _pull(new[0]) + be, ga * _pull(new[0]) + xi
+        force = [-(1.0 / (pr.We * Cn)) * o.avg(phis[0], a) * Gmu[0][a] for a in range(d)]
+    m = [(o.avg(lin, a) * u[a] + J[a]) * (1.0 - o.lo[a]) for a in range(d)]
+    us, rf = [], [o.avg(rho1, a) for a in range(d)]
+    for a in range(d):
+        rhs = 0.5 * (rf[a] + o.avg(rho0, a)) / dt * u[a] - _advection(o, m, u[a], a, True) + force[a]
+        if a == 1:
+            rhs = rhs - rf[a] * pr.inv_Fr
+        us.append(_momentum(o, a, rf[a] / dt, eta1, pr.Re, rhs, lid))
+    p = _Solve.apply(_Pressure(o), -(pr.We / dt) * o.div(us), *[1.0 / x for x in rf])
+    un = [(us[a] - (dt / pr.We) * o.grad(p, a) / rf[a]) * (1.0 - o.lo[a]) for a in range(d)]
+    return new, un, p, mus
+
+
+def _step_cn(o, pr, phi, u, p, picard=3):
+    """One Crank-Nicolson step (midpoint terms, Picard iterations)."""
+    d, dt, Cn, S = o.d, pr.dt, pr.Cn, pr.S
+    kM = 1.0 / (pr.Pe * Cn)
+    al, be, ga, xi = 0.5 * (1 - pr.rho_minus), 0.5 * (1 + pr.rho_minus), 0.5 * (1 - pr.eta_minus), 0.5 * (1 + pr.eta_minus)
+    q, v = phi, u
+    for _ in range(picard):
+        F = [v[a] * o.avg(q, a) for a in range(d)]
+        r = phi - 0.5 * dt * o.div(F) + 0.5 * dt * kM * o.lap(_dpsi(q) - S * q)
+        hat = _ch(o, r, 0.5 * dt * kM * S, 0.5 * dt * kM * Cn * Cn)
+        mu = _dpsi(q) + S * (hat - q) - Cn * Cn * o.lap(hat)
+        G = [o.grad(mu, a) for a in range(d)]
+        new = phi - dt * o.div([F[a] - kM * G[a] for a in range(d)])
+        mid = 0.5 * (phi + new)
+        m = [(o.avg(al * q + be, a) * v[a] - al * kM * G[a]) * (1.0 - o.lo[a]) for a in range(d)]
+        rho, eta = al * _pull(mid) + be, ga * _pull(mid) + xi
+        rf = [o.avg(rho, a) for a in range(d)]
+        vs = []
+        for a in range(d):
+            rhs = 2.0 * rf[a] / dt * u[a] - _advection(o, m, v[a], a, False) - o.grad(p, a) / pr.We
+            rhs = rhs - (1.0 / (pr.We * Cn)) * o.avg(q, a) * G[a]
+            if a == 1:
+                rhs = rhs - rf[a] * pr.inv_Fr
+            vs.append(_momentum(o, a, 2.0 * rf[a] / dt, eta, pr.Re, rhs, None))
+        dp = _Solve.apply(_Pressure(o), -(2.0 * pr.We / dt) * o.div(vs), *[1.0 / x for x in rf])
+        v = [(vs[a] - (0.5 * dt / pr.We) * o.grad(dp, a) / rf[a]) * (1.0 - o.lo[a]) for a in range(d)]
+        p = p + dp
+        q = mid
+    un = [(2.0 * v[a] - u[a]) * (1.0 - o.lo[a]) for a in range(d)]
+    return new, un, p - p.mean(o.dims, keepdim=True), mu
+
+
+def _exact_batch(case, seed):
+    members = _members(case, seed)
+    parts = {k: [[None] * len(members) for _ in range(2 if k == "u" else 1)] for k in ("phi", "u", "p", "mu")}
+    for n in sorted({p.n[0] for p, _ in members}):
+        ids = [i for i, (p, _) in enumerate(members) if p.n[0] == n]
+        first = members[ids[0]][0]
+        o = _Ops(first.n, first.h, first.per)
+        pr = first.props.copy()
+        for key in ("rho_minus", "eta_minus", "dt"):
+            v = [getattr(members[i][0].props, key) for i in ids]
+            setattr(pr, key, torch.tensor(v, dtype=F64, device="cuda").view(-1, 1, 1))
+        phi = torch.stack([_ellipse(members[i][0], _coords(members[i][0]), members[i][1]) for i in ids])
+        new, un, p, mus = _step(o, pr, [phi], [torch.zeros_like(phi) for _ in range(2)])
+        for j, i in enumerate(ids):
+            for key, val in (("phi", new), ("u", un), ("p", [p]), ("mu", mus)):
+                for a, x in enumerate(val):
+                    parts[key][a][i] = x[j].reshape(-1)
+    got = {k: [torch.cat(x) for x in v] for k, v in parts.items()}
+    return {"phi": got["phi"][0], "u": got["u"], "p": got["p"][0], "mu": got["mu"][0]}
+
+
+def exact(case, seed):
+    if case["path"] == "batch":
+        return _exact_batch(case, seed)
+    p, ini = _inputs(case, seed)
+    o, pr = _Ops(p.n, p.h, p.per), p.props
+    one = lambda q: q.unsqueeze(0)  # noqa: E731
+    if case["path"] == "pressure":
+        rho = one(_density(p, ini["phi"]))
+        return _cg(_Pressure(o), one(_rhs(p, ini["phi"], seed)), [1.0 / o.avg(rho, a) for a in range(p.dim)])[0]
+    u = [one(x) for x in ini["u"]]
+    if case["path"] == "rollout":
+        phi0 = ini["phi"].detach().requires_grad_()
+        u0 = [x.detach().requires_grad_() for x in ini["u"]]
+        sigma = torch.tensor(1.1, dtype=F64, device="cuda", requires_grad=True)
+        mobility = torch.tensor(1.2e-3, dtype=F64, device="cuda", requires_grad=True)
+        pr.We, pr.Pe = 1.0 / sigma, 1.0 / (mobility * sigma)
+        phi, u = one(phi0), [one(x) for x in u0]
+        for _ in range(case["steps"]):
+            (phi,), u, _, _ = _step(o, pr, [phi], u)
+        loss = 0.5 * p.h ** 2 * ((phi[0] - torch.roll(ini["phi"], 1, dims=1)) ** 2).sum()
+        loss.backward()
+        return {"phi": phi[0].detach(), "u": [x[0].detach() for x in u], "loss": loss.detach(), "dphi": phi0.grad,
+                "du": [x.grad for x in u0], "dsigma": sigma.grad, "dmobility": mobility.grad}
+    if case["path"] == "cn":
+        new, un, pn, mu = _step_cn(o, pr, one(ini["phi"]), u, torch.zeros_like(u[0]))
+        return {"phi": new[0], "u": [x[0] for x in un], "p": pn[0], "mu": mu[0]}
+    phis = ini["phi"] if isinstance(ini["phi"], list) else [ini["phi"]]
+    new, un, pn, mus = _step(o, pr, [one(q) for q in phis], u, None if p.lid is None else one(p.lid))
+    several = len(phis) > 1
+    return {"phi": [q[0] for q in new] if several else new[0][0], "u": [x[0] for x in un], "p": pn[0],
+            "mu": [q[0] for q in mus] if several else mus[0][0]}
