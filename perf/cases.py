@@ -500,13 +500,14 @@ class _Momentum:
 
 
 def _cg(op, b, c):
-    """Preconditioned conjugate gradients to rounding, restarted on the true residual."""
+    """Preconditioned conjugate gradients to rounding, restarted on the true
+    residual; a member of the batch that is solved stays as it is."""
     dot = lambda x, y: (x * y).sum(op.o.dims, keepdim=True)  # noqa: E731
     b = op.project(b)
     x, bb = torch.zeros_like(b), dot(b, b).clamp_min(1e-300)
     for _ in range(3):
         r = op.project(b - op.apply(x, *c))
-        p, rz = None, None
+        p, rz, open_ = None, None, dot(r, r) > 1e-31 * bb
         for it in range(1500):
             z = op.project(op.precondition(r, c))
             new = dot(r, z)
@@ -514,9 +515,10 @@ def _cg(op, b, c):
             rz = new
             q = op.apply(p, *c)
             pq = dot(p, q)
-            alpha = torch.where(pq > 0, rz / pq, torch.zeros_like(pq))
+            alpha = torch.where(open_ & (pq > 0), rz / pq, torch.zeros_like(pq))
             x, r = x + alpha * p, r - alpha * q
-            if it % 20 == 19 and float((dot(r, r) / bb).max()) < 1e-29:
+            open_ = open_ & (dot(r, r) > 1e-31 * bb)
+            if it % 20 == 19 and not bool(open_.any()):
                 break
     return op.project(x)
 
