@@ -501,6 +501,16 @@ constexpr int kMX = 32, kMY = kBlock / kMX, kMW = kMX + 2, kMH = kMY + 2;
 #define CHNS_MARCH_PLANES 8
 #endif
 constexpr int kMarchPlanes = CHNS_MARCH_PLANES;   // z planes per block (more on grids too large for the partials)
+// A block marches its planes one after another, so the apply is as long as
+// one block's chain unless the chip holds several blocks per CU: the planes
+// per block are halved until there are kMarchApplyBlocks blocks (96^3, FP64:
+// 432 blocks of 8 planes 21.4 us, 864 of 4 planes 18.1, 1728 of 2 planes
+// 17.5; a target of 2048 halves 128^3 too, 28.2 -> 31.1 us).  Below
+// kMarchApplyCells cells one cell per thread (k_pcg_apply_slot) has no chain
+// at all: 64^3 17.3 us marching 8 planes, 10.7 with 1024 blocks, 9.3
+// grid-stride; 32^3 14.8 / 6.3 / 5.5 us; 96^3 17.5 against 18.8 the other way.
+constexpr int kMarchApplyBlocks = 1024;
+constexpr long long kMarchApplyCells = 1LL << 19;
 // RHO (pressure operator): the face coefficients 1/(rho_f h^2) are formed
 // from the cell densities rho (a second ring of planes) with the set-up's
 // expression, instead of read as s and cs[3]: 8 bytes per cell instead of 32
@@ -1851,8 +1861,9 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
     } else {
         precond_rz();
     }
-    // 3D slot operator: the z-marching apply (8 planes per block, more when
-    // the grid would exceed the partial-sum slots)
+    // 3D slot operator: the z-marching apply (kMarchPlanes planes per block,
+    // fewer where that leaves the chip short of blocks, more when the grid
+    // would exceed the partial-sum slots)
     struct {
         int nb = 0, ncolx = 0, ncol = 0, zc = 0;
     } march;
@@ -1860,8 +1871,10 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
         const Geo &g0 = L0.g;
         march.ncolx = (g0.n[0] + kMX - 1) / kMX;
         march.ncol = march.ncolx * ((g0.n[1] + kMY - 1) / kMY);
-        if (march.ncol <= kMaxBlocks) {   // else the grid-stride apply
+        if (march.ncol <= kMaxBlocks && g0.N >= kMarchApplyCells) {   // else the grid-stride apply
             march.zc = kMarchPlanes;
+            while (march.zc > 1 && march.ncol * ((g0.n[2] + march.zc - 1) / march.zc) < kMarchApplyBlocks)
+                march.zc /= 2;
             while (march.zc < g0.n[2] && (long long)march.ncol * ((g0.n[2] + march.zc - 1) / march.zc) > kMaxBlocks)
                 march.zc *= 2;
             march.nb = march.ncol * ((g0.n[2] + march.zc - 1) / march.zc);
