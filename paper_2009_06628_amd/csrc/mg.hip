@@ -352,8 +352,8 @@ __global__ void __launch_bounds__(kSBThreads) k_vcycle_lds(Slot<T> S, int l0, Ld
 
 template <typename T, int DIM>
 __global__ void __launch_bounds__(kSBThreads) k_setup_block(Slot<T> S, int l0) {
-    __shared__ SetupLdsPP sh;
-    setup_block_dev<T, DIM>(S, l0, sh);
+    __shared__ SetupLdsLev<T, DIM> sh;
+    setup_lds_dev<T, DIM>(S, l0, sh);
 }
 
 template <typename T, int DIM>

@@ -708,87 +708,105 @@ __device__ inline void gauss_jordan_inplace(double *A, int n, double *f, double 
     __syncthreads();
 }
 
-// Gauss-Jordan inversion as above with one barrier per pivot: pivot step k
-// reads the whole matrix from src and writes the next one to dst (the same
-// arithmetic per entry, in the same order), then the two swap.  src and dst
-// are n x n arrays; returns the one holding the inverse.  Block-wide; ends
-// with a workgroup barrier.  (n = 32: 19 us against 27 us for the in-place
-// form, which waits on three barriers and a one-thread step per pivot; one
-// wave alone with wavefront fences took 101 us.)
-__device__ inline double *gauss_jordan_pingpong(double *src, double *dst, int n, double *rp) {
-    // Each thread steps its entries' (i, j) by the stride instead of dividing
-    // e by n per pivot, and the thread that writes the next pivot entry also
-    // stores its reciprocal (rp, two slots by pivot parity), so the other
-    // threads read 1 / a_kk instead of each dividing (the same division of
-    // the same value: results unchanged; whole set-up kernel with n = 32:
-    // 34.7 -> 30.8 us, with n = 64 in 3D: 129 -> 108 us).
-    const int nn = n * n, bd = (int)blockDim.x, tid = (int)threadIdx.x;
-    const int di = bd / n, dj = bd - di * n;
-    const int i0 = tid / n, j0 = tid - i0 * n;
-    if (tid == 0) rp[0] = 1.0 / src[0];
+// Gauss-Jordan inversion as above with the matrix in registers: thread
+// (ti, tj) of the first 256 holds the entries (ti + 16 p, tj + 16 q), p, q <
+// NB (n <= 16 NB; entries past n are 0 and stay 0), and only the pivot row,
+// the pivot column and the pivot's reciprocal go through LDS, in two slots by
+// pivot parity: one barrier per pivot.  The chain of a pivot is one LDS read,
+// two multiply-adds, a division and one LDS write; with the matrix in LDS
+// (read and written once per pivot, 96 KB of LDS traffic for n = 64) a pivot
+// took 1.2 us at n = 64.  Block-wide (at least 256 threads); A (n x n, LDS)
+// is replaced by its inverse.  Ends with a workgroup barrier.
+struct GjLds {
+    double row[2][kLdsInverse], col[2][kLdsInverse], rp[2];
+};
+template <int NB>
+__device__ inline void gauss_jordan_regs(double *A, int nn, GjLds &g) {
+    const int n = __builtin_amdgcn_readfirstlane(nn);   // pivot tests in scalar registers
+    const int tid = (int)threadIdx.x, ti = tid >> 4, tj = tid & 15;
+    const bool on = tid < 256;
+    double a[NB][NB];
+#pragma unroll
+    for (int p = 0; p < NB; ++p)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const int i = ti + 16 * p, j = tj + 16 * q;
+            a[p][q] = on && i < n && j < n ? A[i * n + j] : 0.0;
+        }
+    if (tid < kLdsInverse) {
+        g.row[0][tid] = tid == 0 ? 1.0 : (tid < n ? A[tid] : 0.0);   // 1 at the pivot: the scaled row holds its reciprocal there
+        g.col[0][tid] = tid < n ? A[tid * n] : 0.0;
+        if (tid == 0) g.rp[0] = 1.0 / A[0];
+    }
     __syncthreads();
     for (int k = 0; k < n; ++k) {
-        const double p = rp[k & 1];
-        const int kn = k + 1;
-        int i = i0, j = j0;
-        for (int e = tid; e < nn; e += bd) {
-            const double akj = j == k ? p : src[k * n + j] * p;   // the scaled pivot row
-            const double v = i == k ? akj : (j == k ? -src[i * n + k] * p : src[e] - src[i * n + k] * akj);
-            dst[e] = v;
-            if (i == kn && j == kn) rp[kn & 1] = 1.0 / v;
-            i += di;
-            j += dj;
-            if (j >= n) {
-                j -= n;
-                ++i;
+        if (on) {
+            const int s = k & 1, kn = k + 1;
+            const double p = g.rp[s];
+            double c[NB], akj[NB];   // the pivot column, the scaled pivot row
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                c[q] = g.col[s][ti + 16 * q];
+                akj[q] = g.row[s][tj + 16 * q];
             }
+#pragma unroll
+            for (int q = 0; q < NB; ++q) akj[q] = akj[q] * p;
+#pragma unroll
+            for (int pi = 0; pi < NB; ++pi)
+#pragma unroll
+                for (int q = 0; q < NB; ++q) a[pi][q] = a[pi][q] - c[pi] * akj[q];
+            // column k, then row k, then the next pivot's row and column out
+            // (the block index of a pivot is the same in every thread)
+            const int kt = k & 15, kq = k >> 4, nt = kn & 15, nq = kn >> 4;
+#pragma unroll
+            for (int x = 0; x < NB; ++x)
+                if (x == kq) {
+                    if (tj == kt)
+#pragma unroll
+                        for (int pi = 0; pi < NB; ++pi) a[pi][x] = -c[pi] * p;
+                    if (ti == kt)
+#pragma unroll
+                        for (int q = 0; q < NB; ++q) a[x][q] = akj[q];
+                }
+#pragma unroll
+            for (int x = 0; x < NB; ++x)
+                if (x == nq) {
+                    if (ti == nt)
+#pragma unroll
+                        for (int q = 0; q < NB; ++q) g.row[s ^ 1][tj + 16 * q] = q == x && tj == nt ? 1.0 : a[x][q];
+                    if (tj == nt) {
+#pragma unroll
+                        for (int pi = 0; pi < NB; ++pi) g.col[s ^ 1][ti + 16 * pi] = a[pi][x];
+                        if (ti == nt) g.rp[s ^ 1] = 1.0 / a[x][x];
+                    }
+                }
         }
         __syncthreads();
-        double *t = src;
-        src = dst;
-        dst = t;
     }
-    return src;
+#pragma unroll
+    for (int p = 0; p < NB; ++p)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const int i = ti + 16 * p, j = tj + 16 * q;
+            if (on && i < n && j < n) A[i * n + j] = a[p][q];
+        }
+    __syncthreads();
 }
 
-// LDS of the set-up: room for CAP doubles of the coarsest matrix (which is
-// in LDS when it has at most kLdsInverse cells; with room for a second copy
-// the inverse takes one barrier per pivot), a scratch row, reduction slots
-// and the pivot.  SetupLds is the size kernels with other LDS use;
-// SetupLdsPP (64 KB more) is for the set-up kernels alone.
-template <int CAP>
-struct SetupLdsT {
-    double A[CAP];
+// LDS of the set-up: the coarsest matrix (in LDS when it has at most
+// kLdsInverse cells), a scratch row, reduction slots and the pivot.
+struct SetupLds {
+    double A[kLdsInverse * kLdsInverse];
     double f[kMaxCoarse];
     double red[kSBThreads / kWave];
     double piv;
 };
-using SetupLds = SetupLdsT<kLdsInverse * kLdsInverse>;
-using SetupLdsPP = SetupLdsT<2 * kLdsInverse * kLdsInverse>;
 
-// Set-up of the small levels in one workgroup: coarsen from level
-// max(l0,1) - 1 downwards, inverse diagonals, then the coarsest inverse
-// (in LDS when it has at most kLdsInverse cells, else in S.aug).  Ends with
-// a workgroup barrier.
-template <typename T, int DIM, int CAP>
-__device__ inline void setup_block_dev(const Slot<T> &S, int l0, SetupLdsT<CAP> &sh) {
-    double *A = sh.A, *f = sh.f, *red = sh.red;
-    double &piv = sh.piv;
-    const int L = S.nlev;
-    if (l0 == 0) {
-        BLOCK_LOOP(S.lev[0].g.N) invd_cell<T, DIM>(S.lev[0], c);
-        __syncthreads();
-    }
-    for (int l = (l0 > 1 ? l0 : 1); l < L; ++l) {
-        BLOCK_LOOP(S.lev[l].g.N) coarsen_cell<T, DIM>(S.lev[l - 1], S.lev[l], c);
-        __syncthreads();
-        BLOCK_LOOP(S.lev[l].g.N) invd_cell<T, DIM>(S.lev[l], c);
-        __syncthreads();
-    }
-    // dense coarsest operator
-    const Level<T> &C = S.lev[L - 1];
+// The dense operator of the coarsest level C into M (n x n), shifted by the
+// mean of its trace / n for a singular slot.  Block-wide; ends with a barrier.
+template <typename T, int DIM>
+__device__ inline void coarse_matrix_block(const Level<T> &C, int singular, double *M, double *red) {
     const int n = (int)C.g.N;
-    double *M = n <= kLdsInverse ? A : S.aug;
     for (int e = threadIdx.x; e < n * n; e += blockDim.x) M[e] = 0.0;
     __syncthreads();
     double dsum = 0.0;
@@ -814,15 +832,105 @@ __device__ inline void setup_block_dev(const Slot<T> &S, int l0, SetupLdsT<CAP> 
         dsum += d;
     }
     const double tot = block_sum_all(dsum, red);
-    if (S.singular) {
+    if (singular) {
         const double tau = (tot / n) / n;
         for (int e = threadIdx.x; e < n * n; e += blockDim.x) M[e] += tau;
     }
-    // in LDS with room for a second copy: one barrier per pivot
-    if (M == A && 2 * n * n <= CAP)
-        M = gauss_jordan_pingpong(A, A + n * n, n, f);
+    __syncthreads();
+}
+
+// Set-up of the small levels in one workgroup: coarsen from level
+// max(l0,1) - 1 downwards, inverse diagonals, then the coarsest inverse
+// (in LDS when it has at most kLdsInverse cells, else in S.aug).  Ends with
+// a workgroup barrier.
+template <typename T, int DIM>
+__device__ inline void setup_block_dev(const Slot<T> &S, int l0, SetupLds &sh) {
+    const int L = S.nlev;
+    if (l0 == 0) {
+        BLOCK_LOOP(S.lev[0].g.N) invd_cell<T, DIM>(S.lev[0], c);
+        __syncthreads();
+    }
+    for (int l = (l0 > 1 ? l0 : 1); l < L; ++l) {
+        BLOCK_LOOP(S.lev[l].g.N) coarsen_cell<T, DIM>(S.lev[l - 1], S.lev[l], c);
+        __syncthreads();
+        BLOCK_LOOP(S.lev[l].g.N) invd_cell<T, DIM>(S.lev[l], c);
+        __syncthreads();
+    }
+    // dense coarsest operator
+    const int n = (int)S.lev[L - 1].g.N;
+    double *M = n <= kLdsInverse ? sh.A : S.aug;
+    coarse_matrix_block<T, DIM>(S.lev[L - 1], S.singular, M, sh.red);
+    gauss_jordan_inplace(M, n, sh.f, &sh.piv);
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) S.Ainv[e] = M[e];
+    __syncthreads();
+}
+
+// The same set-up (the same arithmetic per entry) for a slot whose coarsest
+// level has at most kLdsInverse cells, in at least 256 threads: the levels it
+// writes are also kept in LDS, where the next level's coarsening, the inverse
+// diagonals and the coarsest matrix read them (the global-memory form waits
+// for a round trip in each of these passes), and the coarsest matrix is
+// inverted in registers.  Falls back to setup_block_dev where that does not
+// apply (a larger coarsest level, or no level below the grid).
+// Whole set-up kernel, FP64, with the levels in memory and the matrix in LDS
+// before: 64^2 (n = 64) 89 -> 43 us, 256 x 512 (n = 32) 30 -> 23 us, 96^3
+// (n = 27) 38 -> 27 us, all bit for bit the same; 512 batched problems, FP32,
+// 134 -> 56 us.
+constexpr int kSetupLdsCells = kSBThreads * 2 * 4 / 3 + 32;   // all levels from 2 kSBThreads cells down (2D; fewer in 3D)
+template <typename T, int DIM>
+struct SetupLdsLev {
+    SetupLds base;
+    GjLds gj;
+    T lev[(1 + DIM) * kSetupLdsCells];
+};
+template <typename T, int DIM>
+__device__ inline void setup_lds_dev(const Slot<T> &S, int l0, SetupLdsLev<T, DIM> &sh) {
+    const int L = S.nlev, n = (int)S.lev[L - 1].g.N;
+    if (n > kLdsInverse || L < 2 || S.lev[l0 > 1 ? l0 : 1].g.N > 2 * kSBThreads) {
+        setup_block_dev<T, DIM>(S, l0, sh.base);
+        return;
+    }
+    if (l0 == 0) BLOCK_LOOP(S.lev[0].g.N) invd_cell<T, DIM>(S.lev[0], c);
+    const int l1 = l0 > 1 ? l0 : 1;
+    int off = 0;
+    auto image = [&](int l, int o) {   // level l with s, cs in LDS
+        Level<T> C = S.lev[l];
+        const int N = (int)C.g.N;
+        C.s = sh.lev + o;
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) C.cs[b] = sh.lev + o + (1 + b) * N;
+        return C;
+    };
+    auto publish = [&](const Level<T> &C, int l) {   // 1 / diag, and s, cs to the level's own arrays
+        BLOCK_LOOP(C.g.N) {
+            invd_cell<T, DIM>(C, c);
+            S.lev[l].s[c] = C.s[c];
+#pragma unroll
+            for (int b = 0; b < DIM; ++b) S.lev[l].cs[b][c] = C.cs[b][c];
+        }
+    };
+    Level<T> C = image(l1, 0);
+    BLOCK_LOOP(C.g.N) coarsen_cell<T, DIM>(S.lev[l1 - 1], C, c);
+    __syncthreads();
+    publish(C, l1);
+    for (int l = l1 + 1; l < L; ++l) {
+        const Level<T> F = image(l - 1, off);
+        off += (1 + DIM) * (int)F.g.N;
+        C = image(l, off);
+        BLOCK_LOOP(C.g.N) coarsen_cell<T, DIM>(F, C, c);
+        __syncthreads();
+        publish(C, l);
+    }
+    double *M = sh.base.A;
+    coarse_matrix_block<T, DIM>(image(L - 1, off), S.singular, M, sh.base.red);
+    if (n <= 16)
+        gauss_jordan_regs<1>(M, n, sh.gj);
+    else if (n <= 32)
+        gauss_jordan_regs<2>(M, n, sh.gj);
+    else if (n <= 48)
+        gauss_jordan_regs<3>(M, n, sh.gj);
     else
-        gauss_jordan_inplace(M, n, f, &piv);
+        gauss_jordan_regs<4>(M, n, sh.gj);
     for (int e = threadIdx.x; e < n * n; e += blockDim.x) S.Ainv[e] = M[e];
     __syncthreads();
 }

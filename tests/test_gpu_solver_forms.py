@@ -62,3 +62,15 @@ def solve_error(n, per, ratio=0.1, precision=0, seed=3):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_cg_apply_forms(n, per, precision):
     assert solve_error(n, per, precision=precision) <= 1e-9
+
+
+# coarsest levels of 15, 32, 45, 60, 64 cells (the register inverse with 1 to 4
+# entries per thread and axis), 121 (the in-place inverse in memory) and grids
+# that are their own coarsest level or one above it
+@pytest.mark.parametrize("n,per", [((40, 24), (True, False)), ((64, 128), (False, True)), ((36, 20), (True, True)),
+                                   ((48, 80), (False, False)), ((64, 64), (True, True)), ((44, 44), (True, False)),
+                                   ((8, 8), (True, True)), ((16, 16), (False, False)), ((24, 24, 24), (True, False, True)),
+                                   ((32, 32, 64), (True, True, True))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_coarse_setup_forms(n, per, precision):
+    assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
