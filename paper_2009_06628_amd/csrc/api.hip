@@ -215,6 +215,7 @@ void layout(Bump &B, const Plan &P, chns_grid *g, int prec) {
     g->vp1 = B.take<double>(N);
     g->vq = B.take<double>(N);
     g->vt = B.take<double>(N);
+    g->vw = P.dim == 2 ? B.take<double>(N) : nullptr;
     carve_slot(B, P, g->ch, 0);
     carve_slot(B, P, g->mom, 0);
     carve_slot(B, P, g->pres, 1);
@@ -241,9 +242,9 @@ void layout(Bump &B, const Plan &P, chns_grid *g, int prec) {
     g->red.part0 = B.take<double>(kMaxBlocks);
     g->red.part1 = B.take<double>(kMaxBlocks);
     g->red.part2 = B.take<double>(kMaxBlocks);
-    g->red.rz0 = B.take<double>(kRedBlocks);
-    g->red.rz1 = B.take<double>(kRedBlocks);
-    g->red.rz2 = B.take<double>(kRedBlocks);
+    g->red.rz0 = B.take<double>(kMaxBlocks);
+    g->red.rz1 = B.take<double>(kMaxBlocks);
+    g->red.rz2 = B.take<double>(kMaxBlocks);
     g->diag = B.take<double>(kDiagSlots * (size_t)kMaxBlocks + 16);
     g->red.counter = B.take<unsigned int>(64);
     g->red.scal = B.take<Scal>(1);
@@ -257,6 +258,7 @@ void layout(Bump &B, const Plan &P, chns_grid *g, int prec) {
         M.vp1 = B.take<double>(N);
         M.vq = B.take<double>(N);
         M.vt = B.take<double>(N);
+        M.vw = P.dim == 2 ? B.take<double>(N) : nullptr;
         carve_slot(B, P, M.mom, 0);
         double *maug = nc > kLdsInverse ? B.take<double>((size_t)nc * nc) : nullptr;
         M.mom.aug = maug;
@@ -272,9 +274,9 @@ void layout(Bump &B, const Plan &P, chns_grid *g, int prec) {
         M.red.part0 = B.take<double>(kMaxBlocks);
         M.red.part1 = B.take<double>(kMaxBlocks);
         M.red.part2 = B.take<double>(kMaxBlocks);
-        M.red.rz0 = B.take<double>(kRedBlocks);
-        M.red.rz1 = B.take<double>(kRedBlocks);
-        M.red.rz2 = B.take<double>(kRedBlocks);
+        M.red.rz0 = B.take<double>(kMaxBlocks);
+        M.red.rz1 = B.take<double>(kMaxBlocks);
+        M.red.rz2 = B.take<double>(kMaxBlocks);
         M.red.counter = B.take<unsigned int>(64);
         M.red.scal = B.take<Scal>(1);
     }
@@ -283,7 +285,7 @@ void layout(Bump &B, const Plan &P, chns_grid *g, int prec) {
 
 StepConst step_const(const chns_grid *g) { return step_const_of(g->props, g->h); }
 
-PcgVecs<double> vecs(chns_grid *g) { return PcgVecs<double>{g->vr, g->vz, g->vp0, g->vp1, g->vq, g->vt}; }
+PcgVecs<double> vecs(chns_grid *g) { return PcgVecs<double>{g->vr, g->vz, g->vp0, g->vp1, g->vq, g->vt, g->vw}; }
 
 int next_predict(int last) { return last < 1 ? 1 : last; }
 
@@ -344,7 +346,7 @@ hipError_t run_solve_ctx(chns_grid *g, const SolveCtx &c, int setup, OpKind kind
         return e;
     }
     Slot<float> &S32 = *c.S32;
-    const PcgVecs2<double, float> v2{v.r, v.p0, v.p1, v.q, v.t, c.f_z, c.f_t, c.f_r};
+    const PcgVecs2<double, float> v2{v.r, v.p0, v.p1, v.q, v.t, c.f_z, c.f_t, c.f_r, v.w};
     return refine_solve(S64, S32, g->dim, kind, ch, b, x, rtol, g->props.max_iter, &g->last_inner[pidx], red, v2,
                         c.s, o, conv0);
 }
@@ -401,7 +403,7 @@ SolveCtx mom_ctx(chns_grid *g, int a) {
     SolveCtx c;
     c.S64 = &M.mom;
     c.S32 = &M.mom32;
-    c.v = PcgVecs<double>{M.vr, M.vz, M.vp0, M.vp1, M.vq, M.vt};
+    c.v = PcgVecs<double>{M.vr, M.vz, M.vp0, M.vp1, M.vq, M.vt, M.vw};
     c.f_z = M.f_z;
     c.f_t = M.f_t;
     c.f_r = M.f_r;

@@ -190,6 +190,7 @@ __device__ inline double sum_partials(const double *part, int nparts, double *ld
 struct Scal {
     double rz, pq, rr, bb, alpha, beta, rtol2, sum0, sum1, zmean;
     double rzs[2];   // single-grid PCG: r.z of iteration k in rzs[k & 1]
+    double als[2];   // 2D single-grid PCG: the step length of iteration k in als[k & 1]
     int done, iter, max_iter, nonfinite;
     int unconverged, pad0, pad1, pad2;
 };
@@ -240,7 +241,7 @@ constexpr long long kTileCycleCells = 1LL << 18;
 // Reduction scratch shared by all solves of a handle.
 struct Red {
     double *part0, *part1, *part2;   // kMaxBlocks partials each
-    double *rz0, *rz1, *rz2;         // kRedBlocks partials each: r.z, sum z, sum r
+    double *rz0, *rz1, *rz2;         // r.z, sum z, sum r: kRedBlocks partials each (kMaxBlocks in a grid handle)
     unsigned int *counter;     // last-block counters (several)
     Scal *scal;                // device scalars
 };
@@ -317,7 +318,7 @@ struct MomCtx {
     Slot<double> mom;
     Slot<float> mom32;
     double *rhs;
-    double *vr, *vz, *vp0, *vp1, *vq, *vt;
+    double *vr, *vz, *vp0, *vp1, *vq, *vt, *vw;   // vw: 2D only
     float *f_z, *f_t, *f_r;
     Red red;
     hipStream_t stream;
@@ -365,7 +366,7 @@ struct chns_grid {
     double *phi_new2, *phihat2, *rch2;       // the second stored phase (nph == 3)
     double *mix3[5];                         // per-step mixture fields (nph == 3)
     double *mflux3[3];                       // per-step face mass fluxes (nph == 3)
-    double *vr, *vz, *vp0, *vp1, *vq, *vt;   // PCG vectors
+    double *vr, *vz, *vp0, *vp1, *vq, *vt, *vw;   // PCG vectors (vw: 2D only)
     chns::Slot<double> ch, mom, pres;
     // precision form (FP32 inner solves under FP64 refinement)
     int prec;

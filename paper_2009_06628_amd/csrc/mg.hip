@@ -322,6 +322,31 @@ __global__ void __launch_bounds__(kTileThreads) k_up_tile2_cg(Level<T> L, Geo gc
         up_tile2<T, kTileThreads>(L, gc, xc, RhsStored<T>{b}, xs, x, tx, ty, skip, d);
 }
 
+// Level 0 of a solve with one reduction point per iteration (tile2d.h).
+template <typename T, typename TR>
+__global__ void __launch_bounds__(kTileThreads) k_cg_down_tile2(Level<T> L, Geo gc, CgVec2<TR> v,
+                                                                const T *__restrict__ z, T *__restrict__ xs,
+                                                                T *__restrict__ bc, int ntx, int ntiles, int k,
+                                                                int singular, Scal *sc, CgPart pt,
+                                                                double *__restrict__ part_rr) {
+    const int tile = xcd_block();
+    if (tile >= ntiles) return;
+    const int ty = tile / ntx, tx = tile - ty * ntx;
+    cg_down_tile2<T, TR>(L, gc, v, z, xs, bc, tx, ty, tile, k, singular, sc, pt, ntiles, part_rr);
+}
+
+template <typename T, typename TR>
+__global__ void __launch_bounds__(kTileThreads) k_cg_up_tile2(Level<T> L, Geo gc, const T *__restrict__ xc,
+                                                              const TR *__restrict__ r, const T *__restrict__ xs,
+                                                              T *__restrict__ z, TR *__restrict__ w, Level<TR> A,
+                                                              int ntx, int ntiles, int singular, CgPart pt,
+                                                              const int *__restrict__ done) {
+    const int tile = xcd_block();
+    if (tile >= ntiles) return;
+    const int ty = tile / ntx, tx = tile - ty * ntx;
+    cg_up_tile2<T, TR>(L, gc, xc, r, xs, z, w, A, tx, ty, tile, singular, pt, *done);
+}
+
 // ---------------------------------------------------------------------------
 // single-workgroup kernels for the small levels
 // ---------------------------------------------------------------------------
@@ -332,18 +357,52 @@ __global__ void __launch_bounds__(kSBThreads) k_vcycle_block(Slot<T> S, int l0, 
     vcycle_block_dev<T, TB, DIM>(S, l0, b0, x0);
 }
 
+// End of a CG iteration: r.r, the iteration count and the stop flags (thread 0)
+__device__ inline void pcg_fin_rr_dev(Scal *sc, double rr) {
+    if (threadIdx.x != 0) return;
+    sc->rr = rr;
+    sc->iter += 1;
+    if (!isfinite(rr)) {
+        sc->nonfinite = 1;
+        sc->done = 1;
+    } else if (rr <= sc->rtol2 * sc->bb) {
+        sc->done = 1;
+    } else if (sc->iter >= sc->max_iter) {
+        sc->unconverged = 1;
+        sc->done = 1;
+    }
+}
+
 // Levels [l0, nlev) out of LDS: the segments cp of their contiguous storage
-// are copied in, x of level l0 is written back.
+// are copied in, x of level l0 is written back.  fin (when given): the CG
+// update of this iteration left nfin partials of r.r there and its end
+// (pcg_fin_rr_dev) is taken here, in the one workgroup every cycle passes
+// through, instead of in a launch of its own; the cycle that follows the
+// last update is completed for nothing.
 template <typename T, int DIM>
 __global__ void __launch_bounds__(kSBThreads) k_vcycle_lds(Slot<T> S, int l0, LdsCopy cp,
-                                                           const int *__restrict__ done) {
+                                                           const int *__restrict__ done, Scal *fsc,
+                                                           const double *__restrict__ fin, int nfin) {
     const int dn = *done;   // tested after the copy (which only reads memory and writes LDS)
     extern __shared__ uint4 lds_words[];
     char *lds = (char *)lds_words;
     const char *base = (const char *)S.lev[l0].s;
+    double rr = 0.0;
+    for (int i = (int)threadIdx.x; i < nfin; i += kSBThreads) rr += fin[i];
     copy_to_lds(lds_words, (const uint4 *)base, cp);
     if (dn) return;
     __syncthreads();
+    if (nfin) {   // scratch: the residual array of level l0 (at least 256 cells, not read before it is written)
+        double *ws = (double *)lds_image(lds, base, S.lev[l0].r);
+        rr = wave_sum(rr);
+        if ((threadIdx.x & (kWave - 1)) == 0) ws[threadIdx.x / kWave] = rr;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            rr = 0.0;
+            for (int q = 0; q < kSBThreads / kWave; ++q) rr += ws[q];
+            pcg_fin_rr_dev(fsc, rr);
+        }
+    }
     vcycle_lds_dev<T, DIM>(S, l0, lds, base);
     const T *xl = lds_image(lds, base, S.lev[l0].x);
     T *xg = S.lev[l0].x;
@@ -1196,22 +1255,6 @@ __global__ void __launch_bounds__(kBlock) k_pcg_ch_apply(Geo g, double ih2, doub
     if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// End of CG iteration: r.r, the iteration count and the stop flags (thread 0)
-__device__ inline void pcg_fin_rr_dev(Scal *sc, double rr) {
-    if (threadIdx.x != 0) return;
-    sc->rr = rr;
-    sc->iter += 1;
-    if (!isfinite(rr)) {
-        sc->nonfinite = 1;
-        sc->done = 1;
-    } else if (rr <= sc->rtol2 * sc->bb) {
-        sc->done = 1;
-    } else if (sc->iter >= sc->max_iter) {
-        sc->unconverged = 1;
-        sc->done = 1;
-    }
-}
-
 // alpha = rz / sum(part_pq) (every block, same order); x += alpha p;
 // r -= alpha q; partial r.r.  TP != T: also rp = r rounded to TP (the
 // right-hand side of the preconditioner in its own precision).
@@ -1685,6 +1728,41 @@ static void vcycle_up(Slot<T> &S, int l, const TB *b, T *x, const int *done, hip
     }
 }
 
+// The levels [S.lsb, nlev) in one workgroup; b0 / x0: right-hand side and
+// result of level 0 where the whole grid is among them.  fin: partials of
+// r.r that end the CG iteration of sc (0: none).
+template <typename T, typename TB, int DIM>
+static void vcycle_small(Slot<T> &S, const TB *b0, T *x0, const int *done, hipStream_t st, Scal *sc = nullptr,
+                         const double *fin = nullptr, int nfin = 0) {
+    constexpr double W = sizeof(T);
+    const int lsb = S.lsb;
+    // storage of the small levels: one contiguous range from lev[lsb].s
+    // to the end of the coarsest inverse
+    const size_t range16 = lds_vcycle_bytes(S, lsb);
+    if (range16) {
+        // the range is read once and x of level lsb written back
+        static const bool attr = [] {   // once per instantiation, thread-safe
+            (void)hipFuncSetAttribute((const void *)k_vcycle_lds<T, DIM>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      kLdsVcycleBytes);
+            return true;
+        }();
+        (void)attr;
+        const LdsCopy cp = lds_copy_plan(S, lsb);
+        const double bytes = 16.0 * cp.total + W * S.lev[lsb].g.N + 8.0 * nfin;
+        TLAUNCHS(K_COARSE_SOLVE, bytes, (k_vcycle_lds<T, DIM>), dim3(1), dim3(kSBThreads), range16, st, S, lsb, cp, done,
+                 sc, fin, nfin);
+        return;
+    }
+    if (nfin) LAUNCH1(K_PCG_UPDATE, 8.0 * nfin, (k_pcg_fin_rr), kBlock, st, sc, fin, nfin);
+    double bytes = 8.0 * S.ncoarse * S.ncoarse;
+    for (int l = lsb; l < S.nlev; ++l) bytes += W * 12.0 * S.lev[l].g.N;
+    if (lsb == 0)
+        LAUNCH1(K_COARSE_SOLVE, bytes, (k_vcycle_block<T, TB, DIM>), kSBThreads, st, S, 0, b0, x0, done);
+    else
+        LAUNCH1(K_COARSE_SOLVE, bytes, (k_vcycle_block<T, T, DIM>), kSBThreads, st, S, lsb, (const T *)S.lev[lsb].b,
+                S.lev[lsb].x, done);
+}
+
 // One V-cycle of slot S: x0 ~ A^{-1} b0 (b0 may be stored in another
 // precision than the hierarchy).
 template <typename T, typename TB, int DIM, typename TR = T>
@@ -1723,32 +1801,7 @@ static void vcycle_d(Slot<T> &S, const TB *b0, T *x0, const int *done, hipStream
         vcycle_down<T, TB, DIM, TR>(S, 0, b0, x0, done, st, cg);
         for (int l = 1; l < lsb; ++l) vcycle_down<T, T, DIM>(S, l, S.lev[l].b, S.lev[l].x, done, st);
     }
-    {
-        // storage of the small levels: one contiguous range from lev[lsb].s
-        // to the end of the coarsest inverse
-        const size_t range16 = lds_vcycle_bytes(S, lsb);
-        if (range16) {
-            // the range is read once and x of level lsb written back
-            static const bool attr = [] {   // once per instantiation, thread-safe
-                (void)hipFuncSetAttribute((const void *)k_vcycle_lds<T, DIM>,
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, kLdsVcycleBytes);
-                return true;
-            }();
-            (void)attr;
-            const LdsCopy cp = lds_copy_plan(S, lsb);
-            const double bytes = 16.0 * cp.total + W * S.lev[lsb].g.N;
-            TLAUNCHS(K_COARSE_SOLVE, bytes, (k_vcycle_lds<T, DIM>), dim3(1), dim3(kSBThreads), range16, st, S, lsb,
-                     cp, done);
-        } else {
-            double bytes = 8.0 * S.ncoarse * S.ncoarse;
-            for (int l = lsb; l < S.nlev; ++l) bytes += W * 12.0 * S.lev[l].g.N;
-            if (lsb == 0)
-                LAUNCH1(K_COARSE_SOLVE, bytes, (k_vcycle_block<T, TB, DIM>), kSBThreads, st, S, 0, b0, x0, done);
-            else
-                LAUNCH1(K_COARSE_SOLVE, bytes, (k_vcycle_block<T, T, DIM>), kSBThreads, st, S, lsb,
-                        (const T *)S.lev[lsb].b, S.lev[lsb].x, done);
-        }
-    }
+    vcycle_small<T, TB, DIM>(S, b0, x0, done, st);
     if (lsb > 0) {
         for (int l = lsb - 1; l >= 1; --l) vcycle_up<T, T, DIM>(S, l, S.lev[l].b, S.lev[l].x, done, st);
         vcycle_up<T, TB, DIM, TR>(S, 0, b0, x0, done, st, cg, rz);
@@ -1793,6 +1846,45 @@ static void precond_cg_d(Slot<TP> &SP, OpKind kind, const TP *r, TP *z, TP *w, c
     } else {
         vcycle_d<TP, TP, DIM, TR>(SP, r, z, done, st, &cg);
     }
+}
+
+// Tiles up to which a 2D solve takes the form with one reduction point per
+// iteration: every tile of its way down sums four partials per tile (64 KB
+// of L2 reads per tile at the limit; at 1152 tiles, 768^2, the step still
+// gains: 2133 -> 2051 us).
+constexpr int kCgTiles = 2048;
+
+// The preconditioner of iteration k of such a solve, and the update before
+// it (k < 0: the first one, from the initial residual b0; no update): level 0
+// through cg_down_tile2 / cg_up_tile2, the levels below as in vcycle_d.
+template <typename TP, typename TR>
+static void cg_cycle2(Slot<TP> &SP, const Level<TR> &A, const TP *b0, TP *z, const PcgVecs2<TR, TP> &v, TR *x, int k,
+                      const Red &red, hipStream_t st) {
+    constexpr double W = sizeof(TP), WR = sizeof(TR);
+    Level<TP> &lv = SP.lev[0];
+    const Geo &gc = SP.lev[1].g;
+    const double N = (double)lv.g.N, Nc = (double)gc.N;
+    const int *done = &red.scal->done;
+    const CgPart pt{red.rz0, red.rz1, red.rz2, red.part0};
+    TR *const R[2] = {v.r, v.p1}, *const Sv[2] = {v.q, v.t};
+    int ntx, ntiles, grid;
+    tile_grid2(lv.g, ntx, ntiles, grid);
+    if (k < 0) {
+        vcycle_down<TP, TP, 2>(SP, 0, b0, z, done, st);
+    } else {
+        const CgVec2<TR> cv{R[k & 1], Sv[k & 1], v.az, R[(k + 1) & 1], Sv[(k + 1) & 1], v.p0, x};
+        // r, s, w, p, x, z in; r, s, p, x out; invd, s, cs in; x, bc out
+        TLAUNCH(K_MG_DOWN, (9.0 * WR + W) * N + W * 5 * N + W * Nc, (k_cg_down_tile2<TP, TR>), dim3(grid),
+                dim3(kTileThreads), st, lv, gc, cv, (const TP *)z, lv.r, SP.lev[1].b, ntx, ntiles, k, SP.singular,
+                red.scal, pt, red.part1);
+    }
+    for (int l = 1; l < SP.lsb; ++l) vcycle_down<TP, TP, 2>(SP, l, SP.lev[l].b, SP.lev[l].x, done, st);
+    vcycle_small<TP, TP, 2>(SP, b0, z, done, st, red.scal, (const double *)red.part1, k < 0 ? 0 : ntiles);
+    for (int l = SP.lsb - 1; l >= 1; --l) vcycle_up<TP, TP, 2>(SP, l, SP.lev[l].b, SP.lev[l].x, done, st);
+    // r, x, invd, cs, xc in; z, w out; the CG's own s, cs where they differ
+    TLAUNCH(K_MG_UP, 2.0 * WR * N + W * 5 * N + W * Nc + (W < WR ? 3.0 * WR * N : 0.0), (k_cg_up_tile2<TP, TR>),
+            dim3(grid), dim3(kTileThreads), st, lv, gc, (const TP *)SP.lev[1].x, (const TR *)R[(k + 1) & 1],
+            (const TP *)lv.r, z, v.az, A, ntx, ntiles, SP.singular, pt, done);
 }
 
 // PCG in precision T (operator SA level 0, vectors, updates) preconditioned
@@ -1852,11 +1944,16 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
         int ntx, grid;
         tile_grid2(SP.lev[0].g, ntx, ntiles0, grid);
     }
-    const bool fuse = DIM == 2 && SP.lsb > 0 && ntiles0 <= kRedBlocks;
+    // one reduction point per iteration: the operator apply rides on the
+    // preconditioner's last pass as well
+    const bool one = DIM == 2 && kind == OP_SLOT && SP.lsb > 0 && v.az && ntiles0 <= kCgTiles;
+    const bool fuse = !one && DIM == 2 && SP.lsb > 0 && ntiles0 <= kRedBlocks;
     const int nrz = fuse ? ntiles0 : nb;
     L0Cg<T> cg{0, 0, 1, (const T *)v.r, (const T *)v.q, nullptr, x, sc, (const double *)red.part0, nb,
                red.part1, red.rz0, red.rz1, red.rz2};
-    if (fuse) {
+    if (one) {
+        if constexpr (DIM == 2) cg_cycle2<TP, T>(SP, L0, rpre, v.z, v, x, -1, red, st);
+    } else if (fuse) {
         precond_cg_d<TP, DIM, T>(SP, kind, rpre, v.z, v.w, done, st, cg);
     } else {
         precond_rz();
@@ -1886,6 +1983,10 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
         if (chunk > max_iter - launched) chunk = max_iter - launched;
         for (int it = 0; it < chunk; ++it) {
             const int k = launched + it;
+            if (one) {
+                if constexpr (DIM == 2) cg_cycle2<TP, T>(SP, L0, rpre, v.z, v, x, k, red, st);
+                continue;
+            }
             T *pnew = (k & 1) ? v.p1 : v.p0;
             T *pold = (k & 1) ? v.p0 : v.p1;
             // the consumer of the r.z partials starts the iteration (beta);
@@ -1951,7 +2052,7 @@ template <typename T>
 hipError_t pcg_solve(Slot<T> &S, int dim, OpKind kind, ChOp ch, const T *b, T *x, double rtol, int max_iter,
                      int predict, Red &red, PcgVecs<T> &v, hipStream_t st, SolveOut *out, int zero_guess,
                      int conv0) {
-    const PcgVecs2<T, T> v2{v.r, v.p0, v.p1, v.q, v.t, v.z, v.t, nullptr};
+    const PcgVecs2<T, T> v2{v.r, v.p0, v.p1, v.q, v.t, v.z, v.t, nullptr, v.w};
     if (dim == 2)
         return pcg_d<T, T, 2>(S, S, kind, ch, b, x, rtol, max_iter, predict, red, v2, st, out, zero_guess, conv0);
     return pcg_d<T, T, 3>(S, S, kind, ch, b, x, rtol, max_iter, predict, red, v2, st, out, zero_guess, conv0);

@@ -11,9 +11,12 @@ constexpr int kSBCells = 2048;
 
 enum OpKind { OP_SLOT = 0, OP_CH = 1 };
 
+// w: A z of the 2D form whose operator apply rides on the preconditioner
+// (null: that form is not used).
 template <typename T>
 struct PcgVecs {
     T *r, *z, *p0, *p1, *q, *t;
+    T *w = nullptr;
 };
 
 // PCG vectors in precision T with the preconditioned vector z and the
@@ -23,6 +26,7 @@ struct PcgVecs2 {
     T *r, *p0, *p1, *q, *t;
     TP *z, *w;
     TP *rp;   // the residual rounded to the preconditioner's precision (TP != T only)
+    T *az = nullptr;   // A z (PcgVecs::w)
 };
 
 struct SolveOut {

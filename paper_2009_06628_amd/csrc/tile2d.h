@@ -140,13 +140,23 @@ struct RzDots {
 // Writes the smoothed x of the tile to xs (the level's residual array, which
 // no longer holds a residual: the way up reads x from there while it writes
 // the level's x) and bc on the tile's coarse cells.
+constexpr int kDownH = 3, kDownWX = kTFX + 2 * kDownH, kDownWY = kTFY + 2 * kDownH, kDownNL = kDownWX * kDownWY;
+template <typename T>
+struct DownTile {
+    T sB[kDownNL], sI[kDownNL], sS[kDownNL], sC0[kDownNL], sC1[kDownNL], sX[kDownNL], sR[kDownNL];
+};
+
+// The passes of the way down on a staged tile (sB .. sC1 filled, barrier done).
+template <typename T, int NT>
+__device__ inline void down_passes2(DownTile<T> &t, const Level<T> &L, const Geo &gc, T *__restrict__ xs,
+                                    T *__restrict__ bc, int tx, int ty);
+
 template <typename T, int NT, typename BS>
 __device__ inline void down_tile2(const Level<T> &L, const Geo &gc, const BS &b, T *__restrict__ xs,
                                   T *__restrict__ bc, int tx, int ty, int skip) {
-    using R = T;
-    constexpr int H = 3, WX = kTFX + 2 * H, WY = kTFY + 2 * H, NL = WX * WY;
+    constexpr int H = kDownH, WX = kDownWX, NL = kDownNL;
     constexpr int KL = (NL + NT - 1) / NT;   // staged cells per thread
-    __shared__ T sB[NL], sI[NL], sS[NL], sC0[NL], sC1[NL], sX[NL], sR[NL];
+    __shared__ DownTile<T> tile;
     const int nx = (int)L.g.n[0], ny = (int)L.g.n[1];
     const int px = L.g.per[0], py = L.g.per[1];
     const int gx0 = tx * kTFX - H, gy0 = ty * kTFY - H;
@@ -179,13 +189,25 @@ __device__ inline void down_tile2(const Level<T> &L, const Geo &gc, const BS &b,
     for (int k = 0; k < KL; ++k) {
         const int i0 = (int)threadIdx.x + k * NT, i = i0 < NL ? i0 : NL - 1;
         const T fv = lv[k] ? (T)1 : (T)0;
-        sB[i] = lb[k] * fv;
-        sI[i] = li[k] * fv;
-        sS[i] = ls[k] * fv;
-        sC0[i] = l0[k] * (m0[k] ? (T)1 : (T)0);
-        sC1[i] = l1[k] * (m1[k] ? (T)1 : (T)0);
+        tile.sB[i] = lb[k] * fv;
+        tile.sI[i] = li[k] * fv;
+        tile.sS[i] = ls[k] * fv;
+        tile.sC0[i] = l0[k] * (m0[k] ? (T)1 : (T)0);
+        tile.sC1[i] = l1[k] * (m1[k] ? (T)1 : (T)0);
     }
     __syncthreads();
+    down_passes2<T, NT>(tile, L, gc, xs, bc, tx, ty);
+}
+
+template <typename T, int NT>
+__device__ inline void down_passes2(DownTile<T> &t, const Level<T> &L, const Geo &gc, T *__restrict__ xs,
+                                    T *__restrict__ bc, int tx, int ty) {
+    using R = T;
+    constexpr int H = kDownH, WX = kDownWX, WY = kDownWY;
+    T *const sB = t.sB, *const sI = t.sI, *const sS = t.sS, *const sC0 = t.sC0, *const sC1 = t.sC1;
+    T *const sX = t.sX, *const sR = t.sR;
+    const int nx = (int)L.g.n[0], ny = (int)L.g.n[1];
+    const int gx0 = tx * kTFX - H, gy0 = ty * kTFY - H;
     // x on the tile and 2 halo cells (local [1, WX-1) x [1, WY-1), rows of
     // even width): the k-th red and the k-th black cell in one thread, so no
     // wave runs both colours' branches
@@ -328,6 +350,284 @@ __device__ inline void up_tile2(const Level<T> &L, const Geo &gc, const T *__res
         dots.add(gx + nx * gy, (double)v);
     }
     dots.template finish<NT>();
+}
+
+// ---------------------------------------------------------------------------
+// Level 0 of a 2D solve with one reduction point per CG iteration (Chronopoulos
+// and Gear's arrangement of conjugate gradients): the way up also forms
+// w = A z, so both inner products r.z and w.z are taken there, and the next
+// way down forms beta, alpha, p = z + beta p, s = w + beta s (= A p),
+// x += alpha p and r -= alpha s before it smooths.  The iterates are those of
+// the usual order in exact arithmetic; what goes is the launch of the
+// operator apply (5.4 us at 128 x 256, 6.9 us at 256 x 512, FP64), which on
+// these grids costs its latency, against 0.3 us more in each of the two tile
+// passes; the end of the iteration moves from a launch of its own (4.1 us)
+// into the single-workgroup coarse kernel.  Residuals and solutions agree
+// with the two-reduction form to rounding (density ratio 1000, 256 x 512:
+// the same iteration counts, true residuals within 1 %).
+// ---------------------------------------------------------------------------
+// Sums of four per-thread values over a workgroup of NT threads, in every
+// thread (fixed order: waves by shuffles, then the waves in order).
+template <int NT>
+__device__ inline void tile_sum4_all(double v[4], double (*ws)[NT / kWave]) {
+    const int lane = (int)threadIdx.x & (kWave - 1), w = (int)threadIdx.x / kWave;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        v[q] = wave_sum(v[q]);
+        if (lane == 0) ws[q][w] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        v[q] = 0.0;
+        for (int k = 0; k < NT / kWave; ++k) v[q] += ws[q][k];
+    }
+}
+
+// Partials per tile of the way up: r.z, sum z, sum r, w.z.
+struct CgPart {
+    double *rz, *z, *r, *wz;
+};
+// Vectors of the way down of iteration k (r, s: old; rn, sn: new, other
+// buffers, since neighbouring tiles read the old ones in their halos).
+template <typename TR>
+struct CgVec2 {
+    const TR *r, *s, *w;
+    TR *rn, *sn, *p, *x;
+};
+
+// One tile of the way down of CG iteration k: scalars, vector updates on the
+// tile's cells (one per thread), the partial of r.r, and the passes of
+// down_tile2 from the new residual.  The old s is not read for k = 0.
+template <typename T, typename TR>
+__device__ inline void cg_down_tile2(const Level<T> &L, const Geo &gc, const CgVec2<TR> &v, const T *__restrict__ z,
+                                     T *__restrict__ xs, T *__restrict__ bc, int tx, int ty, int tile_id, int k,
+                                     int singular, Scal *sc, const CgPart &pt, int nparts,
+                                     double *__restrict__ part_rr) {
+    constexpr int NT = kTileThreads, H = kDownH, WX = kDownWX, NL = kDownNL;
+    constexpr int KL = (NL + NT - 1) / NT;
+    static_assert(kTFX * kTFY == NT, "one owned cell per thread");
+    __shared__ DownTile<T> tile;
+    __shared__ double ws[4][NT / kWave], wr[NT / kWave];
+    const int tid = (int)threadIdx.x;
+    const int nx = (int)L.g.n[0], ny = (int)L.g.n[1];
+    const int px = L.g.per[0], py = L.g.per[1];
+    const int gx0 = tx * kTFX - H, gy0 = ty * kTFY - H;
+    // every load of the thread is issued before anything is waited for
+    const int dn = sc->done;
+    const double prev_rz = k > 0 ? sc->rzs[(k + 1) & 1] : 0.0, prev_al = k > 0 ? sc->als[(k + 1) & 1] : 0.0;
+    TR lr[KL], lw[KL], lo[KL];
+    T li[KL], ls[KL], l0[KL], l1[KL];
+    bool lv[KL], m0[KL], m1[KL];
+#pragma unroll
+    for (int q = 0; q < KL; ++q) {
+        const int i0 = tid + q * NT, i = i0 < NL ? i0 : NL - 1;
+        const int ly = i / WX, lx = i - ly * WX;
+        bool vx, vy;
+        const int gx = tile_coord(gx0 + lx, nx, px, vx), gy = tile_coord(gy0 + ly, ny, py, vy);
+        const bool in = vx && vy;
+        const int g = in ? gx + nx * gy : 0;
+        lr[q] = v.r[g];
+        lw[q] = v.w[g];
+        lo[q] = (TR)0;
+        if (k > 0) lo[q] = v.s[g];
+        li[q] = L.invd[g];
+        ls[q] = L.s[g];
+        l0[q] = L.cs[0][g];
+        l1[q] = L.cs[1][g];
+        lv[q] = in;
+        m0[q] = in && (px || gx > 0);
+        m1[q] = in && (py || gy > 0);
+    }
+    const int oy = tid / kTFX, ox = tid - oy * kTFX;
+    const int cx = tx * kTFX + ox, cy = ty * kTFY + oy;
+    const bool own = cx < nx && cy < ny;
+    const int c = own ? cx + nx * cy : 0;
+    const double oz = (double)z[c], oxx = (double)v.x[c], orr = (double)v.r[c], ow = (double)v.w[c];
+    double op = 0.0, os = 0.0;
+    if (k > 0) {
+        op = (double)v.p[c];
+        os = (double)v.s[c];
+    }
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = tid; i < nparts; i += NT) {
+        sum[0] += pt.rz[i];
+        sum[1] += pt.wz[i];
+        if (singular) {
+            sum[2] += pt.z[i];
+            sum[3] += pt.r[i];
+        }
+    }
+    if (dn) return;
+    tile_sum4_all<NT>(sum, ws);
+    // a singular operator's z is projected onto its range (mean removed); A z
+    // does not see the constant
+    const double zm = singular ? sum[2] / (double)L.g.N : 0.0;
+    const double rz = sum[0] - zm * sum[3];
+    const double beta = (k == 0 || prev_rz == 0.0) ? 0.0 : rz / prev_rz;
+    const double back = (k == 0 || prev_al == 0.0) ? 0.0 : beta * rz / prev_al;
+    const double pq = sum[1] - back;
+    const double alpha = pq != 0.0 ? rz / pq : 0.0;
+    const bool ok = isfinite(rz) && isfinite(alpha);
+    if (tile_id == 0 && tid == 0) {
+        if (ok) {
+            sc->rzs[k & 1] = rz;
+            sc->als[k & 1] = alpha;
+        } else {
+            sc->nonfinite = 1;
+            sc->done = 1;
+        }
+    }
+    if (!ok) return;
+    auto residual = [&](double r, double s) { return (TR)fma(-alpha, s, r); };
+#pragma unroll
+    for (int q = 0; q < KL; ++q) {
+        const int i0 = tid + q * NT, i = i0 < NL ? i0 : NL - 1;
+        const T fv = lv[q] ? (T)1 : (T)0;
+        const TR sn = (TR)fma(beta, (double)lo[q], (double)lw[q]);
+        tile.sB[i] = (T)residual((double)lr[q], (double)sn) * fv;
+        tile.sI[i] = li[q] * fv;
+        tile.sS[i] = ls[q] * fv;
+        tile.sC0[i] = l0[q] * (m0[q] ? (T)1 : (T)0);
+        tile.sC1[i] = l1[q] * (m1[q] ? (T)1 : (T)0);
+    }
+    double rr = 0.0;
+    if (own) {
+        const double pn = (oz - zm) + beta * op;
+        const TR sn = (TR)fma(beta, os, ow), rn = residual(orr, (double)sn);
+        v.p[c] = (TR)pn;
+        v.x[c] = (TR)(oxx + alpha * pn);
+        v.sn[c] = sn;
+        v.rn[c] = rn;
+        rr = (double)rn * (double)rn;
+    }
+    rr = wave_sum(rr);
+    if ((tid & (kWave - 1)) == 0) wr[tid / kWave] = rr;
+    __syncthreads();
+    if (tid == 0) {
+        double t = 0.0;
+        for (int q = 0; q < NT / kWave; ++q) t += wr[q];
+        part_rr[tile_id] = t;
+    }
+    down_passes2<T, NT>(tile, L, gc, xs, bc, tx, ty);
+}
+
+// One tile of the way up that ends the preconditioner of a CG iteration:
+// red x += P e, black GS, red GS as in up_tile2 but on one halo cell more
+// (staged halo 3, black on 2, red on 1), then w = A z and the partials of
+// r.z, sum z, sum r and w.z on the tile's cells.  rhs: the CG residual.
+// A singular operator has s = +0: not read.
+template <typename T, typename TR>
+__device__ inline void cg_up_tile2(const Level<T> &L, const Geo &gc, const T *__restrict__ xc,
+                                   const TR *__restrict__ r, const T *__restrict__ xs, T *__restrict__ z,
+                                   TR *__restrict__ w, const Level<TR> &A, int tx, int ty, int tile_id, int singular,
+                                   const CgPart &pt, int skip) {
+    using R = T;
+    constexpr int NT = kTileThreads, H = 3, WX = kTFX + 2 * H, WY = kTFY + 2 * H, NL = WX * WY;
+    constexpr int KL = (NL + NT - 1) / NT;
+    static_assert(kTFX * kTFY == NT, "one owned cell per thread");
+    __shared__ T sB[NL], sI[NL], sC0[NL], sC1[NL], sX[NL];
+    __shared__ double ws[4][NT / kWave];
+    const int tid = (int)threadIdx.x;
+    const int nx = (int)L.g.n[0], ny = (int)L.g.n[1];
+    const int px = L.g.per[0], py = L.g.per[1];
+    const int gx0 = tx * kTFX - H, gy0 = ty * kTFY - H;
+    T lb[KL], li[KL], l0[KL], l1[KL], lx_[KL];
+    bool lv[KL], m0[KL], m1[KL];
+#pragma unroll
+    for (int q = 0; q < KL; ++q) {
+        const int i0 = tid + q * NT, i = i0 < NL ? i0 : NL - 1;
+        const int ly = i / WX, lx = i - ly * WX;
+        bool vx, vy;
+        const int gx = tile_coord(gx0 + lx, nx, px, vx), gy = tile_coord(gy0 + ly, ny, py, vy);
+        const bool in = vx && vy;
+        const int g = in ? gx + nx * gy : 0;
+        lb[q] = (T)r[g];
+        li[q] = L.invd[g];
+        l0[q] = L.cs[0][g];
+        l1[q] = L.cs[1][g];
+        const int ia[3] = {in ? gx : 0, in ? gy : 0, 0};
+        const R pe = prolong_at<T, 2>(L.g, gc, xc, ia);
+        const T red = (in && ((gx0 + lx + gy0 + ly) & 1) == 0) ? (T)1 : (T)0;
+        lx_[q] = (T)((R)xs[g] + pe) * red;
+        lv[q] = in;
+        m0[q] = in && (px || gx > 0);
+        m1[q] = in && (py || gy > 0);
+    }
+    // the owned cell's operator row (in the CG's precision) and residual
+    const int oy = tid / kTFX, ox = tid - oy * kTFX;
+    const int cx = tx * kTFX + ox, cy = ty * kTFY + oy;
+    const bool own = cx < nx && cy < ny;
+    const int ca[3] = {own ? cx : 0, own ? cy : 0, 0};
+    const int c = ca[0] + nx * ca[1];
+    const int xl = nb_lo(A.g, c, ca[0], 0), xh = nb_hi(A.g, c, ca[0], 0);
+    const int yl = nb_lo(A.g, c, ca[1], 1), yh = nb_hi(A.g, c, ca[1], 1);
+    const double a0 = (double)A.cs[0][c], a1 = (double)A.cs[0][xh >= 0 ? xh : c];
+    const double a2 = (double)A.cs[1][c], a3 = (double)A.cs[1][yh >= 0 ? yh : c];
+    double as = 0.0;
+    if (!singular) as = (double)A.s[c];
+    const double rc = (double)r[c];
+    if (skip) return;
+#pragma unroll
+    for (int q = 0; q < KL; ++q) {
+        const int i0 = tid + q * NT, i = i0 < NL ? i0 : NL - 1;
+        const T fv = lv[q] ? (T)1 : (T)0;
+        sB[i] = lb[q] * fv;
+        sI[i] = li[q] * fv;
+        sC0[i] = l0[q] * (m0[q] ? (T)1 : (T)0);
+        sC1[i] = l1[q] * (m1[q] ? (T)1 : (T)0);
+        sX[i] = lx_[q];
+    }
+    __syncthreads();
+    auto gs = [&](int i) {
+        R acc = 0.0;
+        acc += (R)sC0[i] * (R)sX[i - 1];
+        acc += (R)sC0[i + 1] * (R)sX[i + 1];
+        acc += (R)sC1[i] * (R)sX[i - WX];
+        acc += (R)sC1[i + WX] * (R)sX[i + WX];
+        return (T)(((R)sB[i] + acc) * (R)sI[i]);
+    };
+    const int par = (gx0 + gy0) & 1;
+    // black on the tile and 2 halo cells (local [1, WX-1) x [1, WY-1))
+    constexpr int XB = (WX - 2) / 2;
+    for (int q = tid; q < XB * (WY - 2); q += NT) {
+        const int row = q / XB, m = q - row * XB, ly = 1 + row;
+        const int i = ly * WX + tile_color_x(m, ly, par, 1);
+        sX[i] = gs(i);
+    }
+    __syncthreads();
+    // red on the tile and 1 halo cell (local [2, WX-2) x [2, WY-2)): every
+    // second cell of the rows, whose x of that colour starts at 2 or 3
+    constexpr int XR = (WX - 4) / 2;
+    for (int q = tid; q < XR * (WY - 4); q += NT) {
+        const int row = q / XR, m = q - row * XR, ly = 2 + row;
+        const int i = ly * WX + 2 + 2 * m + ((ly + par) & 1);
+        sX[i] = gs(i);
+    }
+    __syncthreads();
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    if (own) {
+        const int i = (oy + H) * WX + ox + H;
+        const double zc = (double)sX[i];
+        double wv = as * zc;
+        wv += (xl >= 0 ? a0 : 0.0) * (zc - (double)sX[i - 1]);
+        wv += (xh >= 0 ? a1 : 0.0) * (zc - (double)sX[i + 1]);
+        wv += (yl >= 0 ? a2 : 0.0) * (zc - (double)sX[i - WX]);
+        wv += (yh >= 0 ? a3 : 0.0) * (zc - (double)sX[i + WX]);
+        z[c] = (T)sX[i];
+        w[c] = (TR)wv;
+        sum[0] = rc * zc;
+        sum[1] = zc;
+        sum[2] = rc;
+        sum[3] = wv * zc;
+    }
+    tile_sum4_all<NT>(sum, ws);
+    if (tid == 0) {
+        pt.rz[tile_id] = sum[0];
+        pt.z[tile_id] = sum[1];
+        pt.r[tile_id] = sum[2];
+        pt.wz[tile_id] = sum[3];
+    }
 }
 
 }  // namespace chns

@@ -74,3 +74,13 @@ def test_cg_apply_forms(n, per, precision):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_coarse_setup_forms(n, per, precision):
     assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
+
+
+# 2D solves with one reduction point per CG iteration: a single row of tiles,
+# partial tiles, the most tiles of that form (2048) and the first grid past it
+@pytest.mark.parametrize("n,per", [((64, 48), (True, True)), ((72, 88), (False, True)), ((80, 176), (True, False)),
+                                   ((2048, 16), (False, False)), ((1024, 1024), (True, False)),
+                                   ((1088, 1024), (False, True))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_one_reduction_forms(n, per, precision):
+    assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
