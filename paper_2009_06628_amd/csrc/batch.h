@@ -32,7 +32,6 @@ struct BatchProb {
     Scal *sc;                              // solver scalars of the problem
     int lsb;                               // first level handled by one workgroup
     int vlds;                              // LDS bytes of that V-cycle out of LDS (0: from global memory)
-    LdsCopy vcp;                           // its copy plan (the same for every slot of the problem)
     int t0, t1;                            // the problem's tiles in the level-0 tile list
 };
 

@@ -494,15 +494,9 @@ size_t layout_batch(Bump &B, int count, const Plan *plans, const chns_props *pro
         Q.sc = scal ? scal + i : nullptr;
         {
             Q.lsb = batch_lsb(P);   // first level of the single-workgroup part
-            // the V-cycle of those levels out of LDS where it fits; one
-            // plan serves every slot (same carving from a 256-byte boundary)
-            Q.vlds = (int)lds_vcycle_bytes(Q.mom, Q.lsb);
-            memset(&Q.vcp, 0, sizeof Q.vcp);
-            if (Q.vlds) {
-                Q.vcp = lds_copy_plan(Q.mom, Q.lsb);
-                const LdsCopy c2 = lds_copy_plan(Q.chs, Q.lsb);
-                if ((int)lds_vcycle_bytes(Q.chs, Q.lsb) != Q.vlds || memcmp(&c2, &Q.vcp, sizeof c2) != 0) Q.vlds = 0;
-            }
+            // the V-cycle of those levels in registers and LDS where they fit
+            // (the same for every slot of the problem)
+            Q.vlds = (int)vs_lds_bytes(Q.mom, Q.lsb, P.dim);
             if (b) {
                 b->vlds_max = std::max(b->vlds_max, Q.vlds);
                 if (Q.vlds == 0) b->vlds_some_global = 1;

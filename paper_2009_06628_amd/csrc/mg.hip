@@ -23,8 +23,8 @@
 //   * 3D levels above kSBCells cells: one grid-wide kernel per pass (fused
 //     zero-guess pre-smoothing, residual, restriction, prolongation, black
 //     sweep, red sweep);
-//   * all smaller levels: ONE single-workgroup kernel that copies their
-//     storage into LDS and runs every sweep there.
+//   * all smaller levels: ONE single-workgroup kernel that holds their
+//     coefficients in registers and x in LDS.
 // Reductions are deterministic and fence-free: per-block partials from a
 // fixed grid-stride partition, summed in a fixed order either by a
 // one-workgroup finalize kernel or redundantly by every block of the kernel
@@ -357,56 +357,47 @@ __global__ void __launch_bounds__(kSBThreads) k_vcycle_block(Slot<T> S, int l0, 
     vcycle_block_dev<T, TB, DIM>(S, l0, b0, x0);
 }
 
-// End of a CG iteration: r.r, the iteration count and the stop flags (thread 0)
-__device__ inline void pcg_fin_rr_dev(Scal *sc, double rr) {
+// End of a CG iteration: r.r, the iteration count and the stop flags (thread
+// 0; v: the scalars as they were)
+__device__ inline void pcg_fin_rr_dev(Scal *sc, const Scal &v, double rr) {
     if (threadIdx.x != 0) return;
     sc->rr = rr;
-    sc->iter += 1;
+    sc->iter = v.iter + 1;
     if (!isfinite(rr)) {
         sc->nonfinite = 1;
         sc->done = 1;
-    } else if (rr <= sc->rtol2 * sc->bb) {
+    } else if (rr <= v.rtol2 * v.bb) {
         sc->done = 1;
-    } else if (sc->iter >= sc->max_iter) {
+    } else if (v.iter + 1 >= v.max_iter) {
         sc->unconverged = 1;
         sc->done = 1;
     }
 }
 
-// Levels [l0, nlev) out of LDS: the segments cp of their contiguous storage
-// are copied in, x of level l0 is written back.  fin (when given): the CG
-// update of this iteration left nfin partials of r.r there and its end
+// Levels [l0, nlev) in one workgroup (vcycle_small_dev).  fin (when given): the
+// CG update of this iteration left nfin partials of r.r there and its end
 // (pcg_fin_rr_dev) is taken here, in the one workgroup every cycle passes
 // through, instead of in a launch of its own; the cycle that follows the
 // last update is completed for nothing.
 template <typename T, int DIM>
-__global__ void __launch_bounds__(kSBThreads) k_vcycle_lds(Slot<T> S, int l0, LdsCopy cp,
-                                                           const int *__restrict__ done, Scal *fsc,
+__global__ void __launch_bounds__(kVsThreads) k_vcycle_lds(VsArgs<T, DIM> A, const int *__restrict__ done, Scal *fsc,
                                                            const double *__restrict__ fin, int nfin) {
-    const int dn = *done;   // tested after the copy (which only reads memory and writes LDS)
+    const int dn = *done;
     extern __shared__ uint4 lds_words[];
-    char *lds = (char *)lds_words;
-    const char *base = (const char *)S.lev[l0].s;
+    __shared__ double ws[kVsThreads / kWave];
     double rr = 0.0;
-    for (int i = (int)threadIdx.x; i < nfin; i += kSBThreads) rr += fin[i];
-    copy_to_lds(lds_words, (const uint4 *)base, cp);
-    if (dn) return;
-    __syncthreads();
-    if (nfin) {   // scratch: the residual array of level l0 (at least 256 cells, not read before it is written)
-        double *ws = (double *)lds_image(lds, base, S.lev[l0].r);
+    for (int i = (int)threadIdx.x; i < nfin; i += kVsThreads) rr += fin[i];
+    Scal sv{};   // read with the other loads; the sums of the waves meet after the cycle's barriers
+    if (nfin && threadIdx.x == 0) sv = *fsc;
+    vcycle_small_dev<T, DIM>(A, (T *)lds_words, dn, [&] {
+        if (!nfin) return;
         rr = wave_sum(rr);
         if ((threadIdx.x & (kWave - 1)) == 0) ws[threadIdx.x / kWave] = rr;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            rr = 0.0;
-            for (int q = 0; q < kSBThreads / kWave; ++q) rr += ws[q];
-            pcg_fin_rr_dev(fsc, rr);
-        }
-    }
-    vcycle_lds_dev<T, DIM>(S, l0, lds, base);
-    const T *xl = lds_image(lds, base, S.lev[l0].x);
-    T *xg = S.lev[l0].x;
-    LDS_LOOP(S.lev[l0].g.N) xg[c] = xl[c];
+    });
+    if (dn || !nfin || threadIdx.x != 0) return;
+    rr = 0.0;
+    for (int q = 0; q < kVsThreads / kWave; ++q) rr += ws[q];
+    pcg_fin_rr_dev(fsc, sv, rr);
 }
 
 template <typename T, int DIM>
@@ -1293,7 +1284,7 @@ __global__ void __launch_bounds__(kBlock) k_round_vec(int N, const T *__restrict
 __global__ void __launch_bounds__(kBlock) k_pcg_fin_rr(Scal *sc, const double *__restrict__ part_rr, int nparts) {
     if (sc->done) return;
     __shared__ double lds[kBlock / kWave];
-    pcg_fin_rr_dev(sc, sum_parts_all(part_rr, nparts, lds));
+    pcg_fin_rr_dev(sc, *sc, sum_parts_all(part_rr, nparts, lds));
 }
 
 // partials of r.z, sum z, sum r
@@ -1736,21 +1727,12 @@ static void vcycle_small(Slot<T> &S, const TB *b0, T *x0, const int *done, hipSt
                          const double *fin = nullptr, int nfin = 0) {
     constexpr double W = sizeof(T);
     const int lsb = S.lsb;
-    // storage of the small levels: one contiguous range from lev[lsb].s
-    // to the end of the coarsest inverse
-    const size_t range16 = lds_vcycle_bytes(S, lsb);
-    if (range16) {
-        // the range is read once and x of level lsb written back
-        static const bool attr = [] {   // once per instantiation, thread-safe
-            (void)hipFuncSetAttribute((const void *)k_vcycle_lds<T, DIM>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      kLdsVcycleBytes);
-            return true;
-        }();
-        (void)attr;
-        const LdsCopy cp = lds_copy_plan(S, lsb);
-        const double bytes = 16.0 * cp.total + W * S.lev[lsb].g.N + 8.0 * nfin;
-        TLAUNCHS(K_COARSE_SOLVE, bytes, (k_vcycle_lds<T, DIM>), dim3(1), dim3(kSBThreads), range16, st, S, lsb, cp, done,
-                 sc, fin, nfin);
+    if (const size_t lds = vs_lds_bytes(S, lsb, DIM)) {
+        // s, cs, 1 / diag of the swept levels, b and x of the first, the coarsest inverse
+        double bytes = 2.0 * W * S.lev[lsb].g.N + 8.0 * S.ncoarse * S.ncoarse + 8.0 * nfin;
+        for (int l = lsb; l < S.nlev - 1; ++l) bytes += W * (2 + DIM) * S.lev[l].g.N;
+        TLAUNCHS(K_COARSE_SOLVE, bytes, (k_vcycle_lds<T, DIM>), dim3(1), dim3(kVsThreads), lds, st,
+                 (vs_args<T, DIM>(S, lsb)), done, sc, fin, nfin);
         return;
     }
     if (nfin) LAUNCH1(K_PCG_UPDATE, 8.0 * nfin, (k_pcg_fin_rr), kBlock, st, sc, fin, nfin);

@@ -124,25 +124,16 @@ __device__ inline R pro_row(R v, R wyz, R w0, R a, R w1, R b) {
 template <typename R>
 __device__ inline void pro_axis(int f, int nc, int per, int &c0, int &c1, R &w0, R &w1) {
     const int p = f >> 1;
-    int q = (f & 1) ? p + 1 : p - 1;
+    const int q = (f & 1) ? p + 1 : p - 1;
+    const bool out = q < 0 || q >= nc, wall = out && !per;
     c0 = p;
-    if (q < 0 || q >= nc) {
-        if (per) {
-            q = q < 0 ? nc - 1 : 0;
-        } else {
-            c1 = p;
-            w0 = (R)1;
-            w1 = (R)0;
-            return;
-        }
-    }
-    c1 = q;
-    w0 = (R)0.75;
-    w1 = (R)0.25;
+    c1 = out ? (per ? (q < 0 ? nc - 1 : 0) : p) : q;
+    w0 = wall ? (R)1 : (R)0.75;
+    w1 = wall ? (R)0 : (R)0.25;
 }
 
-template <typename T, int DIM>
-__device__ inline T prolong_at(const Geo &gf, const Geo &gc, const T *__restrict__ xc, const int fi[3]) {
+template <typename T, int DIM, typename G>
+__device__ inline T prolong_at(const G &gf, const G &gc, const T *__restrict__ xc, const int fi[3]) {
     using R = T;
     int c0[3], c1[3];
     R w0[3], w1[3];
@@ -386,151 +377,354 @@ __device__ inline void vcycle_block_dev(const Slot<T> &S, int l0, const TB *__re
 }
 
 // ---------------------------------------------------------------------------
-// LDS-resident V-cycle of the small levels
+// V-cycle of the small levels in registers and LDS
 // ---------------------------------------------------------------------------
-// The storage of levels [l0, nlev) of a slot is one contiguous range of the
-// workspace (per level s, cs, invd, r, x, b, then the coarsest inverse).  A
-// one-workgroup launch may land on an XCD whose L2 holds none of it, so the
-// global-memory form pays several dependent memory round trips in every
-// sweep.  Here the workgroup copies the whole range into LDS in one round of
-// independent 16-byte loads, runs every sweep out of LDS with the same
-// per-cell code, and writes back x of level l0.
-constexpr int kLdsCopyUnroll = 10;                  // 16-byte loads in flight per thread
+// Levels [l0, nlev), l0 >= 1, of at most 4 kVsThreads cells, in one workgroup
+// of kVsThreads threads, with the arithmetic of vcycle_block_dev per cell:
+//   pre-smoothing  red x = b / d, black GS from those values, then
+//                  kSmallSweeps - 1 more red | black sweeps
+//   post-smoothing red x += P e, then kSmallSweeps x (black GS | red GS)
+//                  (black x is overwritten by its GS update, so only red
+//                  cells take the prolonged correction)
+// A thread takes pairs of cells 2m, 2m + 1 of a row (x extents are even), one
+// red and one black: two pairs of level l0, one of each level below.
+//
+// One workgroup is alone with its latencies: memory (a launch may land on an
+// XCD whose L2 holds none of this), the index arithmetic and coefficient
+// loads of every level, and per pass one LDS round trip, a chain of multiply-
+// adds and a barrier.  So everything a thread ever needs from memory, for all
+// levels, is loaded into its registers in one round at the start (1 / diag,
+// the face coefficients and s of its pairs, b of level l0, its entries of
+// the coarsest inverse), the index arithmetic (quotients of small integers
+// through a float reciprocal) runs while those loads are in flight, and only x,
+// the residual and the coarser right-hand sides are in LDS.  x and the
+// residual are stored by colour while a level is swept (red of pair k at k,
+// black at N / 2 + k): a pass reads consecutive words where the x order reads
+// every second one (two-way bank conflicts), and a pair's partner is in a
+// register.  512 threads instead of 1024 leave each twice the registers (all
+// levels' coefficients stay resident) and half the waves at each barrier.
+// Faces on walls hold 0 on these levels (coarsen_cell), so every axis is
+// indexed as periodic: the wrapped neighbour of a cell on a wall enters with
+// weight 0, where the masked stencils add 0 for the missing neighbour.
+// Launch, FP64 (before: every level staged in LDS in x order, 1024 threads):
+// 256 x 512 (levels 2048, 512, 128, 32) 15.6 -> 13.7 us, 64^2 11.0 -> 9.9 us,
+// 96^3 (1728, 216, 27) 15.2 -> 11.8 us, 64^3 8.7 -> 7.1 us; bit for bit the
+// same.  What is left is the 41 dependent passes, 250 to 400 cycles each.
+constexpr int kVsThreads = 512;
+template <int DIM>
+constexpr int kVsLevels = DIM == 2 ? 3 : 2;   // levels swept: N > 64 on each, at most 2048 on the first
 
-// The LDS kernel always runs kSBThreads threads; a compile-time stride keeps
-// the loops from reading the workgroup size from the dispatch arguments.
-#define LDS_LOOP(N) for (int c = (int)threadIdx.x; c < (int)(N); c += kSBThreads)
+template <typename T>
+struct VsTwo {
+    typedef T type __attribute__((ext_vector_type(2)));
+};
 
-
-// Copy the segments: every load of a round is issued before its stores.
-// Indices past the end are clamped to the last word, which is then stored
-// again with its own value, so no load or store is conditional.
-__device__ inline void copy_to_lds(uint4 *dst_words, const uint4 *src_words, const LdsCopy &cp) {
-    // src is device memory: global loads (a pointer read from a table would
-    // otherwise be generic, and the loaded words went through scratch)
-    using Word = unsigned int __attribute__((ext_vector_type(4)));
-    using GWord = const __attribute__((address_space(1))) Word;
-    GWord *src = (GWord *)src_words;
-    Word *dst = (Word *)dst_words;
-    const int n = cp.total;
-    for (int base = 0; base < n; base += kLdsCopyUnroll * kSBThreads) {
-        Word v[kLdsCopyUnroll];
-        int w[kLdsCopyUnroll];
-#pragma unroll
-        for (int k = 0; k < kLdsCopyUnroll; ++k) {
-            int i = base + k * kSBThreads + (int)threadIdx.x;
-            i = i < n ? i : n - 1;
-            int sh = cp.shift[0];
-#pragma unroll
-            for (int j = 1; j < kLdsCopySegs; ++j) sh = i >= cp.cend[j - 1] ? cp.shift[j] : sh;
-            w[k] = i + sh;
-            v[k] = src[w[k]];
-        }
-#pragma unroll
-        for (int k = 0; k < kLdsCopyUnroll; ++k) dst[w[k]] = v[k];
-    }
+// LDS bytes of that V-cycle, or 0 where it does not apply (then
+// vcycle_block_dev): lsb == 0, a larger level or more levels.  x and r per
+// swept level, b below the first; b and x of the coarsest.
+template <typename T>
+inline size_t vs_lds_bytes(const Slot<T> &S, int lsb, int dim) {
+    if (lsb <= 0 || S.lev[lsb].g.N > 4 * kVsThreads) return 0;
+    if (S.nlev - 1 - lsb > (dim == 2 ? kVsLevels<2> : kVsLevels<3>)) return 0;
+    size_t n = 2 * (size_t)S.ncoarse;
+    for (int l = lsb; l < S.nlev - 1; ++l) n += (l == lsb ? 2 : 3) * (size_t)S.lev[l].g.N;
+    return (n * sizeof(T) + 15) & ~(size_t)15;
 }
 
-// Copy plan of the LDS V-cycle of levels [lsb, nlev): the byte intervals
-// read before they are written (s, cs, invd of each level, b of level lsb,
-// the coarsest inverse), merged across the smallest gaps down to
-// kLdsCopySegs segments, in whole 16-byte words of the range (arrays start
-// on 256-byte boundaries; a rounded-up end stays inside the workspace).
-template <typename T>
-inline LdsCopy lds_copy_plan(const Slot<T> &S, int lsb) {
-    const char *base = (const char *)S.lev[lsb].s;
-    long long a[2 * kMaxLev + 2], e[2 * kMaxLev + 2];
-    int n = 0;
-    auto add = [&](const void *p, size_t bytes) {
-        a[n] = (const char *)p - base;
-        e[n] = a[n] + (long long)bytes;
-        ++n;
-    };
-    for (int l = lsb; l < S.nlev; ++l) {
-        const Level<T> &L = S.lev[l];
-        add(L.s, (size_t)((const char *)(L.invd + L.g.N) - (const char *)L.s));   // s, cs[], invd
-        if (l == lsb) add(L.b, sizeof(T) * (size_t)L.g.N);
-    }
-    add(S.Ainv, sizeof(double) * (size_t)S.ncoarse * S.ncoarse);
-    // sort by start (a handful of entries)
-    for (int i = 1; i < n; ++i)
-        for (int j = i; j > 0 && a[j] < a[j - 1]; --j) {
-            std::swap(a[j], a[j - 1]);
-            std::swap(e[j], e[j - 1]);
+// What the kernel needs to know, at fixed places: indexing the slot's levels
+// by l0 in the kernel's arguments costs a scalar load from memory before the
+// address of the next is known.  Entries past the coarsest repeat level l0.
+struct VsGeo {
+    int n[3], per[3];
+};
+template <typename T, int DIM>
+struct VsArgs {
+    int ns, n;             // levels swept, cells of the coarsest
+    VsGeo g[kVsLevels<DIM> + 1];
+    const T *s[kVsLevels<DIM>], *cs[kVsLevels<DIM>][DIM], *invd[kVsLevels<DIM>];
+    const T *b;            // level l0
+    T *x;
+    const double *Ainv;
+};
+template <typename T, int DIM>
+__host__ __device__ inline VsArgs<T, DIM> vs_args(const Slot<T> &S, int l0) {
+    VsArgs<T, DIM> A;
+    A.ns = S.nlev - 1 - l0;
+    A.n = S.ncoarse;
+#pragma unroll
+    for (int j = 0; j <= kVsLevels<DIM>; ++j) {
+        const Level<T> &L = S.lev[j <= A.ns ? l0 + j : l0];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            A.g[j].n[a] = L.g.n[a];
+            A.g[j].per[a] = L.g.per[a];
         }
-    while (n > kLdsCopySegs) {
-        int best = 0;
-        for (int i = 1; i + 1 < n; ++i)
-            if (a[i + 1] - e[i] < a[best + 1] - e[best]) best = i;
-        e[best] = std::max(e[best], e[best + 1]);
-        for (int i = best + 1; i + 1 < n; ++i) {
-            a[i] = a[i + 1];
-            e[i] = e[i + 1];
-        }
-        --n;
-    }
-    LdsCopy cp;
-    int done = 0;
-    for (int i = 0; i < kLdsCopySegs; ++i) {
-        if (i < n) {
-            const int w0 = (int)(a[i] / 16), w1 = (int)((e[i] + 15) / 16);
-            cp.shift[i] = w0 - done;
-            done += w1 - w0;
-            cp.cend[i] = done;
-        } else {
-            cp.shift[i] = cp.shift[n - 1];
-            cp.cend[i] = done;
+        if (j < kVsLevels<DIM>) {
+            A.s[j] = L.s;
+            A.invd[j] = L.invd;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) A.cs[j][a] = L.cs[a];
         }
     }
-    cp.total = done;
-    return cp;
+    A.b = S.lev[l0].b;
+    A.x = S.lev[l0].x;
+    A.Ainv = S.Ainv;
+    return A;
+}
+template <int DIM>
+__device__ inline int vs_cells(const VsGeo &g) {
+    return g.n[0] * g.n[1] * (DIM == 3 ? g.n[2] : 1);
 }
 
-// LDS bytes of the V-cycle of levels [lsb, nlev) of S in one workgroup (its
-// storage from lev[lsb].s to the end of the coarsest inverse, in whole
-// 16-byte words), or 0 where that kernel does not apply: lsb == 0, more
-// than kLdsVcycleBytes, or a level with more than one red-black pair per
-// thread.
-template <typename T>
-inline size_t lds_vcycle_bytes(const Slot<T> &S, int lsb) {
-    if (lsb <= 0 || S.lev[lsb].g.N > 2 * kSBThreads) return 0;
-    const size_t range =
-        (size_t)((const char *)(S.Ainv + (size_t)S.ncoarse * S.ncoarse) - (const char *)S.lev[lsb].s);
-    const size_t range16 = (range + 15) & ~(size_t)15;
-    return range16 <= (size_t)kLdsVcycleBytes ? range16 : 0;
-}
-
-// The LDS image of a workspace pointer p of the copied range starting at base.
-template <typename T>
-__device__ inline T *lds_image(char *lds, const char *base, const T *p) {
-    return (T *)(lds + (unsigned)((const char *)p - base));
+// a / b for 0 <= a < 2^20, b >= 1: (a + 1/2) / b is at least 1 / (2 b) away
+// from an integer, more than its error of 2^-22 a / b
+__device__ inline int small_div(int a, int b) {
+    return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
 }
 
 template <typename T, int DIM>
-__device__ inline Level<T> lds_level(const Level<T> &G, char *lds, const char *base) {
-    Level<T> L;
-    L.g = G.g;
-    L.s = lds_image(lds, base, G.s);
-#pragma unroll
-    for (int b = 0; b < 3; ++b) L.cs[b] = b < DIM ? lds_image(lds, base, G.cs[b]) : L.s;
-    L.invd = lds_image(lds, base, G.invd);
-    L.r = lds_image(lds, base, G.r);
-    L.x = lds_image(lds, base, G.x);
-    L.b = lds_image(lds, base, G.b);
-    return L;
+struct VsPair {
+    bool on;
+    int k, par;            // pair index; the red cell's parity in x: red at 2m + par
+    int adj[2];            // the other pair in the row that the red / black cell touches
+    int nb[2 * DIM - 2];   // pairs across the y faces (, z faces)
+    int xh;                // pair of the upper x neighbour of the odd cell
+    int ia[3];             // coordinates of the red cell
+    T b[2], v[2];          // right-hand side and x: red, black
+    T invd[2], s[2];
+    T cw[2][2 * DIM];      // coefficients of the faces: x low, x high, y low, y high (, z low, z high)
+};
+
+template <typename T, int DIM>
+__device__ inline void vs_index(const VsGeo &g, int k, VsPair<T, DIM> &P) {
+    const int nx = g.n[0], ny = g.n[1], nz = DIM == 3 ? g.n[2] : 1, nxh = nx >> 1;
+    P.on = k < nxh * ny * nz;
+    P.k = P.on ? k : 0;
+    const int row = small_div(P.k, nxh), m = P.k - row * nxh;   // row = y + ny z
+    const int z = DIM == 3 ? small_div(row, ny) : 0;
+    const int y = row - z * ny;
+    P.par = (y + z) & 1;
+    P.ia[0] = 2 * m + P.par;
+    P.ia[1] = y;
+    P.ia[2] = z;
+    const int ml = P.k + (m > 0 ? -1 : nxh - 1);
+    P.xh = P.k + (m < nxh - 1 ? 1 : 1 - nxh);
+    P.adj[0] = P.par ? P.xh : ml;
+    P.adj[1] = P.par ? ml : P.xh;
+    P.nb[0] = P.k + (y > 0 ? -nxh : nxh * (ny - 1));
+    P.nb[1] = P.k + (y < ny - 1 ? nxh : -nxh * (ny - 1));
+    if (DIM == 3) {
+        const int nxyh = nxh * ny;
+        P.nb[2 * DIM - 4] = P.k + (z > 0 ? -nxyh : nxyh * (nz - 1));
+        P.nb[2 * DIM - 3] = P.k + (z < nz - 1 ? nxyh : -nxyh * (nz - 1));
+    }
 }
 
-// x = Ainv b on the coarsest level (FP64 inverse, all operands in LDS): G
-// lanes per row (G a power of two, at most a wave, G n <= kSBThreads where
-// n allows), lane q summing columns q, q + G, ... in order, then a butterfly
-// sum over the G lanes.  The lanes of a group (aligned within a wave) run
-// the same rows, so every shuffle pairs two active lanes of one group.
+// even / odd cell -> red / black
+template <typename T, int DIM, typename V>
+__device__ inline void vs_order(const VsPair<T, DIM> &P, V v, T (&o)[2]) {
+    o[0] = P.par ? v.y : v.x;
+    o[1] = P.par ? v.x : v.y;
+}
+
+// The pair's coefficients and b in device memory, as loaded: one aligned load
+// per array and pair.  The loads of every level are issued before any of
+// them is used (vs_take), without a branch between them: a level per branch
+// waited for one memory round trip after another (7600 cycles for
+// five, 4900 for all at once).
 template <typename T>
-__device__ inline void coarse_solve_lds(int n, const double *Ainv, const T *b, T *x) {
+struct VsRaw {
+    typename VsTwo<T>::type invd, s, b, f0, f1, h1, f2, h2;
+    T x2;
+};
+template <typename T, int DIM>
+__device__ inline void vs_load(const VsArgs<T, DIM> &A, int j, const VsPair<T, DIM> &P, VsRaw<T> &r) {
+    using GV = const __attribute__((address_space(1))) typename VsTwo<T>::type;
+    using G1 = const __attribute__((address_space(1))) T;
+    auto two = [](const T *p, int k) { return ((GV *)p)[k]; };
+    r.invd = two(A.invd[j], P.k);
+    r.s = two(A.s[j], P.k);
+    r.f0 = two(A.cs[j][0], P.k);
+    r.x2 = ((G1 *)A.cs[j][0])[2 * P.xh];
+    r.f1 = two(A.cs[j][1], P.k);
+    r.h1 = two(A.cs[j][1], P.nb[1]);
+    if (DIM == 3) {
+        r.f2 = two(A.cs[j][DIM - 1], P.k);
+        r.h2 = two(A.cs[j][DIM - 1], P.nb[2 * DIM - 3]);
+    }
+    r.b = j == 0 ? two(A.b, P.k) : r.s;   // (below level l0 the restriction provides b)
+}
+template <typename T, int DIM>
+__device__ inline void vs_take(const VsRaw<T> &r, VsPair<T, DIM> &P) {
+    vs_order(P, r.invd, P.invd);
+    vs_order(P, r.s, P.s);
+    vs_order(P, r.b, P.b);
+    typename VsTwo<T>::type h0;
+    h0.x = r.f0.y;
+    h0.y = r.x2;
+    T t[2];
+    auto put = [&](typename VsTwo<T>::type v, int i) {
+        vs_order(P, v, t);
+        P.cw[0][i] = t[0];
+        P.cw[1][i] = t[1];
+    };
+    put(r.f0, 0);
+    put(h0, 1);
+    put(r.f1, 2);
+    put(r.h1, 3);
+    if (DIM == 3) {
+        put(r.f2, 2 * DIM - 2);
+        put(r.h2, 2 * DIM - 1);
+    }
+}
+
+// Values across the faces of cell Q of the pair, in the order of cw: x holds
+// the other colour by pair.
+template <int Q, typename T, int DIM>
+__device__ inline void vs_faces(const VsPair<T, DIM> &P, const T *x, T (&v)[2 * DIM]) {
+    const T other = x[P.adj[Q]], mine = P.v[1 - Q];
+    // red: its partner is the upper x neighbour for par 0; black: the lower one
+    const bool low = Q == 0 ? P.par != 0 : P.par == 0;
+    v[0] = low ? mine : other;
+    v[1] = low ? other : mine;
+#pragma unroll
+    for (int i = 0; i < 2 * DIM - 2; ++i) v[2 + i] = x[P.nb[i]];
+}
+
+// Gauss-Seidel value of cell Q of the pair
+template <int Q, typename T, int DIM>
+__device__ inline T vs_gs(const VsPair<T, DIM> &P, const T *x) {
+    T v[2 * DIM], acc = 0.0;
+    vs_faces<Q>(P, x, v);
+#pragma unroll
+    for (int i = 0; i < 2 * DIM; ++i) acc = fmar(P.cw[Q][i], v[i], acc);
+    return (P.b[Q] + acc) * P.invd[Q];
+}
+
+// residual b - A x at cell Q of the pair
+template <int Q, typename T, int DIM>
+__device__ inline T vs_residual(const VsPair<T, DIM> &P, const T *x) {
+    T v[2 * DIM], acc = P.s[Q] * P.v[Q];
+    vs_faces<Q>(P, x, v);
+#pragma unroll
+    for (int i = 0; i < 2 * DIM; ++i) acc = fmar(P.cw[Q][i], P.v[Q] - v[i], acc);
+    return P.b[Q] - acc;
+}
+
+// restrict_cell at coarse coordinates I from a fine residual stored by colour
+// (r: red, then black from half on): the taps are the odd cell of pair I - 1,
+// both cells of pair I and the even cell of pair I + 1 of each row.
+template <typename T, int DIM>
+__device__ inline T vs_restrict(const VsGeo &gf, const VsGeo &gc, const T *r, const int I[3]) {
+    int fx[4], fy[4], fz[4];
+    T wx[4], wy[4], wz[4];
+    res_axis<T>(I[0], gc.n[0], gf.n[0], gc.per[0], fx, wx);
+    res_axis<T>(I[1], gc.n[1], gf.n[1], gc.per[1], fy, wy);
+    if (DIM == 3) res_axis<T>(I[2], gc.n[2], gf.n[2], gc.per[2], fz, wz);
+    const int nxh = gf.n[0] >> 1, half = nxh * gf.n[1] * (DIM == 3 ? gf.n[2] : 1);
+    T v = 0.0;
+#pragma unroll
+    for (int a = 0; a < (DIM == 3 ? 4 : 1); ++a) {
+        const int kz = DIM == 3 ? fz[a] * gf.n[1] : 0;
+        const T wza = DIM == 3 ? wz[a] : (T)1;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = (kz + fy[q]) * nxh;
+            const int par = (fy[q] + (DIM == 3 ? fz[a] : 0)) & 1;
+            // (a clamped tap at a wall has weight 0: any value of its row does)
+            const int odd = row + (par ? 0 : half), even = row + (par ? half : 0);
+            T s = 0.0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = fmar(wx[e], r[((e & 1) ? even : odd) + (fx[e] >> 1)], s);
+            v = fmar(wy[q] * wza, s, v);
+        }
+    }
+    return v;
+}
+
+// x = Ainv b on the coarsest level: G lanes per row (a power of two, at most
+// a wave, G n <= 1024 where n allows), lane q summing columns q, q + G, ...
+// in order, then a butterfly over the G lanes.  For n <= 64 a thread's
+// entries (two rows, four columns at most) are in a, loaded at the start.
+constexpr int kVsRows = 2, kVsCols = 4;
+__device__ inline int vs_lanes(int n, int &lg) {
     int G = 1;
-    while (G < kWave && 2 * G * n <= kSBThreads) G *= 2;
-    const int q = (int)threadIdx.x & (G - 1);
-    for (int i = (int)threadIdx.x / G; i < n; i += kSBThreads / G) {
+    lg = 0;
+    while (G < kWave && 2 * G * n <= 1024) {
+        G *= 2;
+        ++lg;
+    }
+    return G;
+}
+__device__ inline void vs_load_inverse(int n, const double *Ainv, double (&a)[kVsRows][kVsCols]) {
+    int lg;
+    const int G = vs_lanes(n, lg), q = (int)threadIdx.x & (G - 1), i0 = (int)threadIdx.x >> lg;
+#pragma unroll
+    for (int r = 0; r < kVsRows; ++r)
+#pragma unroll
+        for (int c = 0; c < kVsCols; ++c) {
+            const int i = i0 + r * (kVsThreads >> lg), j = q + c * G;
+            a[r][c] = Ainv[i < n && j < n ? i * n + j : 0];
+        }
+}
+// v of the lane that a DPP control pairs with this one
+template <int CTRL>
+__device__ inline double vs_dpp(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// Sum of the two 16-lane (32-lane) halves of each group, in both
+__device__ inline double vs_sum16(double v) {
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+__device__ inline double vs_sum32(double v) {
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+// Butterfly sum over groups of G = 16, 32 or 64 lanes, the widest step first
+// (the sums of __shfl_xor with offsets G / 2 .. 1 without its LDS round trips:
+// coarse solve of 32 cells 2600 -> 1150 cycles).  After the step of
+// distance 8 the values repeat every 8 lanes, so a rotation by 4 within 16
+// is the exchange at distance 4.
+__device__ inline double vs_butterfly(double v, int G) {
+    if (G > 32) v = vs_sum32(v);
+    if (G > 16) v = vs_sum16(v);
+    v += vs_dpp<0x128>(v);   // row_ror:8
+    v += vs_dpp<0x124>(v);   // row_ror:4
+    v += vs_dpp<0x4E>(v);    // quad_perm 2 3 0 1
+    v += vs_dpp<0xB1>(v);    // quad_perm 1 0 3 2
+    return v;
+}
+template <typename T>
+__device__ inline void vs_coarse(int n, const double *Ainv, const double (&a)[kVsRows][kVsCols], const T *b, T *x) {
+    int lg;
+    const int G = vs_lanes(n, lg), q = (int)threadIdx.x & (G - 1), i0 = (int)threadIdx.x >> lg;
+    if (n <= kLdsInverse) {
+        double bv[kVsCols];
+#pragma unroll
+        for (int c = 0; c < kVsCols; ++c) bv[c] = (double)b[q + c * G < n ? q + c * G : 0];
+        double v[kVsRows] = {0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < kVsCols; ++c) {
+            if (c * G >= n) break;
+            const bool in = q + c * G < n;
+#pragma unroll
+            for (int r = 0; r < kVsRows; ++r) v[r] = in ? v[r] + a[r][c] * bv[c] : v[r];
+        }
+#pragma unroll
+        for (int r = 0; r < kVsRows; ++r) v[r] = vs_butterfly(v[r], G);
+#pragma unroll
+        for (int r = 0; r < kVsRows; ++r) {
+            const int i = i0 + r * (kVsThreads >> lg);
+            if (q == 0 && i < n) x[i] = (T)v[r];
+        }
+        return;
+    }
+    for (int i = i0; i < n; i += kVsThreads >> lg) {
         const double *row = Ainv + i * n;
         double v = 0.0;
         for (int j = q; j < n; j += G) v += row[j] * (double)b[j];
@@ -539,152 +733,152 @@ __device__ inline void coarse_solve_lds(int n, const double *Ainv, const T *b, T
     }
 }
 
-// V-cycle over levels [l0, nlev), l0 >= 1, on the LDS image of their
-// storage, with the arithmetic of vcycle_block_dev per cell:
-//   pre-smoothing  red x = b / d and black GS from its red neighbours' b / d
-//                  in one pass, then kSmallSweeps - 1 more red | black sweeps
-//   post-smoothing red x += P e, then kSmallSweeps x (black GS | red GS)
-//                  (black x is overwritten by its GS update, so only red
-//                  cells take the prolonged correction)
-// Thread k takes the k-th red and the k-th black cell of a level (x extent
-// even), a pair in one row: row = y + ny z = k / (nx / 2), red at
-// x = 2 (k mod nx / 2) + ((y + z) & 1), black at x ^ 1.  The host runs this
-// kernel only when every level has at most 2 kSBThreads cells, so each
-// thread owns at most one pair per level and keeps it in registers for all
-// passes of a side of the cycle: its neighbour indices, b, 1 / diag and the
-// coefficients of its faces.  A pass then issues only the reads of the
-// neighbours' x and one write per cell, where recomputing the indices (an
-// integer division) and re-reading the coefficients took most of the issue
-// slots of a pass (bubble 256 x 512: 2.09 -> 1.90 ms per step, with
-// bit-identical results).
-// Faces on walls hold 0 on these levels (coarsen_cell), so every axis is
-// indexed as periodic: the wrapped neighbour of a cell on a wall enters with
-// weight 0, where the masked stencils add 0 for the missing neighbour.
-template <typename T, int DIM>
-struct LdsPair {
-    int c[2];              // red, black
-    int nb[2][2 * DIM];    // wrapped neighbours: x low, x high, y low, y high (, z low, z high)
-    int ia[3];             // coordinates of the red cell
-    T b[2], invd[2];
-    T cw[2][2 * DIM];      // coefficients of the faces towards nb, in the same order
-};
-
-template <typename T, int DIM>
-__device__ inline void load_lds_pair(const Level<T> &lv, int k, LdsPair<T, DIM> &P) {
-    const int nx = (int)lv.g.n[0], ny = (int)lv.g.n[1], nz = DIM == 3 ? (int)lv.g.n[2] : 1;
-    const int nxy = nx * ny;
-    const int row = k / (nx >> 1);   // y + ny z
-    const int z = DIM == 3 ? row / ny : 0;
-    const int y = row - z * ny;
-    const int xr = 2 * (k - row * (nx >> 1)) + ((y + z) & 1);
-    P.ia[0] = xr;
-    P.ia[1] = y;
-    P.ia[2] = z;
+// One side of the cycle on one level (NP pairs per thread; X, R: x and
+// residual by colour, half = N / 2).
+template <typename T, int DIM, int NP>
+__device__ inline void vs_down(VsPair<T, DIM> (&P)[NP], T *X, T *R, int half) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int x = q ? xr ^ 1 : xr;
-        const int c = x + nx * row;
-        int *nb = P.nb[q];
-        P.c[q] = c;
-        nb[0] = x > 0 ? c - 1 : c + nx - 1;
-        nb[1] = x < nx - 1 ? c + 1 : c + 1 - nx;
-        nb[2] = y > 0 ? c - nx : c + nx * (ny - 1);
-        nb[3] = y < ny - 1 ? c + nx : c - nx * (ny - 1);
-        if (DIM == 3) {
-            nb[2 * DIM - 2] = z > 0 ? c - nxy : c + nxy * (nz - 1);
-            nb[2 * DIM - 1] = z < nz - 1 ? c + nxy : c - nxy * (nz - 1);
-        }
-        P.b[q] = lv.b[c];
-        P.invd[q] = lv.invd[c];
+    for (int p = 0; p < NP; ++p)
+        if (P[p].on) X[P[p].k] = P[p].v[0] = P[p].b[0] * P[p].invd[0];
+    __syncthreads();
+    for (int sw = 0;; ++sw) {
 #pragma unroll
-        for (int a = 0; a < DIM; ++a) {
-            P.cw[q][2 * a] = lv.cs[a][c];
-            P.cw[q][2 * a + 1] = lv.cs[a][nb[2 * a + 1]];
-        }
-    }
-}
-
-// sum over the faces of cell Q of the pair of cs * v(neighbour)
-template <int Q, typename T, int DIM, typename V>
-__device__ inline T pair_offsum(const LdsPair<T, DIM> &P, V v) {
-    T acc = 0.0;
-#pragma unroll
-    for (int i = 0; i < 2 * DIM; ++i) acc = fmar(P.cw[Q][i], v(P.nb[Q][i]), acc);
-    return acc;
-}
-
-// Gauss-Seidel update of cell Q of the pair from its neighbours' current x
-template <int Q, typename T, int DIM>
-__device__ inline void pair_gs(const LdsPair<T, DIM> &P, T *x) {
-    x[P.c[Q]] = (P.b[Q] + pair_offsum<Q>(P, [&](int e) { return x[e]; })) * P.invd[Q];
-}
-
-// residual b - A x at cell Q of the pair
-template <int Q, typename T, int DIM>
-__device__ inline T pair_residual(const LdsPair<T, DIM> &P, const T *s, const T *x) {
-    const T xc = x[P.c[Q]];
-    T acc = s[P.c[Q]] * xc;
-#pragma unroll
-    for (int i = 0; i < 2 * DIM; ++i) acc = fmar(P.cw[Q][i], xc - x[P.nb[Q][i]], acc);
-    return P.b[Q] - acc;
-}
-
-template <typename T, int DIM>
-__device__ __forceinline__ void vcycle_lds_dev(const Slot<T> &S, int l0, char *lds, const char *base) {
-    const int L = S.nlev;
-    const int tid = (int)threadIdx.x;
-    LdsPair<T, DIM> own;   // pair tid of the current level, if the level has one
-    auto load_own = [&](const Level<T> &lv) {
-        if (tid < (int)lv.g.N / 2) load_lds_pair(lv, tid, own);
-    };
-    auto each_pair = [&](const Level<T> &lv, auto body) {
-        if (tid < (int)lv.g.N / 2) body(own);
-    };
-    using P_t = LdsPair<T, DIM>;
-    for (int l = l0; l < L - 1; ++l) {
-        const Level<T> lv = lds_level<T, DIM>(S.lev[l], lds, base);
-        const Level<T> lc = lds_level<T, DIM>(S.lev[l + 1], lds, base);
-        load_own(lv);
-        // zero-guess smoothing: red x = b / d, black GS from those values
-        each_pair(lv, [&](const P_t &P) {
-            lv.x[P.c[0]] = P.b[0] * P.invd[0];
-            lv.x[P.c[1]] = (P.b[1] + pair_offsum<1>(P, [&](int e) { return lv.b[e] * lv.invd[e]; })) * P.invd[1];
-        });
+        for (int p = 0; p < NP; ++p)
+            if (P[p].on) X[half + P[p].k] = P[p].v[1] = vs_gs<1>(P[p], X);
         __syncthreads();
-        for (int sw = 1; sw < kSmallSweeps; ++sw) {
-            each_pair(lv, [&](const P_t &P) { pair_gs<0>(P, lv.x); });
-            __syncthreads();
-            each_pair(lv, [&](const P_t &P) { pair_gs<1>(P, lv.x); });
-            __syncthreads();
-        }
-        each_pair(lv, [&](const P_t &P) {
-            lv.r[P.c[0]] = pair_residual<0>(P, lv.s, lv.x);
-            lv.r[P.c[1]] = pair_residual<1>(P, lv.s, lv.x);
-        });
-        __syncthreads();
-        LDS_LOOP(lc.g.N) restrict_cell<T, DIM>(lv.g, lc.g, lv.r, lc.b, c);
+        if (sw + 1 >= kSmallSweeps) break;
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (P[p].on) X[P[p].k] = P[p].v[0] = vs_gs<0>(P[p], X + half);
         __syncthreads();
     }
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+        if (P[p].on) {
+            R[P[p].k] = vs_residual<0>(P[p], X + half);
+            R[half + P[p].k] = vs_residual<1>(P[p], X);
+        }
+    __syncthreads();
+}
+// out: x in cell order
+template <typename T, int DIM, int NP>
+__device__ inline void vs_up(VsPair<T, DIM> (&P)[NP], const VsGeo &gf, const VsGeo &gc, const T *xc, T *X, int half,
+                             T *out) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+        if (P[p].on) X[P[p].k] = P[p].v[0] = P[p].v[0] + prolong_at<T, DIM>(gf, gc, xc, P[p].ia);
+    __syncthreads();
+    for (int sw = 0; sw < kSmallSweeps; ++sw) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (P[p].on) X[half + P[p].k] = P[p].v[1] = vs_gs<1>(P[p], X);
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (P[p].on) {
+                P[p].v[0] = vs_gs<0>(P[p], X + half);
+                if (sw + 1 < kSmallSweeps) X[P[p].k] = P[p].v[0];
+            }
+        if (sw + 1 < kSmallSweeps) __syncthreads();
+    }
+    using V = typename VsTwo<T>::type;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+        if (P[p].on) {
+            V t;
+            t.x = P[p].par ? P[p].v[1] : P[p].v[0];
+            t.y = P[p].par ? P[p].v[0] : P[p].v[1];
+            *(V *)(out + 2 * P[p].k) = t;
+        }
+    __syncthreads();
+}
+
+// The whole V-cycle: b of level l0 and x of level l0 are the level's arrays.
+// skip: stop once the loads have been issued (nothing is written).  fin: see
+// the kernel.
+template <typename T, int DIM, typename FIN>
+__device__ __forceinline__ void vcycle_small_dev(const VsArgs<T, DIM> &A, T *lds, int skip, FIN fin) {
+    constexpr int NL = kVsLevels<DIM>;
+    const int ns = A.ns, n = A.n, tid = (int)threadIdx.x;
+    VsPair<T, DIM> top[2], low[NL - 1][1];
+    // loads of every level and of the coarsest inverse (a level the cycle does
+    // not have: those of pair 0 of level l0, unused)
+    vs_index(A.g[0], tid, top[0]);
+    vs_index(A.g[0], tid + kVsThreads, top[1]);
+    VsRaw<T> rt[2], rl[NL - 1];
+    vs_load(A, 0, top[0], rt[0]);
+    vs_load(A, 0, top[1], rt[1]);
+#pragma unroll
+    for (int j = 1; j < NL; ++j) {
+        vs_index(A.g[j], j < ns ? tid : 1 << 19, low[j - 1][0]);
+        vs_load(A, j, low[j - 1][0], rl[j - 1]);
+    }
+    double ai[kVsRows][kVsCols];
+    vs_load_inverse(n, A.Ainv, ai);
+    if (skip) return;
+    fin();
+    vs_take(rt[0], top[0]);
+    vs_take(rt[1], top[1]);
+#pragma unroll
+    for (int j = 1; j < NL; ++j) vs_take(rl[j - 1], low[j - 1][0]);
+    // LDS: x, r of level l0; b, x, r of the levels below; b, x of the coarsest
+    T *X[NL], *R[NL], *B[NL + 1];
+    int half[NL];
     {
-        const Level<T> lc = lds_level<T, DIM>(S.lev[L - 1], lds, base);
-        coarse_solve_lds<T>((int)lc.g.N, lds_image(lds, base, S.Ainv), lc.b, lc.x);
-        __syncthreads();
-    }
-    for (int l = L - 2; l >= l0; --l) {
-        const Level<T> lv = lds_level<T, DIM>(S.lev[l], lds, base);
-        const Level<T> lc = lds_level<T, DIM>(S.lev[l + 1], lds, base);
-        load_own(lv);
-        each_pair(lv, [&](const P_t &P) {
-            lv.x[P.c[0]] = lv.x[P.c[0]] + prolong_at<T, DIM>(lv.g, lc.g, lc.x, P.ia);
-        });
-        __syncthreads();
-        for (int sw = 0; sw < kSmallSweeps; ++sw) {
-            each_pair(lv, [&](const P_t &P) { pair_gs<1>(P, lv.x); });
-            __syncthreads();
-            each_pair(lv, [&](const P_t &P) { pair_gs<0>(P, lv.x); });
-            __syncthreads();
+        T *o = lds;
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const int N = j < ns ? vs_cells<DIM>(A.g[j]) : 0;
+            half[j] = N / 2;
+            B[j] = o;
+            if (j) o += N;
+            X[j] = o;
+            R[j] = o + N;
+            o += 2 * N;
         }
+        B[NL] = o;   // coarsest b; x follows
     }
+    T *const bc = B[NL], *const xcs = B[NL] + n;
+    auto restrict_to = [&](int j, const T *r) {   // onto level j (of the cycle's levels) from the one above
+        const VsGeo &gc = A.g[j];
+        if (tid < vs_cells<DIM>(gc)) {
+            int I[3];
+            const int t = small_div(tid, gc.n[0]);
+            I[0] = tid - t * gc.n[0];
+            I[2] = DIM == 3 ? small_div(t, gc.n[1]) : 0;
+            I[1] = t - I[2] * gc.n[1];
+            (j == ns ? bc : B[j])[tid] = vs_restrict<T, DIM>(A.g[j - 1], gc, r, I);
+        }
+        __syncthreads();
+    };
+    if (ns == 0) {
+        for (int c = tid; c < n; c += kVsThreads) bc[c] = A.b[c];
+        __syncthreads();
+    } else {
+        vs_down<T, DIM, 2>(top, X[0], R[0], half[0]);
+        restrict_to(1, R[0]);
+    }
+#pragma unroll
+    for (int j = 1; j < NL; ++j)
+        if (j < ns) {
+            using V = typename VsTwo<T>::type;
+            VsPair<T, DIM>(&P)[1] = low[j - 1];
+            if (P[0].on) vs_order(P[0], ((const V *)B[j])[P[0].k], P[0].b);
+            vs_down<T, DIM, 1>(P, X[j], R[j], half[j]);
+            restrict_to(j + 1, R[j]);
+        }
+    vs_coarse<T>(n, A.Ainv, ai, bc, xcs);
+    __syncthreads();
+    if (ns == 0) {
+        for (int c = tid; c < n; c += kVsThreads) A.x[c] = xcs[c];
+        return;
+    }
+#pragma unroll
+    for (int j = NL - 1; j >= 1; --j)
+        if (j < ns)
+            vs_up<T, DIM, 1>(low[j - 1], A.g[j], A.g[j + 1], j + 1 == ns ? xcs : R[j + 1 < NL ? j + 1 : 0], X[j], half[j],
+                             R[j]);
+    vs_up<T, DIM, 2>(top, A.g[0], A.g[1], ns == 1 ? xcs : R[1], X[0], half[0], A.x);
 }
 
 // In-place Gauss-Jordan inversion of the n x n SPD matrix held in A (no

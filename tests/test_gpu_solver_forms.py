@@ -84,3 +84,15 @@ def test_coarse_setup_forms(n, per, precision):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_one_reduction_forms(n, per, precision):
     assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
+
+
+# the one-workgroup V-cycle: one, two and three swept levels, no swept level
+# (343 and 270 coarsest cells, inverse read from memory), 121 coarsest cells
+# below two swept levels, and rows of one pair
+@pytest.mark.parametrize("n,per", [((128, 64), (True, False)), ((96, 96), (False, False)), ((88, 88), (True, True)),
+                                   ((512, 8), (True, False)), ((14, 14, 14), (True, False, True)),
+                                   ((18, 10, 12), (False, True, True)), ((24, 24, 48), (False, True, False)),
+                                   ((16, 16, 32), (True, True, True)), ((8, 32, 32), (True, False, True))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_small_level_cycle_forms(n, per, precision):
+    assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
