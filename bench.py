@@ -122,16 +122,15 @@ def recorded_traffic(workload, kernel_class):
 # Kernel classes of the library's per-kernel timing, by kernel name (the
 # template arguments after the name are matched by the workload filters).
 KERNEL_CLASSES = {
-    "smooth": ("k_presmooth_pair", "k_presmooth", "k_gs_color", "k_presmooth_march", "k_gs_color_march", "k_gs_red_rz"),
+    "smooth": ("k_presmooth_pair", "k_presmooth", "k_presmooth_march", "k_sweep3"),
     "residual": ("k_residual", "k_residual_march"),
     "restrict": ("k_restrict3_lds", "k_restrict3_pair", "k_restrict"),
-    "prolong": ("k_prolong_add3",),
     "coarse_solve": ("k_vcycle_lds", "k_vcycle_block"),
-    "mg_down": ("k_down_tile2", "k_down_tile2_cg", "k_down3_tile"),
-    "mg_up": ("k_up_tile2", "k_up_tile2_cg", "k_up3_tile"),
+    "mg_down": ("k_down_tile2", "k_down_tile2_cg", "k_cg_down_tile2", "k_down3_tile"),
+    "mg_up": ("k_up_tile2", "k_up_tile2_cg", "k_cg_up_tile2", "k_up3_tile"),
     "pcg_apply": ("k_pcg_apply3_march", "k_pcg_apply_slot", "k_pcg_ch_lap", "k_pcg_ch_apply"),
     "pcg_update": ("k_pcg_update", "k_pcg_fin_rr"),
-    "pcg_dot": ("k_pcg_rz",),
+    "pcg_dot": ("k_pcg_rz", "k_pcg_rz3"),
     # the batched tiled form (one launch per sweep over the tiles of all problems)
     "t_down": ("k_t_down2",),
     "t_up": ("k_t_up2",),

@@ -20,9 +20,10 @@
 //   * 2D levels above kSBCells cells: two tile kernels per level, one for
 //     the way down (pre-smoothing, residual, restriction) and one for the
 //     way up (prolongation, black sweep, red sweep), on LDS tiles with halos;
-//   * 3D levels above kSBCells cells: one grid-wide kernel per pass (fused
-//     zero-guess pre-smoothing, residual, restriction, prolongation, black
-//     sweep, red sweep);
+//   * 3D levels above kSBCells cells: zero-guess pre-smoothing, residual and
+//     restriction as one grid-wide kernel each, prolongation, black and red
+//     sweep in one kernel that marches along z (k_sweep3); levels of few cells
+//     in two tile kernels as in 2D;
 //   * all smaller levels: ONE single-workgroup kernel that holds their
 //     coefficients in registers and x in LDS.
 // Reductions are deterministic and fence-free: per-block partials from a
@@ -81,66 +82,6 @@ template <typename T>
 struct Pair2 {
     T v[2];
 };
-
-// 3D prolongation x += P e, one thread per coarse cell: the 3 x 3 x 3 coarse
-// neighbourhood (parent, lower and upper side neighbour per axis, from
-// pro_axis) is loaded once and the eight children are updated with the taps,
-// weights and summation order of prolong_at.  Needs an even fine x extent.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_prolong_add3(Geo gf, Geo gc, const T *__restrict__ xc,
-                                                         T *__restrict__ x, const int *__restrict__ done) {
-    if (*done) return;
-    using R = T;
-    GRID_LOOP(gc.N) {
-        int I[3];
-        coords_of<3>(gc, c, I);
-        int q[3][3];   // [axis][0: parent, 1: lower child's neighbour, 2: upper child's neighbour]
-        R w0[3][2], w1[3][2];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            q[a][0] = I[a];
-#pragma unroll
-            for (int sd = 0; sd < 2; ++sd) {
-                int c0, c1;
-                pro_axis<R>(2 * I[a] + sd, (int)gc.n[a], gc.per[a], c0, c1, w0[a][sd], w1[a][sd]);
-                q[a][1 + sd] = c1;
-            }
-        }
-        const int nx = (int)gc.n[0], nxy = nx * (int)gc.n[1];
-        R X[3][3][3];
-#pragma unroll
-        for (int z = 0; z < 3; ++z)
-#pragma unroll
-            for (int y = 0; y < 3; ++y)
-#pragma unroll
-                for (int xx = 0; xx < 3; ++xx) X[z][y][xx] = (R)xc[q[2][z] * nxy + q[1][y] * nx + q[0][xx]];
-        const int fnx = (int)gf.n[0], fnxy = fnx * (int)gf.n[1];
-#pragma unroll
-        for (int dz = 0; dz < 2; ++dz)
-#pragma unroll
-            for (int dy = 0; dy < 2; ++dy) {
-                const int f = 2 * I[0] + fnx * (2 * I[1] + dy) + fnxy * (2 * I[2] + dz);
-                Pair2<T> pr = *(const Pair2<T> *)(x + f);
-#pragma unroll
-                for (int dx = 0; dx < 2; ++dx) {
-                    R v = 0.0;
-#pragma unroll
-                    for (int dz2 = 0; dz2 < 2; ++dz2) {
-                        const R wz = dz2 ? w1[2][dz] : w0[2][dz];
-                        const int zi = dz2 ? 1 + dz : 0;
-#pragma unroll
-                        for (int dy2 = 0; dy2 < 2; ++dy2) {
-                            const R wyz = wz * (dy2 ? w1[1][dy] : w0[1][dy]);
-                            const int yi = dy2 ? 1 + dy : 0;
-                            v = pro_row(v, wyz, w0[0][dx], X[zi][yi][0], w1[0][dx], X[zi][yi][1 + dx]);
-                        }
-                    }
-                    pr.v[dx] = (T)((T)pr.v[dx] + v);
-                }
-                *(Pair2<T> *)(x + f) = pr;
-            }
-    }
-}
 
 // 3D restriction through LDS: a workgroup takes a tile of kRCX x kRCY x kRCZ
 // coarse cells and stages the fine cells 2I-1 .. 2I+2 of all of them once
@@ -214,13 +155,6 @@ __global__ void __launch_bounds__(kBlock) k_restrict3_lds(Geo gf, Geo gc, const 
         }
     }
     bc[(I[2] * (int)gc.n[1] + I[1]) * (int)gc.n[0] + I[0]] = (T)acc;
-}
-
-template <typename T, typename TB, int DIM>
-__global__ void __launch_bounds__(kBlock) k_gs_color(Level<T> L, const TB *__restrict__ b, T *__restrict__ x,
-                                                     int color, const int *__restrict__ done) {
-    if (*done) return;
-    GRID_LOOP(L.g.N) gs_color_cell<T, TB, DIM>(L, b, x, color, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -806,21 +740,6 @@ __global__ void __launch_bounds__(kBlock) k_presmooth_march(Level<T> L, const TB
     });
 }
 
-// in-place Gauss-Seidel update of one colour
-template <typename T, typename TB>
-__global__ void __launch_bounds__(kBlock) k_gs_color_march(Level<T> L, const TB *__restrict__ b, T *__restrict__ x,
-                                                           int color, const int *__restrict__ done, int ncolx,
-                                                           int ncol, int ntiles) {
-    if (*done) return;
-    using R = T;
-    __shared__ SweepRing<T> ring;
-    march_sweep<T>(L.g, ncolx, ncol, ntiles, ring, [&](int e) { return x[e]; },
-                   [&](int c, const int ia[3], T vc, const T nbv[3][2]) {
-                       if (((ia[0] + ia[1] + ia[2]) & 1) != color) return;
-                       x[c] = (T)(((R)b[c] + march_offsum<T>(L, c, ia, vc, nbv)) * (R)L.invd[c]);
-                   });
-}
-
 // r = b - A x
 template <typename T, typename TB>
 __global__ void __launch_bounds__(kBlock) k_residual_march(Level<T> L, const TB *__restrict__ b,
@@ -1184,6 +1103,433 @@ __global__ void __launch_bounds__(kT3Threads) k_up3_tile(Level<T> L, Geo gc, con
     }
 }
 
+// ---------------------------------------------------------------------------
+// 3D post-smoothing in one pass over the level: red values, black sweep, red
+// sweep (and the r.z partials of CG) on columns that march along z.
+//   PRO   red start = x + P e (the way up: x the pre-smoothed one, e the
+//         coarse correction)
+//   !PRO  red start = b / d (the symmetric sweep from zero that ends a
+//         truncated cycle)
+// A block owns kUX x kUY cells of every plane of its z chunk.  Its waves split
+// by role, each two planes behind the one before: the first form the red
+// start values with a halo of two cells, the next the black values with a
+// halo of one, the last the red values of the owned cells, and store the
+// pair.  Values pass through rings of four planes in LDS, stored by x-pair
+// (one red and one black cell; the red one is at x = 2 m + parity), so one
+// barrier per plane is enough, and every role loads the next plane's operands
+// before it works on this one's.  The stored x may not be the one read
+// (neighbouring blocks still read their halos): the way down leaves the
+// pre-smoothed x in the level's r array.
+// Per-cell arithmetic and order are those of prolong_at / presmooth_cell and
+// gs_color_cell (a neighbour past a wall enters as 0 with weight 0).
+// What bounds it is memory: x, b, 1 / d and three coefficients are read once
+// (b, 1 / d and coefficients of the halo twice, from the caches) and x is
+// written once, 56 B per cell in FP64, where three passes moved 129.
+// Measured against the three passes (prolongation, black, red), the second on
+// the same inputs: 128^3 FP64 46.6 us -> 24.5, FP32 29.6 -> 16.9; 96^3 FP64
+// 26.5 -> 15.6, FP32 19.1 -> 11.2; 80^3 FP64 19.4 -> 13.1.  128^3 FP64 moves
+// 117 MB, 24.6 us at the rate of a large copy; the smaller levels are bound
+// by the cache lines the stride-2 loads touch and by the halo.  A tile of 16
+// rows reads less halo and is level at 128^3 (23.8) but leaves CUs idle below
+// (96^3 16.8, 80^3 14.3); 512^3: 438 ms per solve with it, 423 with 8.
+// ---------------------------------------------------------------------------
+constexpr int kUX = 32, kUY = 8, kUM = kUX / 2 + 2;   // owned cells; pairs per row with one more on each side
+constexpr int kUPlanes = 16, kUBlocks = 256;
+
+// LDS of one plane is written before and read after: the barrier alone, without
+// waiting for the loads in flight
+__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Cell (x, y, z) wrapped on periodic axes; false past a wall (indices inside).
+__device__ inline bool wrap_axis(int v, int n, int per, int &w) {
+    w = v < 0 ? v + n : (v >= n ? v - n : v);
+    const bool ok = (v >= 0 && v < n) || per != 0;
+    w = w < 0 ? 0 : (w >= n ? n - 1 : w);   // past a wall, or past the tile's part of the grid
+    return ok;
+}
+
+// Element at byte offset off of a plane (a scalar base and one vector register)
+template <typename T>
+__device__ inline T plane_at(const T *plane, unsigned off) {
+    return *(const T *)((const char *)plane + off);
+}
+
+// The cells of one lane of the black or red role: byte offsets in a plane of
+// the cell and of its upper x and y neighbours (the cell itself where there is
+// none), by parity of the step.
+struct SweepAt {
+    unsigned c[2], hx[2], hy[2];
+};
+template <typename T>
+__device__ inline void sweep_at(const Geo &g, int gx, int gy, int p, SweepAt &A) {
+    const int c = gx + g.n[0] * gy;
+    const int hx = nb_hi(g, c, gx, 0), hy = nb_hi(g, c, gy, 1);
+    A.c[p] = (unsigned)c * sizeof(T);
+    A.hx[p] = (unsigned)(hx >= 0 ? hx : c) * sizeof(T);
+    A.hy[p] = (unsigned)(hy >= 0 ? hy : c) * sizeof(T);
+}
+// Operands of a Gauss-Seidel value: b, 1 / d and the face coefficients x low,
+// x high, .., z high.  The coefficient of a face past a wall may be any: the
+// value it multiplies is 0.
+template <typename T>
+struct SweepOps {
+    T b, invd, w[6];
+};
+template <typename T, typename TB>
+__device__ inline void sweep_load(const Level<T> &L, const TB *b, const SweepAt &A, int p, int gz, SweepOps<T> &o) {
+    static_assert(sizeof(T) == sizeof(TB), "offsets in bytes of both");
+    const int nxy = L.g.n[0] * L.g.n[1];
+    const long long z = (long long)gz * nxy, zh = (long long)(gz + 1 < L.g.n[2] ? gz + 1 : (L.g.per[2] ? 0 : gz)) * nxy;
+    o.b = (T)plane_at(b + z, A.c[p]);
+    o.invd = plane_at(L.invd + z, A.c[p]);
+    o.w[0] = plane_at(L.cs[0] + z, A.c[p]);
+    o.w[1] = plane_at(L.cs[0] + z, A.hx[p]);
+    o.w[2] = plane_at(L.cs[1] + z, A.c[p]);
+    o.w[3] = plane_at(L.cs[1] + z, A.hy[p]);
+    o.w[4] = plane_at(L.cs[2] + z, A.c[p]);
+    o.w[5] = plane_at(L.cs[2] + zh, A.c[p]);
+}
+template <typename T>
+__device__ inline T sweep_gs(const SweepOps<T> &o, const T (&v)[6]) {
+    T acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) acc = fmar(o.w[i], v[i], acc);
+    return (o.b + acc) * o.invd;
+}
+
+// One role of the pass: body(s, K, o) for the steps from FIRST on, in whole
+// groups of four until `last` is past, a barrier after every one of `total`
+// steps; load(s, P, o) fetches a step's operands two steps ahead of its body,
+// into one of two sets of registers.  The group has no branch in it: with a
+// test around a load or a body the compiler cannot know which loads are in
+// flight and waits for all of them in every step, which makes a step as long
+// as the way to memory.  (The up to three steps past `last` work on clamped
+// planes and write only ring planes that are no longer read.)  K = s mod 4
+// and P = s mod 2 are constants, so that ring planes are immediate offsets
+// and a lane's two alternating cells cost no arithmetic.
+template <int FIRST, typename O, typename LOAD, typename BODY>
+__device__ __forceinline__ void sweep_role(int last, int total, LOAD load, BODY body) {
+    O o0, o1;
+    load(FIRST, std::integral_constant<int, FIRST & 1>(), o0);
+    load(FIRST + 1, std::integral_constant<int, (FIRST + 1) & 1>(), o1);
+    for (int s = 0; s < FIRST; ++s) lds_barrier();
+    auto step = [&](int s, auto J, O &o) {
+        constexpr int k = (FIRST + decltype(J)::value) & 3;
+        body(s, std::integral_constant<int, k>(), o);
+        load(s + 2, std::integral_constant<int, (k & 1)>(), o);
+        lds_barrier();
+    };
+    int s = FIRST;
+    for (; s <= last; s += 4) {
+        step(s, std::integral_constant<int, 0>(), o0);
+        step(s + 1, std::integral_constant<int, 1>(), o1);
+        step(s + 2, std::integral_constant<int, 2>(), o0);
+        step(s + 3, std::integral_constant<int, 3>(), o1);
+    }
+    for (; s < total; ++s) lds_barrier();
+}
+
+// Pairs per plane of the red start / black / owned values, coarse cells per
+// plane that the red start reads, first wave of the black / red role, threads.
+struct SweepShape {
+    static constexpr int E = (kUY + 4) * kUM, B = (kUY + 2) * kUM, R = kUX / 2 * kUY;
+    static constexpr int CX = kUX / 2 + 4, CY = kUY / 2 + 4, C = CX * CY;
+    static constexpr int wB = (E + kWave - 1) / kWave, wR = wB + (B + kWave - 1) / kWave, nR = (R + kWave - 1) / kWave;
+    static constexpr int threads = (wR + nR) * kWave;
+};
+
+// r.z, sum z, sum r of a thread's pair, and the block's partials of them (u:
+// thread among those that own cells, whole waves)
+template <typename TR, typename T>
+__device__ inline void sweep_dots(const Pair2<TR> &r, const Pair2<T> &z, double &arz, double &az, double &ar) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        arz += (double)r.v[e] * (double)z.v[e];
+        az += (double)z.v[e];
+        ar += (double)r.v[e];
+    }
+}
+__device__ inline void sweep_partials(double arz, double az, double ar, int u, double (*ws)[SweepShape::nR],
+                                      double *p0, double *p1, double *p2) {
+    arz = wave_sum(arz);
+    az = wave_sum(az);
+    ar = wave_sum(ar);
+    if ((u & (kWave - 1)) == 0) {
+        ws[0][u / kWave] = arz;
+        ws[1][u / kWave] = az;
+        ws[2][u / kWave] = ar;
+    }
+    lds_barrier();
+    if (u == 0) {
+        arz = az = ar = 0.0;
+        for (int k = 0; k < SweepShape::nR; ++k) {
+            arz += ws[0][k];
+            az += ws[1][k];
+            ar += ws[2][k];
+        }
+        *p0 = arz;
+        *p1 = az;
+        *p2 = ar;
+    }
+}
+
+template <typename T, typename TB, bool PRO, bool DOTS, typename TR>
+__global__ void __launch_bounds__(SweepShape::threads) k_sweep3(Level<T> L, const TB *__restrict__ b,
+                                                      const T *__restrict__ xpre, Geo gc,
+                                                      const T *__restrict__ xc, T *__restrict__ x, int ntx, int ncol,
+                                                      int zc, int ntiles, const int *__restrict__ done,
+                                                      const TR *__restrict__ r, double *__restrict__ p0,
+                                                      double *__restrict__ p1, double *__restrict__ p2) {
+    using Sh = SweepShape;
+    const int tile = xcd_block();
+    if (tile >= ntiles || *done) return;
+    __shared__ T E[4][Sh::E], B[4][Sh::B], C[4][PRO ? Sh::C : 1];
+    __shared__ double ws[3][Sh::nR];
+    static_assert(Sh::C <= Sh::wB * kWave, "one coarse cell per lane of the first role");
+    const Geo &g = L.g;
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const int col = tile % ncol, z0 = (tile / ncol) * zc, z1 = z0 + zc < nz ? z0 + zc : nz;
+    const int x0 = (col % ntx) * kUX, y0 = (col / ntx) * kUY;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    // the red role is four planes behind the first; every role ends its group
+    // of four within `total` steps
+    const int steps = z1 - z0 + 6, total = steps + 4;
+    if (wave < Sh::wB) {
+        // red start of plane z0 - 2 + s, into E[s & 3]
+        const int u = (int)threadIdx.x;
+        const bool on = u < Sh::E;
+        const int ly = on ? u / kUM : 0, m = (on ? u : 0) - ly * kUM;
+        int gy;
+        const bool oky = wrap_axis(y0 - 2 + ly, ny, g.per[1], gy);
+        bool ok[2];
+        unsigned off[2];
+        int t00[2], t01[2], t10[2], t11[2];   // coarse taps (y, x) in a plane of C
+        T w0x[2], w1x[2], w0y = 0, w1y = 0;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int par = (y0 + ly + z0 + p) & 1;   // of plane z0 - 2 + s, s = p mod 2
+            int gx;
+            ok[p] = wrap_axis(x0 - 2 + 2 * m + par, nx, g.per[0], gx) && oky;
+            off[p] = (unsigned)(gx + nx * gy) * sizeof(T);
+            if (PRO) {   // weights of prolong_at; a tap past a wall has weight 0
+                int c0, c1;
+                pro_axis<T>(gx, gc.n[0], gc.per[0], c0, c1, w0x[p], w1x[p]);
+                pro_axis<T>(gy, gc.n[1], gc.per[1], c0, c1, w0y, w1y);
+                const int a0 = m + 1, a1 = a0 + (par ? 1 : -1);
+                const int b0 = (ly >> 1) + 1, b1 = b0 + ((ly & 1) ? 1 : -1);   // (y0 is even)
+                t00[p] = a0 + Sh::CX * b0;
+                t01[p] = a1 + Sh::CX * b0;
+                t10[p] = a0 + Sh::CX * b1;
+                t11[p] = a1 + Sh::CX * b1;
+            }
+        }
+        // coarse cell u of the planes around (z0 is even): plane Zc of the
+        // coarse level is at C[Zc & 3]; fine planes 2 Z and 2 Z + 1 read
+        // Z - 1, Z and Z + 1, and plane Z + 2 is stored in the first of their steps
+        const int Zf = z0 / 2 - 1;
+        T cnext = (T)0;
+        const T *cu = xc;
+        const bool con = PRO && u < Sh::C;
+        auto cplane = [&](int Z) {
+            int w;
+            (void)wrap_axis(Z, gc.n[2], gc.per[2], w);
+            return cu[(long long)w * gc.n[0] * gc.n[1]];
+        };
+        if (PRO) {
+            const int ry = u / Sh::CX, rx = u - ry * Sh::CX;
+            int cx, cy;
+            (void)wrap_axis(x0 / 2 - 2 + rx, gc.n[0], gc.per[0], cx);
+            (void)wrap_axis(y0 / 2 - 2 + ry, gc.n[1], gc.per[1], cy);
+            cu = xc + (cx + gc.n[0] * cy);
+            const T c0 = cplane(Zf - 1), c1 = cplane(Zf), c2 = cplane(Zf + 1);
+            cnext = cplane(Zf + 2);
+            if (con) {
+                C[(Zf - 1) & 3][u] = c0;
+                C[Zf & 3][u] = c1;
+                C[(Zf + 1) & 3][u] = c2;
+            }
+            lds_barrier();
+        }
+        struct Ops {
+            T a, b;
+        };
+        sweep_role<0, Ops>(
+            steps - 3, total,
+            [&](int s, auto P, Ops &o) {
+                constexpr int p = decltype(P)::value;
+                int gz;
+                (void)wrap_axis(z0 - 2 + s, nz, g.per[2], gz);
+                const long long z = (long long)gz * nx * ny;
+                if (PRO) {
+                    o.a = plane_at(xpre + z, off[p]);
+                } else {
+                    o.a = (T)plane_at(b + z, off[p]);
+                    o.b = plane_at(L.invd + z, off[p]);
+                }
+            },
+            [&](int s, auto K, const Ops &o) {
+                constexpr int k = decltype(K)::value, p = k & 1;
+                int gz;
+                const bool okz = wrap_axis(z0 - 2 + s, nz, g.per[2], gz);
+                T v;
+                if (PRO) {   // prolong_at's weights and order
+                    const int Z = Zf + (s >> 1);
+                    int c0, c1;
+                    T w0, w1;
+                    pro_axis<T>(gz, gc.n[2], gc.per[2], c0, c1, w0, w1);
+                    const T *e0 = C[Z & 3], *e1 = C[(p ? Z + 1 : Z - 1) & 3];
+                    v = pro_row((T)0, w0 * w0y, w0x[p], e0[t00[p]], w1x[p], e0[t01[p]]);
+                    v = pro_row(v, w0 * w1y, w0x[p], e0[t10[p]], w1x[p], e0[t11[p]]);
+                    v = pro_row(v, w1 * w0y, w0x[p], e1[t00[p]], w1x[p], e1[t01[p]]);
+                    v = pro_row(v, w1 * w1y, w0x[p], e1[t10[p]], w1x[p], e1[t11[p]]);
+                    v = o.a + v;
+                    if (p == 0) {
+                        if (con) C[(Z + 2) & 3][u] = cnext;
+                        cnext = cplane(Z + 3);
+                    }
+                } else {
+                    v = o.a * o.b;
+                }
+                if (on) E[k][u] = okz && ok[p] ? v : (T)0;
+            });
+        if (DOTS) lds_barrier();
+        return;
+    }
+    if (wave < Sh::wR) {
+        // black values of plane z0 - 4 + s into B[s & 3]; the red start around
+        // plane z0 - 4 + s is in E[s - 3 .. s - 1]
+        const int u = (int)threadIdx.x - Sh::wB * kWave;
+        const bool on = u < Sh::B;
+        const int ly = on ? u / kUM : 0, m = (on ? u : 0) - ly * kUM;
+        int gy;
+        const bool oky = wrap_axis(y0 - 1 + ly, ny, g.per[1], gy);
+        if (PRO) lds_barrier();
+        const int q = (ly + 1) * kUM + m;   // the pair in a plane of E
+        const int ql = m > 0 ? q - 1 : q, qh = m < kUM - 1 ? q + 1 : q;   // (the outermost pairs' outer cells are not used)
+        bool ok[2];
+        int xl[2], xh[2];
+        SweepAt A;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int par = (y0 - 1 + ly + z0 + p) & 1;
+            int gx;
+            ok[p] = wrap_axis(x0 - 2 + 2 * m + 1 - par, nx, g.per[0], gx) && oky;
+            sweep_at<T>(g, gx, gy, p, A);
+            xl[p] = par ? ql : q;
+            xh[p] = par ? q : qh;
+        }
+        sweep_role<3, SweepOps<T>>(
+            steps - 2, total,
+            [&](int s, auto P, SweepOps<T> &o) {
+                int gz;
+                (void)wrap_axis(z0 - 4 + s, nz, g.per[2], gz);
+                sweep_load(L, b, A, decltype(P)::value, gz, o);
+            },
+            [&](int s, auto K, const SweepOps<T> &o) {
+                constexpr int k = decltype(K)::value, p = k & 1;
+                int gz;
+                const bool okz = wrap_axis(z0 - 4 + s, nz, g.per[2], gz);
+                const T *e0 = E[(k + 2) & 3], *em = E[(k + 1) & 3], *ep = E[(k + 3) & 3];
+                const T v[6] = {e0[xl[p]], e0[xh[p]], e0[q - kUM], e0[q + kUM], em[q], ep[q]};
+                const T val = sweep_gs(o, v);
+                if (on) B[k][u] = okz && ok[p] ? val : (T)0;
+            });
+        if (DOTS) lds_barrier();
+        return;
+    }
+    // red values of the owned cells of plane z0 - 6 + s, and the stores; the
+    // black values around it are in B[s - 3 .. s - 1]
+    const int u0 = (int)threadIdx.x - Sh::wR * kWave, u = u0 < Sh::R ? u0 : 0;
+    const int ly = u / (kUX / 2), m = u - ly * (kUX / 2);
+    const int gy = y0 + ly, ex = x0 + 2 * m;
+    const bool own = u0 < Sh::R && ex < nx && gy < ny;
+    const int cy = own ? gy : 0, cx = own ? ex : 0;
+    const int q = (ly + 1) * kUM + m + 1;   // the pair in a plane of B
+    double arz = 0.0, az = 0.0, ar = 0.0;
+    int par[2], xl[2], xh[2];
+    SweepAt A;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        par[p] = (gy + z0 + p) & 1;
+        sweep_at<T>(g, cx + (own ? par[p] : 0), cy, p, A);
+        xl[p] = par[p] ? q : q - 1;
+        xh[p] = par[p] ? q + 1 : q;
+    }
+    if (PRO) lds_barrier();
+    const unsigned pair = (unsigned)(cx + nx * cy);
+    struct Ops {
+        SweepOps<T> g;
+        Pair2<TR> r;
+    };
+    sweep_role<6, Ops>(
+        steps - 1, total,
+        [&](int s, auto P, Ops &o) {
+            const int zz = z0 - 6 + s < nz ? z0 - 6 + s : nz - 1;
+            sweep_load(L, b, A, decltype(P)::value, zz, o.g);
+            if (DOTS) o.r = *(const Pair2<TR> *)((const char *)(r + (long long)zz * nx * ny) + pair * sizeof(TR));
+        },
+        [&](int s, auto K, const Ops &o) {
+            constexpr int k = decltype(K)::value, p = k & 1;
+            const T *b0 = B[(k + 2) & 3], *bm = B[(k + 1) & 3], *bp = B[(k + 3) & 3];
+            const T v[6] = {b0[xl[p]], b0[xh[p]], b0[q - kUM], b0[q + kUM], bm[q], bp[q]};
+            const T red = sweep_gs(o.g, v), mine = par[p] ? v[0] : v[1];
+            if (own && s < steps) {
+                Pair2<T> t;
+                t.v[0] = par[p] ? mine : red;
+                t.v[1] = par[p] ? red : mine;
+                *(Pair2<T> *)((char *)(x + (long long)(z0 - 6 + s) * nx * ny) + pair * sizeof(T)) = t;
+                if (DOTS) sweep_dots(o.r, t, arz, az, ar);
+            }
+        });
+    if (DOTS) sweep_partials(arz, az, ar, u0, ws, p0 + tile, p1 + tile, p2 + tile);
+}
+
+// The same partials in the same order as a pass of its own, for a level 0
+// that runs the tile passes: one block per block of the sweep, one thread per
+// pair of cells of its column, marching along z.  Both forms of the cycle then
+// give the same bits.
+template <typename T, typename TZ>
+__global__ void __launch_bounds__(SweepShape::nR * kWave) k_pcg_rz3(Geo g, const T *__restrict__ r,
+                                                                    const TZ *__restrict__ z,
+                                                                    const Scal *__restrict__ sc,
+                                                                    double *__restrict__ p0, double *__restrict__ p1,
+                                                                    double *__restrict__ p2, int ntx, int ncol, int zc,
+                                                                    int ntiles) {
+    const int tile = xcd_block();
+    if (tile >= ntiles || sc->done) return;
+    __shared__ double ws[3][SweepShape::nR];
+    const int nx = g.n[0], nxy = nx * g.n[1];
+    const int col = tile % ncol, z0 = (tile / ncol) * zc, z1 = z0 + zc < g.n[2] ? z0 + zc : g.n[2];
+    const int ly = (int)threadIdx.x / (kUX / 2), m = (int)threadIdx.x - ly * (kUX / 2);
+    const int ex = (col % ntx) * kUX + 2 * m, gy = (col / ntx) * kUY + ly;
+    double arz = 0.0, az = 0.0, ar = 0.0;
+    if (ex < nx && gy < g.n[1]) {
+        const int c = ex + nx * gy;
+#pragma unroll 4
+        for (int kz = z0; kz < z1; ++kz) {
+            const Pair2<T> rc = *(const Pair2<T> *)(r + c + (long long)kz * nxy);
+            const Pair2<TZ> zv = *(const Pair2<TZ> *)(z + c + (long long)kz * nxy);
+            sweep_dots(rc, zv, arz, az, ar);
+        }
+    }
+    sweep_partials(arz, az, ar, (int)threadIdx.x, ws, p0 + tile, p1 + tile, p2 + tile);
+}
+
+// Columns, planes per block (a multiple of 4) and blocks of that pass: 16
+// planes, fewer where that leaves a CU without a block (80^3 FP64 13.1 us with
+// 8 planes, 20.8 with 16), more where the blocks would outnumber the partials
+// of r.z.
+static int sweep3_grid(const Geo &g, int &ntx, int &ncol, int &zc, int &ntiles) {
+    ntx = (g.n[0] + kUX - 1) / kUX;
+    ncol = ntx * ((g.n[1] + kUY - 1) / kUY);
+    zc = kUPlanes;
+    auto blocks = [&] { return ncol * ((g.n[2] + zc - 1) / zc); };
+    while (zc > 4 && blocks() < kUBlocks) zc /= 2;
+    while (blocks() > kRedBlocks && zc < g.n[2]) zc *= 2;
+    ntiles = blocks();
+    return ntiles > 8 ? (ntiles + 7) & ~7 : ntiles;
+}
+
 // Whether level l of a 3D slot runs the tile passes: above the
 // single-workgroup part, below march_cells and at most tile_cells cells,
 // with even extents (every level that has a coarser one).
@@ -1297,36 +1643,6 @@ __global__ void __launch_bounds__(kBlock) k_pcg_rz(int N, const T *__restrict__ 
     double arz = 0.0, az = 0.0, ar = 0.0;
     GRID_LOOP(N) {
         const double rc = (double)r[c], zc = (double)z[c];
-        arz += rc * zc;
-        az += zc;
-        ar += rc;
-    }
-    const double s0 = block_sum(arz, lds);
-    const double s1 = singular ? block_sum(az, lds) : 0.0;
-    const double s2 = singular ? block_sum(ar, lds) : 0.0;
-    if (threadIdx.x == 0) {
-        p0[blockIdx.x] = s0;
-        p1[blockIdx.x] = s1;
-        p2[blockIdx.x] = s2;
-    }
-}
-
-// The last pass of a 3D preconditioner (the red sweep of level 0) with the
-// partials of k_pcg_rz: the same cells per thread and block (grid-stride
-// over grid_red(N) blocks) and the same sums, so the partials are those of
-// the separate pass bit for bit; the z of a black cell is read back, the
-// z of a red cell is its new value.
-template <typename T, typename TB, int DIM, typename TR>
-__global__ void __launch_bounds__(kBlock) k_gs_red_rz(Level<T> L, const TB *__restrict__ b, T *__restrict__ x,
-                                                      const TR *__restrict__ r, const Scal *__restrict__ sc,
-                                                      double *__restrict__ p0, double *__restrict__ p1,
-                                                      double *__restrict__ p2, int singular) {
-    if (sc->done) return;
-    __shared__ double lds[kBlock / kWave];
-    double arz = 0.0, az = 0.0, ar = 0.0;
-    GRID_LOOP(L.g.N) {
-        gs_color_cell<T, TB, DIM>(L, b, x, 0, c);
-        const double rc = (double)r[c], zc = (double)x[c];
         arz += rc * zc;
         az += zc;
         ar += rc;
@@ -1582,28 +1898,35 @@ static void tile_grid2(const Geo &g, int &ntx, int &ntiles, int &grid) {
 }
 
 // The r.z partials of CG (k_pcg_rz) taken by the last pass of a 3D
-// preconditioner, the red sweep of level 0 (k_gs_red_rz); *taken is set
-// when that pass ran in the grid-wide form, which is the one that can.
+// preconditioner, k_sweep3 on level 0: *nparts is the number of partials
+// where that pass took them, one per block.
 template <typename TR>
 struct RzFuse {
     const TR *r;
-    const Scal *sc;
     double *p0, *p1, *p2;
-    int singular;
-    bool *taken;
+    int *nparts;
 };
 
-// red sweep of level 0, with the r.z partials when rz is given
-template <typename T, typename TB, int DIM, typename TR>
-static void gs_red_last(Level<T> &L, const TB *b, T *x, const int *done, hipStream_t st, const RzFuse<TR> *rz) {
+// The post-smoothing of a 3D level in one pass (k_sweep3): from the
+// pre-smoothed xpre and the coarse correction xc (PRO), or the symmetric sweep
+// from zero; x != xpre; with the r.z partials when rz is given.
+template <bool PRO, typename T, typename TB, typename TR>
+static void sweep3(const Level<T> &L, const TB *b, const T *xpre, const Geo &gc, const T *xc, T *x, const int *done,
+                   hipStream_t st, const RzFuse<TR> *rz) {
+    int ntx, ncol, zc, ntiles;
+    const int grid = sweep3_grid(L.g, ntx, ncol, zc, ntiles);
     const double N = (double)L.g.N;
-    const double bytes = sizeof(T) * (3.5 + DIM) * N + (sizeof(TB) - sizeof(T)) * N;
-    if (rz) {
-        LAUNCHR(K_SMOOTH, bytes + sizeof(TR) * N, (k_gs_red_rz<T, TB, DIM, TR>), L.g.N, st, L, b, x, rz->r, rz->sc,
-                rz->p0, rz->p1, rz->p2, rz->singular);
-        *rz->taken = true;
+    // b, 1 / d, cs, (x and e) in; x out
+    const double bytes = sizeof(T) * (5 + (PRO ? 1 : 0)) * N + sizeof(TB) * N + (PRO ? sizeof(T) * (double)gc.N : 0.0);
+    if (rz && ntiles <= kRedBlocks) {
+        TLAUNCH(K_SMOOTH, bytes + sizeof(TR) * N, (k_sweep3<T, TB, PRO, true, TR>), dim3(grid),
+                dim3(SweepShape::threads), st, L, b, xpre, gc, xc, x, ntx, ncol, zc, ntiles, done, rz->r, rz->p0,
+                rz->p1, rz->p2);
+        *rz->nparts = ntiles;
     } else {
-        LAUNCH(K_SMOOTH, bytes, (k_gs_color<T, TB, DIM>), L.g.N, st, L, b, x, 0, done);
+        TLAUNCH(K_SMOOTH, bytes, (k_sweep3<T, TB, PRO, false, TR>), dim3(grid), dim3(SweepShape::threads), st, L, b,
+                xpre, gc, xc, x, ntx, ncol, zc, ntiles, done, (const TR *)nullptr, (double *)nullptr,
+                (double *)nullptr, (double *)nullptr);
     }
 }
 
@@ -1641,27 +1964,32 @@ static void vcycle_down(Slot<T> &S, int l, const TB *b, T *x, const int *done, h
                 dim3(kT3Threads), st, lv, S.lev[l + 1].g, b, S.lev[l + 1].b, ntx, nty, ntiles, done);
         return;
     }
+    // the pre-smoothed x goes to the level's r array and the residual to x:
+    // the way up reads the one while it writes the other
+    T *const xp = lv.r;
+    Level<T> lr = lv;
+    lr.r = x;
     if (DIM == 3 && lv.g.N >= S.march_cells) {
         int ncolx, ncol, ntiles;
         const int grid = march_sweep_grid(lv.g, ncolx, ncol, ntiles);
         TLAUNCH(K_SMOOTH, W * (3 + DIM) * N + WB * N, (k_presmooth_march<T, TB>), dim3(grid), dim3(kBlock), st, lv, b,
-                x, done, ncolx, ncol, ntiles);
-        TLAUNCH(K_RESIDUAL, W * (4 + DIM) * N + WB * N, (k_residual_march<T, TB>), dim3(grid), dim3(kBlock), st, lv,
-                b, (const T *)x, done, ncolx, ncol, ntiles);
+                xp, done, ncolx, ncol, ntiles);
+        TLAUNCH(K_RESIDUAL, W * (4 + DIM) * N + WB * N, (k_residual_march<T, TB>), dim3(grid), dim3(kBlock), st, lr,
+                b, (const T *)xp, done, ncolx, ncol, ntiles);
     } else {
         if ((lv.g.n[0] & 1) == 0)
-            LAUNCH(K_SMOOTH, W * (3 + DIM) * N + WB * N, (k_presmooth_pair<T, TB, DIM>), N / 2, st, lv, b, x, done);
+            LAUNCH(K_SMOOTH, W * (3 + DIM) * N + WB * N, (k_presmooth_pair<T, TB, DIM>), N / 2, st, lv, b, xp, done);
         else
-            LAUNCH(K_SMOOTH, W * (3 + DIM) * N + WB * N, (k_presmooth<T, TB, DIM>), N, st, lv, b, x, done);
-        LAUNCH(K_RESIDUAL, W * (4 + DIM) * N + WB * N, (k_residual<T, TB, DIM>), N, st, lv, b, (const T *)x, done);
+            LAUNCH(K_SMOOTH, W * (3 + DIM) * N + WB * N, (k_presmooth<T, TB, DIM>), N, st, lv, b, xp, done);
+        LAUNCH(K_RESIDUAL, W * (4 + DIM) * N + WB * N, (k_residual<T, TB, DIM>), N, st, lr, b, (const T *)xp, done);
     }
     {
         const Geo &gc = S.lev[l + 1].g;
         const int ntx = (int)((gc.n[0] + kRCX - 1) / kRCX), nty = (int)((gc.n[1] + kRCY - 1) / kRCY);
         const int ntiles = ntx * nty * (int)((gc.n[2] + kRCZ - 1) / kRCZ);
         const int grid = ntiles > 8 ? (ntiles + 7) & ~7 : ntiles;
-        TLAUNCH(K_RESTRICT, W * (N + Nc), (k_restrict3_lds<T>), dim3(grid), dim3(kBlock), st, lv.g, gc,
-                (const T *)lv.r, S.lev[l + 1].b, ntx, nty, ntiles, done);
+        TLAUNCH(K_RESTRICT, W * (N + Nc), (k_restrict3_lds<T>), dim3(grid), dim3(kBlock), st, lv.g, gc, (const T *)x,
+                S.lev[l + 1].b, ntx, nty, ntiles, done);
     }
 }
 
@@ -1702,21 +2030,8 @@ static void vcycle_up(Slot<T> &S, int l, const TB *b, T *x, const int *done, hip
                 ntiles, done);
         return;
     }
-    if (DIM == 3) {
-        // one thread per coarse cell (fine x extent is even on every level above the coarsest)
-        LAUNCH(K_PROLONG, W * (2 * N + Nc), (k_prolong_add3<T>), Nc, st, lv.g, S.lev[l + 1].g,
-               (const T *)S.lev[l + 1].x, x, done);
-        if (lv.g.N >= S.march_cells) {
-            int ncolx, ncol, ntiles;
-            const int grid = march_sweep_grid(lv.g, ncolx, ncol, ntiles);
-            for (int color = 1; color >= 0; --color)
-                TLAUNCH(K_SMOOTH, W * (3.5 + DIM) * N + WB * N, (k_gs_color_march<T, TB>), dim3(grid), dim3(kBlock),
-                        st, lv, b, x, color, done, ncolx, ncol, ntiles);
-        } else {
-            LAUNCH(K_SMOOTH, W * (3.5 + DIM) * N + WB * N, (k_gs_color<T, TB, DIM>), N, st, lv, b, x, 1, done);
-            gs_red_last<T, TB, DIM, TR>(lv, b, x, done, st, rz);
-        }
-    }
+    if constexpr (DIM == 3)
+        sweep3<true, T, TB, TR>(lv, b, (const T *)lv.r, S.lev[l + 1].g, (const T *)S.lev[l + 1].x, x, done, st, rz);
 }
 
 // The levels [S.lsb, nlev) in one workgroup; b0 / x0: right-hand side and
@@ -1759,14 +2074,7 @@ static void vcycle_d(Slot<T> &S, const TB *b0, T *x0, const int *done, hipStream
         // half would repeat the forward one), then back up; at lt = 0 the
         // preconditioner is that sweep alone
         auto sgs = [&](Level<T> &L, const auto *b, T *x, const RzFuse<TR> *rzl) {
-            using TL = std::remove_cv_t<std::remove_pointer_t<decltype(b)>>;
-            const double WL = sizeof(TL) - W;
-            const int N = (int)L.g.N;
-            if ((L.g.n[0] & 1) == 0)
-                LAUNCH(K_SMOOTH, W * (3 + DIM) * N + WL * N, (k_presmooth_pair<T, TL, DIM>), N / 2, st, L, b, x, done);
-            else
-                LAUNCH(K_SMOOTH, W * (3 + DIM) * N + WL * N, (k_presmooth<T, TL, DIM>), N, st, L, b, x, done);
-            gs_red_last<T, TL, DIM, TR>(L, b, x, done, st, rzl);
+            sweep3<false>(L, b, (const T *)nullptr, L.g, (const T *)nullptr, x, done, st, rzl);
         };
         if (lt == 0) {
             sgs(S.lev[0], b0, x0, rz);
@@ -1910,13 +2218,26 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
         LAUNCH(K_PCG_INIT, (W + WP) * N, (k_round_vec<T, TP>), N, st, N, (const T *)v.r, v.rp);
     // preconditioner, then the r.z partials (in 3D with the slot operator
     // they ride on the preconditioner's last pass where that can take them)
+    int nrz = nb;   // partials of r.z, sum z, sum r
     auto precond_rz = [&]() {
-        bool taken = false;
-        const RzFuse<T> rzf{(const T *)v.r, (const Scal *)sc, red.rz0, red.rz1, red.rz2, singular, &taken};
+        int taken = 0;
+        const RzFuse<T> rzf{(const T *)v.r, red.rz0, red.rz1, red.rz2, &taken};
         precond_d<TP, TP, DIM, T>(SP, kind, rpre, v.z, v.w, done, st, DIM == 3 && kind == OP_SLOT ? &rzf : nullptr);
-        if (!taken)
-            LAUNCHR(K_PCG_DOT, (W + WP) * N, (k_pcg_rz<T, TP>), N, st, N, (const T *)v.r, (const TP *)v.z,
-                    (const Scal *)sc, red.rz0, red.rz1, red.rz2, singular);
+        nrz = taken ? taken : nb;
+        if (taken) return;
+        if constexpr (DIM == 3) {
+            int ntx, ncol, zc, ntiles;
+            const int grid = sweep3_grid(g, ntx, ncol, zc, ntiles);
+            if (kind == OP_SLOT && SP.lsb > 0 && ntiles <= kRedBlocks) {   // (level 0 above the small levels: even extents)
+                TLAUNCH(K_PCG_DOT, (W + WP) * N, (k_pcg_rz3<T, TP>), dim3(grid), dim3(SweepShape::nR * kWave), st, g,
+                        (const T *)v.r, (const TP *)v.z, (const Scal *)sc, red.rz0, red.rz1, red.rz2, ntx, ncol, zc,
+                        ntiles);
+                nrz = ntiles;
+                return;
+            }
+        }
+        LAUNCHR(K_PCG_DOT, (W + WP) * N, (k_pcg_rz<T, TP>), N, st, N, (const T *)v.r, (const TP *)v.z,
+                (const Scal *)sc, red.rz0, red.rz1, red.rz2, singular);
     };
     // 2D with tiled level 0: the update and the r.z partials ride on the
     // level-0 tile passes (one partial per tile), and the residual store
@@ -1930,7 +2251,7 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
     // preconditioner's last pass as well
     const bool one = DIM == 2 && kind == OP_SLOT && SP.lsb > 0 && v.az && ntiles0 <= kCgTiles;
     const bool fuse = !one && DIM == 2 && SP.lsb > 0 && ntiles0 <= kRedBlocks;
-    const int nrz = fuse ? ntiles0 : nb;
+    if (fuse) nrz = ntiles0;
     L0Cg<T> cg{0, 0, 1, (const T *)v.r, (const T *)v.q, nullptr, x, sc, (const double *)red.part0, nb,
                red.part1, red.rz0, red.rz1, red.rz2};
     if (one) {

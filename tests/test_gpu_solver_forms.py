@@ -43,10 +43,12 @@ def manufactured(n, per, ratio, seed):
     return g, rho, x, rhs
 
 
-def solve_error(n, per, ratio=0.1, precision=0, seed=3):
+def solve_error(n, per, ratio=0.1, precision=0, seed=3, tile_cells=None):
     P = _lib()
     g, rho, x, rhs = manufactured(n, per, ratio, seed)
     h = P.create_grid(n, g.h, ["periodic" if q else "wall" for q in per], precision=precision)
+    if tile_cells is not None:   # largest 3D level of the tile passes
+        h.set_option(P.CHNS_OPT_TILE_CYCLE_CELLS, tile_cells)
     p = dev(np.zeros(g.shape))
     out = h.solve_pressure(dev(rho), dev(rhs), p, rtol=1e-13, max_iter=300)
     assert out["rc"] == 0, out
@@ -96,3 +98,15 @@ def test_one_reduction_forms(n, per, precision):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_small_level_cycle_forms(n, per, precision):
     assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
+
+
+# post-smoothing of a 3D level in one pass: ragged tiles in x and y, chunks of 4,
+# 8, 16 and (past 1024 blocks of 16 planes) 32 planes, a single column of tiles
+# in x, walls on each axis
+@pytest.mark.parametrize("n,per", [((36, 20, 40), (True, False, True)), ((40, 24, 96), (False, True, False)),
+                                   ((24, 32, 64), (True, True, True)), ((72, 56, 48), (False, False, False)),
+                                   ((80, 144, 80), (True, True, False)), ((160, 80, 80), (False, True, True)),
+                                   ((512, 256, 64), (True, False, True))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_post_sweep_forms(n, per, precision):
+    assert solve_error(n, per, ratio=0.01, precision=precision, tile_cells=0) <= 1e-9
