@@ -122,11 +122,9 @@ def recorded_traffic(workload, kernel_class):
 # Kernel classes of the library's per-kernel timing, by kernel name (the
 # template arguments after the name are matched by the workload filters).
 KERNEL_CLASSES = {
-    "smooth": ("k_presmooth_pair", "k_presmooth", "k_presmooth_march", "k_sweep3"),
-    "residual": ("k_residual", "k_residual_march"),
-    "restrict": ("k_restrict3_lds", "k_restrict3_pair", "k_restrict"),
+    "smooth": ("k_sweep3",),
     "coarse_solve": ("k_vcycle_lds", "k_vcycle_block"),
-    "mg_down": ("k_down_tile2", "k_down_tile2_cg", "k_cg_down_tile2", "k_down3_tile"),
+    "mg_down": ("k_down_tile2", "k_down_tile2_cg", "k_cg_down_tile2", "k_down3", "k_down3_tile"),
     "mg_up": ("k_up_tile2", "k_up_tile2_cg", "k_cg_up_tile2", "k_up3_tile"),
     "pcg_apply": ("k_pcg_apply3_march", "k_pcg_apply_slot", "k_pcg_ch_lap", "k_pcg_ch_apply"),
     "pcg_update": ("k_pcg_update", "k_pcg_fin_rr"),

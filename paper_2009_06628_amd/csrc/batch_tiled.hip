@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(kTileThreadsBatch) k_t_down2(const BatchProb<T
     if (!tile_of(tiles, ntiles, t)) return;
     const BatchProb<TP> &P = probs[t.prob];
     const Slot<TP> &S = tslot(P, s);
-    down_tile2<TP, kTileThreadsBatch>(S.lev[l], S.lev[l + 1].g, RhsStored<TB>{level_b<TP, TB>(P, S, l, bsel)},
+    down_tile2<TP, kTileThreadsBatch, true>(S.lev[l], S.lev[l + 1].g, RhsStored<TB>{level_b<TP, TB>(P, S, l, bsel)},
                                       S.lev[l].r, S.lev[l + 1].b, t.c0, t.c1, P.sc->done);
 }
 

@@ -20,10 +20,8 @@
 //   * 2D levels above kSBCells cells: two tile kernels per level, one for
 //     the way down (pre-smoothing, residual, restriction) and one for the
 //     way up (prolongation, black sweep, red sweep), on LDS tiles with halos;
-//   * 3D levels above kSBCells cells: zero-guess pre-smoothing, residual and
-//     restriction as one grid-wide kernel each, prolongation, black and red
-//     sweep in one kernel that marches along z (k_sweep3); levels of few cells
-//     in two tile kernels as in 2D;
+//   * 3D levels above kSBCells cells: two kernels per level as well, columns
+//     that march along z (k_down3, k_sweep3), on levels of few cells LDS tiles;
 //   * all smaller levels: ONE single-workgroup kernel that holds their
 //     coefficients in registers and x in LDS.
 // Reductions are deterministic and fence-free: per-block partials from a
@@ -49,113 +47,11 @@ static int sb_cells() { return kSBCells; }
 #define GRID_LOOP(N) \
     for (int c = xcd_block() * (int)blockDim.x + (int)threadIdx.x; c < (int)(N); c += (int)(gridDim.x * blockDim.x))
 
-template <typename T, typename TB, int DIM>
-__global__ void __launch_bounds__(kBlock) k_presmooth(Level<T> L, const TB *__restrict__ b, T *__restrict__ x,
-                                                      const int *__restrict__ done) {
-    if (*done) return;
-    GRID_LOOP(L.g.N) presmooth_cell<T, TB, DIM>(L, b, x, c);
-}
-
-// The same pass with one thread per x-adjacent pair of cells (even x
-// extent): each lane updates one red and one black cell, so a wave whose
-// lanes share a row runs each colour's branch once instead of both with
-// half of its lanes masked off.
-template <typename T, typename TB, int DIM>
-__global__ void __launch_bounds__(kBlock) k_presmooth_pair(Level<T> L, const TB *__restrict__ b, T *__restrict__ x,
-                                                           const int *__restrict__ done) {
-    if (*done) return;
-    GRID_LOOP(L.g.N / 2) {
-        presmooth_cell<T, TB, DIM>(L, b, x, 2 * c);
-        presmooth_cell<T, TB, DIM>(L, b, x, 2 * c + 1);
-    }
-}
-
-template <typename T, typename TB, int DIM>
-__global__ void __launch_bounds__(kBlock) k_residual(Level<T> L, const TB *__restrict__ b, const T *__restrict__ x,
-                                                     const int *__restrict__ done) {
-    if (*done) return;
-    GRID_LOOP(L.g.N) residual_cell<T, TB, DIM>(L, b, x, c);
-}
-
 // Two consecutive values along x (the pair starts at an even index).
 template <typename T>
 struct Pair2 {
     T v[2];
 };
-
-// 3D restriction through LDS: a workgroup takes a tile of kRCX x kRCY x kRCZ
-// coarse cells and stages the fine cells 2I-1 .. 2I+2 of all of them once
-// (wrapped on periodic axes; clamped at walls, where restrict_cell gives
-// those taps weight 0 and reads the same clamped cell); each thread then
-// sums the 64 taps of its coarse cell out of LDS with the weights and the
-// summation order of restrict_cell.  The per-thread form read every fine
-// value eight times from the caches, 64 loads per coarse cell.
-constexpr int kRCX = 16, kRCY = 4, kRCZ = 4;   // coarse tile (kRCX * kRCY * kRCZ = kBlock)
-constexpr int kRFX = 2 * kRCX + 2, kRFY = 2 * kRCY + 2, kRFZ = 2 * kRCZ + 2;
-static_assert(kRCX * kRCY * kRCZ == kBlock, "one coarse cell per thread");
-
-// Fine index of staged position g (>= -1): one wrap on a periodic axis (the
-// taps of coarse cells inside the grid reach -1 .. n at most), clamped to the
-// grid otherwise and for positions past a partial tile's last coarse cell.
-__device__ inline int res_fine_index(int g, int n, int per) {
-    if (per) g = g < 0 ? g + n : (g >= n ? g - n : g);
-    return g < 0 ? 0 : (g >= n ? n - 1 : g);
-}
-
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_restrict3_lds(Geo gf, Geo gc, const T *__restrict__ rf,
-                                                          T *__restrict__ bc, int ntx, int nty, int ntiles,
-                                                          const int *__restrict__ done) {
-    using R = T;
-    const int tile = xcd_block();
-    if (tile >= ntiles || *done) return;
-    __shared__ T sf[kRFZ][kRFY][kRFX];
-    const int tz = tile / (ntx * nty), trem = tile - tz * ntx * nty, ty = trem / ntx, tx = trem - ty * ntx;
-    const int X0 = tx * kRCX, Y0 = ty * kRCY, Z0 = tz * kRCZ;
-    const int nfx = (int)gf.n[0], nfy = (int)gf.n[1], nfz = (int)gf.n[2];
-    // every staging load of a thread is issued before its first LDS store
-    constexpr int kStage = kRFX * kRFY * kRFZ, kPer = (kStage + kBlock - 1) / kBlock;
-    T v[kPer];
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int e = (int)threadIdx.x + r * kBlock;
-        if (e < kStage) {
-            const int z = e / (kRFX * kRFY), r2 = e - z * (kRFX * kRFY), y = r2 / kRFX, x = r2 - y * kRFX;
-            const int gx = res_fine_index(2 * X0 - 1 + x, nfx, gc.per[0]);
-            const int gy = res_fine_index(2 * Y0 - 1 + y, nfy, gc.per[1]);
-            const int gz = res_fine_index(2 * Z0 - 1 + z, nfz, gc.per[2]);
-            v[r] = rf[(gz * nfy + gy) * nfx + gx];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int e = (int)threadIdx.x + r * kBlock;
-        if (e < kStage) (&sf[0][0][0])[e] = v[r];
-    }
-    __syncthreads();
-    const int lx = (int)threadIdx.x % kRCX, ly = ((int)threadIdx.x / kRCX) % kRCY, lz = (int)threadIdx.x / (kRCX * kRCY);
-    const int I[3] = {X0 + lx, Y0 + ly, Z0 + lz};
-    if (I[0] >= gc.n[0] || I[1] >= gc.n[1] || I[2] >= gc.n[2]) return;
-    int f[4];
-    R wx[4], wy[4], wz[4];
-    res_axis<R>(I[0], gc.n[0], nfx, gc.per[0], f, wx);
-    res_axis<R>(I[1], gc.n[1], nfy, gc.per[1], f, wy);
-    res_axis<R>(I[2], gc.n[2], nfz, gc.per[2], f, wz);
-    R acc = 0.0;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const R wza = wz[a];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const T *row = &sf[2 * lz + a][2 * ly + q][2 * lx];
-            R s = 0.0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s = fmar(wx[e], (R)row[e], s);
-            acc = fmar(wy[q] * wza, s, acc);
-        }
-    }
-    bc[(I[2] * (int)gc.n[1] + I[1]) * (int)gc.n[0] + I[0]] = (T)acc;
-}
 
 // ---------------------------------------------------------------------------
 // 2D tile kernels of the grid levels (bodies in tile2d.h); tiles along x
@@ -617,163 +513,6 @@ __global__ void __launch_bounds__(kBlock) k_pcg_apply3_march(Level<T> L, const T
 }
 
 // ---------------------------------------------------------------------------
-// 3D smoother and residual sweeps marching along z (levels of at least
-// Slot::march_cells cells, by default those whose arrays exceed the Infinity
-// Cache): block b
-// owns the kMX x kMY columns of tile b mod ncol over kSweepPlanes planes of z
-// chunk b / ncol.  The value a stencil reads at the neighbours (x, or b / diag
-// for the zero-guess pre-smoothing) is formed once per plane with a one-cell
-// x / y halo into a ring of three LDS planes, so the z neighbours come from
-// LDS instead of another pass over memory (a grid-stride sweep capped at
-// 4096 workgroups spreads four z planes over the eight XCDs per round, and
-// the z neighbours of a cell then sit in another XCD's L2).  Per-cell
-// arithmetic and order as the grid-stride bodies (a missing neighbour enters
-// as the cell itself with weight 0).
-// ---------------------------------------------------------------------------
-constexpr int kSweepPlanes = 16;
-
-// Ring of three planes (with halo) of a value v(e), 0 outside the domain.
-template <typename T>
-struct SweepRing {
-    T pl[3][kMH * kMW];
-};
-
-struct MarchTile {
-    int x0, y0, z0, z1, gx, gy, li;
-    bool own;
-};
-
-// Tile of logical block lb (XCD-contiguous numbering: the columns of a z
-// chunk, whose halos overlap, run on the same XCD).
-__device__ inline MarchTile march_tile(const Geo &g, int ncolx, int ncol, int lb) {
-    MarchTile t;
-    const int col = lb % ncol;
-    t.z0 = (lb / ncol) * kSweepPlanes;
-    t.z1 = t.z0 + kSweepPlanes < (int)g.n[2] ? t.z0 + kSweepPlanes : (int)g.n[2];
-    t.x0 = (col % ncolx) * kMX;
-    t.y0 = (col / ncolx) * kMY;
-    const int tx = (int)threadIdx.x % kMX, ty = (int)threadIdx.x / kMX;
-    t.gx = t.x0 + tx;
-    t.gy = t.y0 + ty;
-    t.li = (ty + 1) * kMW + tx + 1;
-    t.own = t.gx < g.n[0] && t.gy < g.n[1];
-    return t;
-}
-
-// fill plane slot P with v at plane zz of the tile and its halo
-template <typename T, typename V>
-__device__ inline void march_form(const Geo &g, const MarchTile &t, int zz, T *P, V v) {
-    auto wrapc = [](int q, int n, int per, int &w) {
-        if (q >= 0 && q < n) {
-            w = q;
-            return true;
-        }
-        w = q < 0 ? q + n : q - n;
-        return per != 0 && w >= 0 && w < n;
-    };
-    int gz;
-    const bool vz = wrapc(zz, (int)g.n[2], g.per[2], gz);
-    for (int i = (int)threadIdx.x; i < kMH * kMW; i += kBlock) {
-        const int ly = i / kMW, lx = i - ly * kMW;
-        int gx, gy;
-        const bool vx = wrapc(t.x0 - 1 + lx, (int)g.n[0], g.per[0], gx);
-        const bool vy = wrapc(t.y0 - 1 + ly, (int)g.n[1], g.per[1], gy);
-        P[i] = (vx && vy && vz) ? v(gx + (int)g.n[0] * (gy + (int)g.n[1] * gz)) : (T)0;
-    }
-}
-
-// March over the tile's planes: cell(c, ia, xc, nbv) for every owned cell,
-// with the ring values of the cell and its six neighbours.
-template <typename T, typename V, typename Cell>
-__device__ inline void march_sweep(const Geo &g, int ncolx, int ncol, int ntiles, SweepRing<T> &R, V v, Cell cell) {
-    const int lb = xcd_block();
-    if (lb >= ntiles) return;   // the whole block (grid rounded up to whole XCD groups)
-    const MarchTile t = march_tile(g, ncolx, ncol, lb);
-    march_form(g, t, t.z0 - 1, R.pl[(t.z0 + 2) % 3], v);
-    march_form(g, t, t.z0, R.pl[t.z0 % 3], v);
-    for (int zz = t.z0; zz < t.z1; ++zz) {
-        march_form(g, t, zz + 1, R.pl[(zz + 1) % 3], v);
-        __syncthreads();
-        const T *Pm = R.pl[(zz + 2) % 3], *P0 = R.pl[zz % 3], *Pp = R.pl[(zz + 1) % 3];
-        if (t.own) {
-            const int c = t.gx + (int)g.n[0] * (t.gy + (int)g.n[1] * zz);
-            const int ia[3] = {t.gx, t.gy, zz};
-            const T nbv[3][2] = {{P0[t.li - 1], P0[t.li + 1]}, {P0[t.li - kMW], P0[t.li + kMW]}, {Pm[t.li], Pp[t.li]}};
-            cell(c, ia, P0[t.li], nbv);
-        }
-        __syncthreads();   // the next plane overwrites this iteration's lower plane
-    }
-}
-
-// sum_b cs * v_nb with the neighbour values of the ring
-template <typename T>
-__device__ inline T march_offsum(const Level<T> &L, int c, const int ia[3], T vc, const T nbv[3][2]) {
-    using R = T;
-    R acc = 0.0;
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-        const int lo = nb_lo(L.g, c, ia[b], b);
-        const int hi = nb_hi(L.g, c, ia[b], b);
-        const int h = hi >= 0 ? hi : c;
-        const R vl = lo >= 0 ? (R)nbv[b][0] : (R)vc, vh = hi >= 0 ? (R)nbv[b][1] : (R)vc;
-        const R wl = (R)L.cs[b][c], wh = (R)L.cs[b][h];
-        acc = fmar(lo >= 0 ? wl : (R)0, vl, acc);
-        acc = fmar(hi >= 0 ? wh : (R)0, vh, acc);
-    }
-    return acc;
-}
-
-// zero-guess pre-smoothing: red x = b / d, black from those red values
-template <typename T, typename TB>
-__global__ void __launch_bounds__(kBlock) k_presmooth_march(Level<T> L, const TB *__restrict__ b, T *__restrict__ x,
-                                                            const int *__restrict__ done, int ncolx, int ncol,
-                                                            int ntiles) {
-    if (*done) return;
-    using R = T;
-    __shared__ SweepRing<T> ring;
-    auto red = [&](int e) { return (T)((R)b[e] * (R)L.invd[e]); };
-    march_sweep<T>(L.g, ncolx, ncol, ntiles, ring, red, [&](int c, const int ia[3], T vc, const T nbv[3][2]) {
-        if (((ia[0] + ia[1] + ia[2]) & 1) == 0)
-            x[c] = vc;
-        else
-            x[c] = (T)(((R)b[c] + march_offsum<T>(L, c, ia, vc, nbv)) * (R)L.invd[c]);
-    });
-}
-
-// r = b - A x
-template <typename T, typename TB>
-__global__ void __launch_bounds__(kBlock) k_residual_march(Level<T> L, const TB *__restrict__ b,
-                                                           const T *__restrict__ x, const int *__restrict__ done,
-                                                           int ncolx, int ncol, int ntiles) {
-    if (*done) return;
-    using R = T;
-    __shared__ SweepRing<T> ring;
-    march_sweep<T>(L.g, ncolx, ncol, ntiles, ring, [&](int e) { return x[e]; },
-                   [&](int c, const int ia[3], T vc, const T nbv[3][2]) {
-                       R acc = (R)L.s[c] * (R)vc;
-#pragma unroll
-                       for (int a = 0; a < 3; ++a) {
-                           const int lo = nb_lo(L.g, c, ia[a], a);
-                           const int hi = nb_hi(L.g, c, ia[a], a);
-                           const int h = hi >= 0 ? hi : c;
-                           const R xl = lo >= 0 ? (R)nbv[a][0] : (R)vc, xh = hi >= 0 ? (R)nbv[a][1] : (R)vc;
-                           const R wl = (R)L.cs[a][c], wh = (R)L.cs[a][h];
-                           acc = fmar(lo >= 0 ? wl : (R)0, (R)vc - xl, acc);
-                           acc = fmar(hi >= 0 ? wh : (R)0, (R)vc - xh, acc);
-                       }
-                       L.r[c] = (T)((R)b[c] - acc);
-                   });
-}
-
-// tiles and grid (rounded up to whole XCD groups) of a marching sweep
-static inline int march_sweep_grid(const Geo &g, int &ncolx, int &ncol, int &ntiles) {
-    ncolx = (int)((g.n[0] + kMX - 1) / kMX);
-    ncol = ncolx * (int)((g.n[1] + kMY - 1) / kMY);
-    ntiles = ncol * (int)((g.n[2] + kSweepPlanes - 1) / kSweepPlanes);
-    return ntiles > 8 ? (ntiles + 7) & ~7 : ntiles;
-}
-
-// ---------------------------------------------------------------------------
 // 3D V-cycle passes on cubic tiles (levels of at most Slot::tile_cells cells
 // above the single-workgroup part): ONE launch per level on the way down
 // (zero-guess pre-smoothing, residual, restriction) and one on the way up
@@ -783,7 +522,8 @@ static inline int march_sweep_grid(const Geo &g, int &ncolx, int &ncol, int &nti
 // cells) and recomputes into LDS what its cells' stencils reach in the
 // neighbouring tiles:
 //   down: b / d of the red cells on a halo of 3, x on a halo of 2, the
-//         residual on a halo of 1 (the restriction's outer taps);
+//         residual of the red cells on a halo of 1 (the restriction's outer
+//         taps; that of a black cell is 0);
 //   up:   red x + P e on a halo of 2, the black GS values on a halo of 1,
 //         then the red GS values of the owned cells.
 // Each value is formed with the arithmetic and order of the grid-wide
@@ -843,9 +583,8 @@ __device__ inline void tile_split(int q, int &lx, int &ly, int &lz) {
 
 // The loads of one cell's stencil, issued at the start of a tile kernel
 // (each kernel then waits on one round of loads, not one per pass):
-// neighbour existence (nb_lo / nb_hi), b, the diagonal term (1 / d for a
-// sweep, s for the residual) and the coefficients of the faces towards the
-// neighbours.
+// neighbour existence (nb_lo / nb_hi), b and 1 / d (for a sweep) and the
+// coefficients of the faces towards the neighbours.
 template <typename T>
 struct TileSt {
     bool lo[3], hi[3];
@@ -855,8 +594,10 @@ struct TileSt {
 template <typename T, typename TB, bool RES>
 __device__ inline void tile_load(const Level<T> &L, const TB *__restrict__ b, int c, const int ia[3], TileSt<T> &S) {
     using R = T;
-    S.bv = (R)b[c];
-    S.dv = RES ? (R)L.s[c] : (R)L.invd[c];
+    if (!RES) {
+        S.bv = (R)b[c];
+        S.dv = (R)L.invd[c];
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const int lo = nb_lo(L.g, c, ia[a], a);
@@ -869,11 +610,11 @@ __device__ inline void tile_load(const Level<T> &L, const TB *__restrict__ b, in
     }
 }
 
-// GS value (b_c + sum_b cs * v_nb) / d_c from the neighbours' values at
-// stride offsets of position q of an LDS region of edge E (offsum_at's
-// order; a missing neighbour enters as 0 with weight 0)
+// sum_b cs * v_nb from the neighbours' values at stride offsets of position q
+// of an LDS region of edge E (offsum_at's order; a missing neighbour enters
+// as 0 with weight 0): the residual of a red cell after the black sweep
 template <typename T, int E>
-__device__ inline T tile_gs(const TileSt<T> &S, const T *v, int q) {
+__device__ inline T tile_offsum(const TileSt<T> &S, const T *v, int q) {
     using R = T;
     constexpr int st[3] = {1, E, E * E};
     R acc = 0.0;
@@ -883,23 +624,12 @@ __device__ inline T tile_gs(const TileSt<T> &S, const T *v, int q) {
         acc = fmar(S.lo[a] ? S.wl[a] : (R)0, vl, acc);
         acc = fmar(S.hi[a] ? S.wh[a] : (R)0, vh, acc);
     }
-    return (T)((S.bv + acc) * S.dv);
+    return acc;
 }
-
-// residual b - A x at position q (apply_at's order)
+// GS value (b_c + sum_b cs * v_nb) / d_c
 template <typename T, int E>
-__device__ inline T tile_res(const TileSt<T> &S, const T *v, int q) {
-    using R = T;
-    constexpr int st[3] = {1, E, E * E};
-    const R xc = (R)v[q];
-    R acc = S.dv * xc;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const R xl = S.lo[a] ? (R)v[q - st[a]] : xc, xh = S.hi[a] ? (R)v[q + st[a]] : xc;
-        acc = fmar(S.lo[a] ? S.wl[a] : (R)0, xc - xl, acc);
-        acc = fmar(S.hi[a] ? S.wh[a] : (R)0, xc - xh, acc);
-    }
-    return (T)(S.bv - acc);
+__device__ inline T tile_gs(const TileSt<T> &S, const T *v, int q) {
+    return (T)((S.bv + tile_offsum<T, E>(S, v, q)) * S.dv);
 }
 
 // P e at fine cell fi: the eight coarse taps loaded up front, then
@@ -953,18 +683,18 @@ __global__ void __launch_bounds__(kT3Threads) k_down3_tile(Level<T> L, Geo gc, c
     const int tile = xcd_block();
     if (tile >= ntiles || *done) return;
     constexpr int E3 = kTF + 6, E2 = kTF + 4, E1 = kTF + 2;
-    constexpr int N3 = E3 * E3 * E3 / 2, N2 = E2 * E2 * E2 / 2, N1 = E1 * E1 * E1;
+    constexpr int N3 = E3 * E3 * E3 / 2, N2 = E2 * E2 * E2 / 2, N1 = E1 * E1 * E1 / 2;
     constexpr int K3 = (N3 + kT3Threads - 1) / kT3Threads;
-    static_assert(N2 <= kT3Threads && N1 <= kT3Threads, "one x pair and one residual cell per thread");
+    static_assert(N2 <= kT3Threads && N1 <= kT3Threads, "one x pair and one red residual per thread");
     __shared__ T sd[E3 * E3 * E3];   // red b / d, halo 3
     __shared__ T sx[E2 * E2 * E2];   // pre-smoothed x, halo 2
-    __shared__ T sr[E1 * E1 * E1];   // residual, halo 1
+    __shared__ T sr[E1 * E1 * E1];   // residual of the red cells, halo 1
     const Geo &g = L.g;
     const int tz = tile / (ntx * nty), trem = tile - tz * ntx * nty, ty = trem / ntx, tx = trem - ty * ntx;
     const int f0[3] = {tx * kTF, ty * kTF, tz * kTF};
     const int tid = (int)threadIdx.x;
     // loads: red b and 1 / d (halo 3), the black member of an x-pair (halo 2),
-    // a residual cell (halo 1)
+    // a red residual (halo 1)
     R rb[K3], rd[K3];
     int rq[K3];
     bool rok[K3];
@@ -985,7 +715,7 @@ __global__ void __launch_bounds__(kT3Threads) k_down3_tile(Level<T> L, Geo gc, c
     tile_load<T, TB, false>(L, b, tile_cell<2>(g, f0, x2, y2, z2, ia2, ok2), ia2, S2);
     int x1, y1, z1, ia1[3];
     bool ok1;
-    tile_split<E1>(tid < N1 ? tid : 0, x1, y1, z1);
+    tile_pair<E1, 1>(tid < N1 ? tid : 0, 0, x1, y1, z1);
     TileSt<T> S1;
     tile_load<T, TB, true>(L, b, tile_cell<1>(g, f0, x1, y1, z1, ia1, ok1), ia1, S1);
 #pragma unroll
@@ -1002,10 +732,10 @@ __global__ void __launch_bounds__(kT3Threads) k_down3_tile(Level<T> L, Geo gc, c
         sx[q + d] = sd[q3 + d];
     }
     __syncthreads();
-    // r = b - A x
+    // red residuals
     if (tid < N1) {
-        const T v = tile_res<T, E2>(S1, sx, (x1 + 1) + E2 * ((y1 + 1) + E2 * (z1 + 1)));
-        sr[tid] = ok1 ? v : (T)0;
+        const T v = tile_offsum<T, E2>(S1, sx, (x1 + 1) + E2 * ((y1 + 1) + E2 * (z1 + 1)));
+        sr[x1 + E1 * (y1 + E1 * z1)] = ok1 ? v : (T)0;
     }
     // the owned cells' pre-smoothed x (read back on the way up)
     if (tid < kTF * kTF * kTF) {
@@ -1016,7 +746,7 @@ __global__ void __launch_bounds__(kT3Threads) k_down3_tile(Level<T> L, Geo gc, c
             L.r[gx + g.n[0] * (gy + g.n[1] * gz)] = sx[(lx + 2) + E2 * ((ly + 2) + E2 * (lz + 2))];
     }
     __syncthreads();
-    // restriction (restrict_cell's weights and order) of the tile's coarse cells
+    // restriction (restrict_cell's weights and order, the red taps) of the tile's coarse cells
     if (tid < kTC * kTC * kTC) {
         int cx, cy, cz;
         tile_split<kTC>(tid, cx, cy, cz);
@@ -1036,7 +766,7 @@ __global__ void __launch_bounds__(kT3Threads) k_down3_tile(Level<T> L, Geo gc, c
                     const T *row = &sr[2 * cx + E1 * ((2 * cy + q) + E1 * (2 * cz + a))];
                     R s = 0.0;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) s = fmar(wx[e], (R)row[e], s);
+                    for (int e = (1 + q + a) & 1; e < 4; e += 2) s = fmar(wx[e], (R)row[e], s);   // (tap 2 I - 1 + e, ..)
                     acc = fmar(wy[q] * wza, s, acc);
                 }
             }
@@ -1134,7 +864,7 @@ __global__ void __launch_bounds__(kT3Threads) k_up3_tile(Level<T> L, Geo gc, con
 // (96^3 16.8, 80^3 14.3); 512^3: 438 ms per solve with it, 423 with 8.
 // ---------------------------------------------------------------------------
 constexpr int kUX = 32, kUY = 8, kUM = kUX / 2 + 2;   // owned cells; pairs per row with one more on each side
-constexpr int kUPlanes = 16, kUBlocks = 256;
+constexpr int kUPlanes = 16, kUBlocks = 256;   // planes of a chunk; CUs
 
 // LDS of one plane is written before and read after: the barrier alone, without
 // waiting for the loads in flight
@@ -1513,6 +1243,251 @@ __global__ void __launch_bounds__(SweepShape::nR * kWave) k_pcg_rz3(Geo g, const
         }
     }
     sweep_partials(arz, az, ar, (int)threadIdx.x, ws, p0 + tile, p1 + tile, p2 + tile);
+}
+
+// ---------------------------------------------------------------------------
+// 3D way down of a level in one pass: zero-guess pre-smoothing (red x = b / d,
+// black from those), the residual, its restriction.  After the black sweep the
+// residual of a black cell is 0 and that of a red cell is the sum of its
+// black neighbours' x over the face coefficients (d x = b cancels), so only
+// red residuals are formed, s is not read, and the restriction takes the 32
+// red of its 64 taps.
+// Columns of kUX x kDY cells march along z as in k_sweep3, with three roles:
+// red values b / d (halo of 3 cells), black values and, two planes behind, the
+// red residuals (halos of 2 and 1), and one wave with a coarse cell per lane,
+// which adds a plane of residuals per step to the two coarse planes it
+// belongs to.  The lanes of a wave of the second role have rows of one parity,
+// so which cell of a pair is red is known at compile time and both cells'
+// coefficients come from one load per pair (a load of every second cell
+// touches as many cache lines).
+// b, 1 / d and three coefficients are read and x written once: 48 B per cell in
+// FP64 where pre-smoothing, residual and restriction moved 121.  Measured
+// against these three: 128^3 FP64 43.7 us -> 24.7, FP32 29.8 -> 18.3; 96^3 FP64
+// 34.3 -> 16.8; 512^3 3.37 ms -> 2.0.  What bounds it is, at 512^3, memory (the
+// least bytes take 1.35 ms), and below the cache lines a CU can look up (halos
+// of 3, 2 and 1 cells make it load 1.7 times the owned cells) and the steps by
+// which the roles trail.  8 rows per column instead of 16: 96^3 level and 128^3
+// 10 % slower, 512^3 solve 377 ms against 350.
+// ---------------------------------------------------------------------------
+constexpr int kDY = 16;
+struct DownShape {
+    static constexpr int DM = kUX / 2 + 4, D = (kDY + 6) * DM;   // pairs of the red values: per row, per plane
+    static constexpr int rows = kDY + 4, X = rows * kUM;         // black values and residuals
+    static constexpr int half = rows / 2 * kUM, wHalf = (half + kWave - 1) / kWave;   // lanes, waves of one row parity
+    static constexpr int wX = (D + kWave - 1) / kWave, wC = wX + 2 * wHalf;
+    static constexpr int wN = kUX / 2 * kDY / 2 / kWave;   // a coarse cell per lane
+    static constexpr int threads = (wC + wN) * kWave;
+};
+
+template <typename T, typename TB>
+__global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const TB *__restrict__ b, Geo gc,
+                                                              T *__restrict__ xp, T *__restrict__ bc, int ntx,
+                                                              int ncol, int zc, int ntiles,
+                                                              const int *__restrict__ done) {
+    using Sh = DownShape;
+    const int tile = xcd_block();
+    if (tile >= ntiles || *done) return;
+    static_assert(sizeof(T) == sizeof(TB), "offsets in bytes of both");
+    __shared__ T D[4][Sh::D], X[2][Sh::X], R[2][Sh::X];
+    const Geo &g = L.g;
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const long long nxy = (long long)nx * ny;
+    const int col = tile % ncol, z0 = (tile / ncol) * zc, z1 = z0 + zc < nz ? z0 + zc : nz, n = z1 - z0;
+    const int x0 = (col % ntx) * kUX, y0 = (col / ntx) * kDY;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = (int)threadIdx.x & (kWave - 1);
+    const int total = n + 11;   // every role ends its group of four within these steps
+    if (wave < Sh::wX) {
+        // red b / d of plane z0 - 3 + s, into D[s & 3]
+        const int u = (int)threadIdx.x;
+        const bool on = u < Sh::D;
+        const int ly = on ? u / Sh::DM : 0, m = (on ? u : 0) - ly * Sh::DM;
+        int gx, gy;
+        const bool ok = wrap_axis(x0 - 4 + 2 * m, nx, g.per[0], gx) & wrap_axis(y0 - 3 + ly, ny, g.per[1], gy);
+        gx &= ~1;
+        unsigned off[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) off[p] = (unsigned)(gx + ((ly + p) & 1) + nx * gy) * sizeof(T);   // (y0 - 3 + ly + z0 - 3 + s even: red at 0)
+        struct Ops {
+            T a, d;
+        };
+        sweep_role<0, Ops>(
+            n + 5, total,
+            [&](int s, auto P, Ops &o) {
+                int gz;
+                (void)wrap_axis(z0 - 3 + s, nz, g.per[2], gz);
+                const long long z = gz * nxy;
+                o.a = (T)plane_at(b + z, off[decltype(P)::value]);
+                o.d = plane_at(L.invd + z, off[decltype(P)::value]);
+            },
+            [&](int s, auto K, const Ops &o) {
+                int gz;
+                const bool okz = wrap_axis(z0 - 3 + s, nz, g.per[2], gz);
+                const T v = o.a * o.d;
+                if (on) D[decltype(K)::value][u] = okz && ok ? v : (T)0;
+            });
+        return;
+    }
+    if (wave < Sh::wC) {
+        // black values of plane z0 - 5 + s into X[s & 1] (the red ones around
+        // it are in D[s - 3 .. s - 1]); red residuals of the plane below into
+        // R[s & 1] (its black values are in X[s - 1]; the black cells above and
+        // below a red one are in this lane's pair)
+        const int w = wave - Sh::wX, rp = w / Sh::wHalf, u = (w - rp * Sh::wHalf) * kWave + lane;
+        const bool on = u < Sh::half;
+        const int row = on ? u / kUM : 0, m = (on ? u : 0) - row * kUM, ly = 2 * row + rp;
+        int gx, gy;
+        const bool ok = wrap_axis(x0 - 2 + 2 * m, nx, g.per[0], gx) & wrap_axis(y0 - 2 + ly, ny, g.per[1], gy);
+        gx &= ~1;
+        const int c = gx + nx * gy, hx = nb_hi(g, c + 1, gx + 1, 0), hy = nb_hi(g, c, gy, 1);
+        const unsigned off = (unsigned)c * sizeof(T), offn = (unsigned)(hx >= 0 ? hx : c + 1) * sizeof(T),
+                       offh = (unsigned)(hy >= 0 ? hy : c) * sizeof(T);
+        const bool own = on && m >= 1 && m <= kUX / 2 && ly >= 2 && ly < kDY + 2 && x0 - 2 + 2 * m < nx && y0 - 2 + ly < ny;
+        const int q = (ly + 1) * Sh::DM + m + 1, qx = ly * kUM + m;
+        // (the outermost pairs' and rows' outer neighbours are not used)
+        const int xl = m > 0 ? qx - 1 : qx, xh = m < kUM - 1 ? qx + 1 : qx;
+        const int yl = ly > 0 ? qx - kUM : qx, yh = ly < Sh::rows - 1 ? qx + kUM : qx;
+        struct Ops {
+            T b, d, n;
+            Pair2<T> c0, c1, h1, c2;   // c2: of the plane above
+        };
+        auto pair_at = [](const T *plane, unsigned o) { return *(const Pair2<T> *)((const char *)plane + o); };
+        auto run = [&](auto RP) {
+            constexpr int rpar = decltype(RP)::value;
+            // of the plane below: the red cell's coefficients but the upper one,
+            // the black value; the black value below that
+            T keep[5], v1 = 0.0, v2 = 0.0;
+#pragma unroll
+            for (int i = 0; i < 5; ++i) keep[i] = (T)0;
+            int gf;
+            (void)wrap_axis(z0 - 2, nz, g.per[2], gf);
+            Pair2<T> c2 = pair_at(L.cs[2] + gf * nxy, off);
+            sweep_role<3, Ops>(
+                n + 6, total,
+                [&](int s, auto P, Ops &o) {
+                    constexpr int blk = (rpar + decltype(P)::value) & 1;   // the black cell of the pair
+                    int gz, gh;
+                    (void)wrap_axis(z0 - 5 + s, nz, g.per[2], gz);
+                    (void)wrap_axis(z0 - 4 + s, nz, g.per[2], gh);
+                    const long long z = gz * nxy;
+                    o.b = (T)plane_at(b + z, off + blk * (unsigned)sizeof(T));
+                    o.d = plane_at(L.invd + z, off + blk * (unsigned)sizeof(T));
+                    o.c0 = pair_at(L.cs[0] + z, off);
+                    o.n = plane_at(L.cs[0] + z, offn);
+                    o.c1 = pair_at(L.cs[1] + z, off);
+                    o.h1 = pair_at(L.cs[1] + z, offh);
+                    o.c2 = pair_at(L.cs[2] + gh * nxy, off);
+                },
+                [&](int s, auto K, const Ops &o) {
+                    constexpr int k = decltype(K)::value, blk = (rpar + k) & 1, red = 1 - blk;
+                    const int p = z0 - 5 + s;
+                    int gz;
+                    const bool okz = wrap_axis(p, nz, g.per[2], gz);
+                    T val;
+                    {
+                        const T *d0 = D[(k + 2) & 3], *dm = D[(k + 1) & 3], *dp = D[(k + 3) & 3];
+                        const T dq = d0[q];
+                        const T v[6] = {blk ? dq : d0[q - 1], blk ? d0[q + 1] : dq, d0[q - Sh::DM], d0[q + Sh::DM], dm[q], dp[q]};
+                        const T wt[6] = {o.c0.v[blk], blk ? o.n : o.c0.v[1], o.c1.v[blk], o.h1.v[blk], c2.v[blk], o.c2.v[blk]};
+                        T acc = 0.0;
+#pragma unroll
+                        for (int i = 0; i < 6; ++i) acc = fmar(wt[i], v[i], acc);
+                        val = (o.b + acc) * o.d;
+                        val = okz && ok ? val : (T)0;
+                        if (on) X[k & 1][qx] = val;
+                        if (own && p >= z0 && p < z1) {
+                            Pair2<T> t;
+                            t.v[blk] = val;
+                            t.v[red] = dq;
+                            *(Pair2<T> *)((char *)(xp + p * nxy) + off) = t;
+                        }
+                    }
+                    {
+                        // (the plane below has its red and black cells the other way round)
+                        const T *a = X[(k + 1) & 1];
+                        const T v[6] = {blk ? v1 : a[xl], blk ? a[xh] : v1, a[yl], a[yh], v2, val};
+                        T acc = 0.0;
+#pragma unroll
+                        for (int i = 0; i < 5; ++i) acc = fmar(keep[i], v[i], acc);
+                        acc = fmar(c2.v[blk], v[5], acc);
+                        if (on) R[k & 1][qx] = acc;
+                    }
+                    keep[0] = o.c0.v[red];
+                    keep[1] = red ? o.n : o.c0.v[1];
+                    keep[2] = o.c1.v[red];
+                    keep[3] = o.h1.v[red];
+                    keep[4] = c2.v[red];
+                    c2 = o.c2;
+                    v2 = v1;
+                    v1 = val;
+                });
+        };
+        if (rp)
+            run(std::integral_constant<int, 1>());
+        else
+            run(std::integral_constant<int, 0>());
+        return;
+    }
+    // coarse cell (I, J) of this lane: plane z0 - 7 + s of the residual (in
+    // R[s - 1]) is tap 2 of coarse plane Z and tap 0 of Z + 1 (an odd plane), or
+    // tap 3, the last, of Z and tap 1 of Z + 1
+    const int u = (int)threadIdx.x - Sh::wC * kWave, i = u % (kUX / 2), j = u / (kUX / 2), I = x0 / 2 + i, J = y0 / 2 + j;
+    const bool own = I < gc.n[0] && J < gc.n[1];
+    int f[4];
+    T wx[4], wy[4], wo[4], wn[4];
+    res_axis<T>(own ? I : 0, gc.n[0], nx, gc.per[0], f, wx);
+    res_axis<T>(own ? J : 0, gc.n[1], ny, gc.per[1], f, wy);
+    res_axis<T>(z0 / 2, gc.n[2], nz, gc.per[2], f, wn);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) wo[a] = (T)0;
+    T ao = 0.0, an = 0.0;   // sums of Z and Z + 1
+    struct None {};
+    sweep_role<6, None>(
+        n + 7, total, [](int, auto, None &) {},
+        [&](int s, auto K, const None &) {
+            constexpr int k = decltype(K)::value, odd = (k + 1) & 1;
+            const T *r = R[(k + 1) & 1];
+            T sum[4];
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                // row 2 J - 1 + y: its red cells are at even or (par) odd x (z0 and y0 are even)
+                const int par = (y + 1 + odd) & 1;
+                const T *rr = r + (2 * j + y + 1) * kUM + i + (par ? 0 : 1);
+                sum[y] = fmar(wx[par ? 2 : 3], rr[1], fmar(wx[par ? 0 : 1], rr[0], (T)0));
+            }
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                ao = fmar(wy[y] * wo[odd ? 2 : 3], sum[y], ao);
+                an = fmar(wy[y] * wn[odd ? 0 : 1], sum[y], an);
+            }
+            if (!odd) {
+                const int Z = (z0 - 7 + s) / 2 - 1;
+                if (own && s >= 9 && s <= n + 7) bc[(Z * gc.n[1] + J) * gc.n[0] + I] = ao;
+                ao = an;
+                an = (T)0;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) wo[a] = wn[a];
+                const int Zn = Z + 2 < gc.n[2] ? Z + 2 : gc.n[2] - 1;
+                res_axis<T>(Zn, gc.n[2], nz, gc.per[2], f, wn);
+            }
+        });
+}
+
+// Columns, planes per block (a multiple of 4) and blocks of the way down.  A CU
+// holds one block (15 waves of 118 registers in FP64), so the pass takes
+// ceil(blocks / CUs) rounds of a chunk's planes and the 11 steps by which
+// the roles trail: the planes that make this least (FP64 96^3 level, 8 planes,
+// 216 blocks: 17 us, 4 planes, 432 blocks: 22; 128^3, 16 planes, 256 blocks: 23,
+// 32 planes: 33).
+static int down3_grid(const Geo &g, int &ntx, int &ncol, int &zc, int &ntiles) {
+    ntx = (g.n[0] + kUX - 1) / kUX;
+    ncol = ntx * ((g.n[1] + kDY - 1) / kDY);
+    auto blocks = [&](int z) { return ncol * ((g.n[2] + z - 1) / z); };
+    auto steps = [&](int z) { return (long long)((blocks(z) + kUBlocks - 1) / kUBlocks) * (z + 11); };
+    zc = 4;
+    for (int z = 8; z / 2 < g.n[2]; z *= 2)
+        if (steps(z) < steps(zc)) zc = z;
+    ntiles = blocks(zc);
+    return ntiles > 8 ? (ntiles + 7) & ~7 : ntiles;
 }
 
 // Columns, planes per block (a multiple of 4) and blocks of that pass: 16
@@ -1955,41 +1930,20 @@ static void vcycle_down(Slot<T> &S, int l, const TB *b, T *x, const int *done, h
                 lv.r, S.lev[l + 1].b, ntx, ntiles, done);
         return;
     }
-    const double WB = sizeof(TB) - W;   // extra bytes of a wider right-hand side
     if (DIM == 3 && tile3_level(S, l)) {
-        // b, invd, s, cs in; pre-smoothed x (to r) and the coarse b out
+        // b, invd, cs in; pre-smoothed x (to r) and the coarse b out
         int ntx, nty, ntiles;
         const int grid = tile3_grid(S.lev[l + 1].g, ntx, nty, ntiles);
-        TLAUNCH(K_MG_DOWN, (sizeof(TB) + W * (3 + DIM)) * N + W * Nc, (k_down3_tile<T, TB>), dim3(grid),
+        TLAUNCH(K_MG_DOWN, (sizeof(TB) + W * (2 + DIM)) * N + W * Nc, (k_down3_tile<T, TB>), dim3(grid),
                 dim3(kT3Threads), st, lv, S.lev[l + 1].g, b, S.lev[l + 1].b, ntx, nty, ntiles, done);
         return;
     }
-    // the pre-smoothed x goes to the level's r array and the residual to x:
-    // the way up reads the one while it writes the other
-    T *const xp = lv.r;
-    Level<T> lr = lv;
-    lr.r = x;
-    if (DIM == 3 && lv.g.N >= S.march_cells) {
-        int ncolx, ncol, ntiles;
-        const int grid = march_sweep_grid(lv.g, ncolx, ncol, ntiles);
-        TLAUNCH(K_SMOOTH, W * (3 + DIM) * N + WB * N, (k_presmooth_march<T, TB>), dim3(grid), dim3(kBlock), st, lv, b,
-                xp, done, ncolx, ncol, ntiles);
-        TLAUNCH(K_RESIDUAL, W * (4 + DIM) * N + WB * N, (k_residual_march<T, TB>), dim3(grid), dim3(kBlock), st, lr,
-                b, (const T *)xp, done, ncolx, ncol, ntiles);
-    } else {
-        if ((lv.g.n[0] & 1) == 0)
-            LAUNCH(K_SMOOTH, W * (3 + DIM) * N + WB * N, (k_presmooth_pair<T, TB, DIM>), N / 2, st, lv, b, xp, done);
-        else
-            LAUNCH(K_SMOOTH, W * (3 + DIM) * N + WB * N, (k_presmooth<T, TB, DIM>), N, st, lv, b, xp, done);
-        LAUNCH(K_RESIDUAL, W * (4 + DIM) * N + WB * N, (k_residual<T, TB, DIM>), N, st, lr, b, (const T *)xp, done);
-    }
-    {
-        const Geo &gc = S.lev[l + 1].g;
-        const int ntx = (int)((gc.n[0] + kRCX - 1) / kRCX), nty = (int)((gc.n[1] + kRCY - 1) / kRCY);
-        const int ntiles = ntx * nty * (int)((gc.n[2] + kRCZ - 1) / kRCZ);
-        const int grid = ntiles > 8 ? (ntiles + 7) & ~7 : ntiles;
-        TLAUNCH(K_RESTRICT, W * (N + Nc), (k_restrict3_lds<T>), dim3(grid), dim3(kBlock), st, lv.g, gc, (const T *)x,
-                S.lev[l + 1].b, ntx, nty, ntiles, done);
+    if constexpr (DIM == 3) {
+        // b, invd, cs in; pre-smoothed x (to r: the way up reads it there while it writes x) and the coarse b out
+        int ntx, ncol, zc, ntiles;
+        const int grid = down3_grid(lv.g, ntx, ncol, zc, ntiles);
+        TLAUNCH(K_MG_DOWN, (sizeof(TB) + W * (2 + DIM)) * N + W * Nc, (k_down3<T, TB>), dim3(grid),
+                dim3(DownShape::threads), st, lv, b, S.lev[l + 1].g, lv.r, S.lev[l + 1].b, ntx, ncol, zc, ntiles, done);
     }
 }
 
@@ -2020,7 +1974,6 @@ static void vcycle_up(Slot<T> &S, int l, const TB *b, T *x, const int *done, hip
                 (const T *)S.lev[l + 1].x, b, (const T *)lv.r, x, ntx, ntiles, done);
         return;
     }
-    const double WB = sizeof(TB) - W;
     if (DIM == 3 && tile3_level(S, l)) {
         // pre-smoothed x (from r), b, invd, cs, coarse x in; x out
         int ntx, nty, ntiles;

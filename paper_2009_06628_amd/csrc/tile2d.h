@@ -136,27 +136,37 @@ struct RzDots {
 };
 
 // Way down: zero-guess pre-smoothing (red x = b / d, black GS from those),
-// residual r = b - A x, restriction of r to the coarse right-hand side bc.
+// residual, restriction to the coarse right-hand side bc.  After the black
+// sweep the residual of a black cell is 0 and that of a red cell is the sum of
+// its black neighbours' x over the face coefficients (d x = b cancels): only
+// the red ones are formed, s is not read and the restriction takes the red
+// half of its taps (with s and every residual: 256 x 512 bubble step 1233 us,
+// 1185 without; 768^2 drop step 2.12 -> 2.05 ms).
+// FULL (the batched form): b - A x in every cell instead, whose rounding in the
+// FP32 hierarchy that form's iterates carry: its refinement rounds end far
+// above FP64 rounding, and without the rounding its velocities move by 1e-8.
 // Writes the smoothed x of the tile to xs (the level's residual array, which
 // no longer holds a residual: the way up reads x from there while it writes
 // the level's x) and bc on the tile's coarse cells.
 constexpr int kDownH = 3, kDownWX = kTFX + 2 * kDownH, kDownWY = kTFY + 2 * kDownH, kDownNL = kDownWX * kDownWY;
-template <typename T>
+template <typename T, bool FULL>
 struct DownTile {
-    T sB[kDownNL], sI[kDownNL], sS[kDownNL], sC0[kDownNL], sC1[kDownNL], sX[kDownNL], sR[kDownNL];
+    T sB[kDownNL], sI[kDownNL], sC0[kDownNL], sC1[kDownNL];
+    T sX[kDownNL];   // x of the black cells, residual of the red ones (FULL: x)
+    T sS[FULL ? kDownNL : 1], sR[FULL ? kDownNL : 1];
 };
 
 // The passes of the way down on a staged tile (sB .. sC1 filled, barrier done).
-template <typename T, int NT>
-__device__ inline void down_passes2(DownTile<T> &t, const Level<T> &L, const Geo &gc, T *__restrict__ xs,
+template <typename T, int NT, bool FULL>
+__device__ inline void down_passes2(DownTile<T, FULL> &t, const Level<T> &L, const Geo &gc, T *__restrict__ xs,
                                     T *__restrict__ bc, int tx, int ty);
 
-template <typename T, int NT, typename BS>
+template <typename T, int NT, bool FULL = false, typename BS>
 __device__ inline void down_tile2(const Level<T> &L, const Geo &gc, const BS &b, T *__restrict__ xs,
                                   T *__restrict__ bc, int tx, int ty, int skip) {
     constexpr int H = kDownH, WX = kDownWX, NL = kDownNL;
     constexpr int KL = (NL + NT - 1) / NT;   // staged cells per thread
-    __shared__ DownTile<T> tile;
+    __shared__ DownTile<T, FULL> tile;
     const int nx = (int)L.g.n[0], ny = (int)L.g.n[1];
     const int px = L.g.per[0], py = L.g.per[1];
     const int gx0 = tx * kTFX - H, gy0 = ty * kTFY - H;
@@ -175,7 +185,7 @@ __device__ inline void down_tile2(const Level<T> &L, const Geo &gc, const BS &b,
         const int g = v ? gx + nx * gy : 0;
         lb[k] = b.template at<T>(g);
         li[k] = L.invd[g];
-        ls[k] = L.s[g];
+        if (FULL) ls[k] = L.s[g];
         l0[k] = L.cs[0][g];
         l1[k] = L.cs[1][g];
         lv[k] = v;
@@ -191,33 +201,31 @@ __device__ inline void down_tile2(const Level<T> &L, const Geo &gc, const BS &b,
         const T fv = lv[k] ? (T)1 : (T)0;
         tile.sB[i] = lb[k] * fv;
         tile.sI[i] = li[k] * fv;
-        tile.sS[i] = ls[k] * fv;
+        if (FULL) tile.sS[i] = ls[k] * fv;
         tile.sC0[i] = l0[k] * (m0[k] ? (T)1 : (T)0);
         tile.sC1[i] = l1[k] * (m1[k] ? (T)1 : (T)0);
     }
     __syncthreads();
-    down_passes2<T, NT>(tile, L, gc, xs, bc, tx, ty);
+    down_passes2<T, NT, FULL>(tile, L, gc, xs, bc, tx, ty);
 }
 
-template <typename T, int NT>
-__device__ inline void down_passes2(DownTile<T> &t, const Level<T> &L, const Geo &gc, T *__restrict__ xs,
+template <typename T, int NT, bool FULL>
+__device__ inline void down_passes2(DownTile<T, FULL> &t, const Level<T> &L, const Geo &gc, T *__restrict__ xs,
                                     T *__restrict__ bc, int tx, int ty) {
     using R = T;
     constexpr int H = kDownH, WX = kDownWX, WY = kDownWY;
-    T *const sB = t.sB, *const sI = t.sI, *const sS = t.sS, *const sC0 = t.sC0, *const sC1 = t.sC1;
-    T *const sX = t.sX, *const sR = t.sR;
+    T *const sB = t.sB, *const sI = t.sI, *const sC0 = t.sC0, *const sC1 = t.sC1, *const sX = t.sX;
+    T *const sR = FULL ? t.sR : t.sX;
     const int nx = (int)L.g.n[0], ny = (int)L.g.n[1];
     const int gx0 = tx * kTFX - H, gy0 = ty * kTFY - H;
-    // x on the tile and 2 halo cells (local [1, WX-1) x [1, WY-1), rows of
-    // even width): the k-th red and the k-th black cell in one thread, so no
-    // wave runs both colours' branches
+    // black x on the tile and 2 halo cells (local [1, WX-1) x [1, WY-1), rows
+    // of even width): the k-th black cell in one thread, so no wave runs both
+    // colours' branches
     const int par = (gx0 + gy0) & 1;
     constexpr int XP = (WX - 2) / 2;   // cells of one colour per row
     for (int k = (int)threadIdx.x; k < XP * (WY - 2); k += NT) {
         const int row = k / XP, m = k - row * XP, ly = 1 + row;
-        const int ir = ly * WX + tile_color_x(m, ly, par, 0);
         const int i = ly * WX + tile_color_x(m, ly, par, 1);
-        sX[ir] = (T)((R)sB[ir] * (R)sI[ir]);
         auto red = [&](int j) { return (R)sB[j] * (R)sI[j]; };
         R acc = 0.0;
         acc += (R)sC0[i] * red(i - 1);
@@ -225,19 +233,35 @@ __device__ inline void down_passes2(DownTile<T> &t, const Level<T> &L, const Geo
         acc += (R)sC1[i] * red(i - WX);
         acc += (R)sC1[i + WX] * red(i + WX);
         sX[i] = (T)(((R)sB[i] + acc) * (R)sI[i]);
+        if (FULL) {
+            const int ir = ly * WX + tile_color_x(m, ly, par, 0);
+            sX[ir] = (T)((R)sB[ir] * (R)sI[ir]);
+        }
     }
     __syncthreads();
-    // residual on the tile and 1 halo cell (local [2, WX-2) x [2, WY-2))
-    constexpr int RW = WX - 4;
-    for (int j = (int)threadIdx.x; j < RW * (WY - 4); j += NT) {
-        const int ry = j / RW, i = (ry + 2) * WX + (j - ry * RW) + 2;
-        const R xc = (R)sX[i];
-        R acc = (R)sS[i] * xc;
-        acc += (R)sC0[i] * (xc - (R)sX[i - 1]);
-        acc += (R)sC0[i + 1] * (xc - (R)sX[i + 1]);
-        acc += (R)sC1[i] * (xc - (R)sX[i - WX]);
-        acc += (R)sC1[i + WX] * (xc - (R)sX[i + WX]);
-        sR[i] = (T)((R)sB[i] - acc);
+    // red residuals on the tile and 1 halo cell (local [2, WX-2) x [2, WY-2))
+    constexpr int RW = WX - 4, RP = RW / 2;
+    if (FULL) {
+        for (int j = (int)threadIdx.x; j < RW * (WY - 4); j += NT) {
+            const int ry = j / RW, i = (ry + 2) * WX + (j - ry * RW) + 2;
+            const R xc = (R)sX[i];
+            R acc = (R)t.sS[i] * xc;
+            acc += (R)sC0[i] * (xc - (R)sX[i - 1]);
+            acc += (R)sC0[i + 1] * (xc - (R)sX[i + 1]);
+            acc += (R)sC1[i] * (xc - (R)sX[i - WX]);
+            acc += (R)sC1[i + WX] * (xc - (R)sX[i + WX]);
+            sR[i] = (T)((R)sB[i] - acc);
+        }
+    } else {
+        for (int k = (int)threadIdx.x; k < RP * (WY - 4); k += NT) {
+            const int row = k / RP, m = k - row * RP, ly = 2 + row;
+            const int i = ly * WX + 2 + 2 * m + ((ly + par) & 1);
+            R acc = (R)sC0[i] * (R)sX[i - 1];
+            acc += (R)sC0[i + 1] * (R)sX[i + 1];
+            acc += (R)sC1[i] * (R)sX[i - WX];
+            acc += (R)sC1[i + WX] * (R)sX[i + WX];
+            sX[i] = (T)acc;
+        }
     }
     __syncthreads();
     // restriction (taps 2I-1 .. 2I+2 per axis; an absent tap has weight 0)
@@ -257,7 +281,7 @@ __device__ inline void down_passes2(DownTile<T> &t, const Level<T> &L, const Geo
             const int row = (2 * cy + H - 1 + q) * WX + 2 * cx + H - 1;
             R s = 0.0;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s += wx[e] * (R)sR[row + e];
+            for (int e = FULL ? 0 : q & 1; e < 4; e += FULL ? 1 : 2) s += wx[e] * (R)sR[row + e];   // (red taps: 2 I - 1 + e of row 2 J - 1 + q)
             v += (wy[q] * (R)1.0) * s;
         }
         bc[I + ncx * J] = (T)v;
@@ -266,7 +290,8 @@ __device__ inline void down_passes2(DownTile<T> &t, const Level<T> &L, const Geo
     for (int j = (int)threadIdx.x; j < kTFX * kTFY; j += NT) {
         const int ly = j / kTFX, lx = j - ly * kTFX;
         const int gx = tx * kTFX + lx, gy = ty * kTFY + ly;
-        if (gx < nx && gy < ny) xs[gx + nx * gy] = sX[(ly + H) * WX + lx + H];
+        const int i = (ly + H) * WX + lx + H;
+        if (gx < nx && gy < ny) xs[gx + nx * gy] = FULL || (gx + gy) & 1 ? sX[i] : (T)((R)sB[i] * (R)sI[i]);
     }
 }
 
@@ -407,7 +432,7 @@ __device__ inline void cg_down_tile2(const Level<T> &L, const Geo &gc, const CgV
     constexpr int NT = kTileThreads, H = kDownH, WX = kDownWX, NL = kDownNL;
     constexpr int KL = (NL + NT - 1) / NT;
     static_assert(kTFX * kTFY == NT, "one owned cell per thread");
-    __shared__ DownTile<T> tile;
+    __shared__ DownTile<T, false> tile;
     __shared__ double ws[4][NT / kWave], wr[NT / kWave];
     const int tid = (int)threadIdx.x;
     const int nx = (int)L.g.n[0], ny = (int)L.g.n[1];
@@ -417,7 +442,7 @@ __device__ inline void cg_down_tile2(const Level<T> &L, const Geo &gc, const CgV
     const int dn = sc->done;
     const double prev_rz = k > 0 ? sc->rzs[(k + 1) & 1] : 0.0, prev_al = k > 0 ? sc->als[(k + 1) & 1] : 0.0;
     TR lr[KL], lw[KL], lo[KL];
-    T li[KL], ls[KL], l0[KL], l1[KL];
+    T li[KL], l0[KL], l1[KL];
     bool lv[KL], m0[KL], m1[KL];
 #pragma unroll
     for (int q = 0; q < KL; ++q) {
@@ -432,7 +457,6 @@ __device__ inline void cg_down_tile2(const Level<T> &L, const Geo &gc, const CgV
         lo[q] = (TR)0;
         if (k > 0) lo[q] = v.s[g];
         li[q] = L.invd[g];
-        ls[q] = L.s[g];
         l0[q] = L.cs[0][g];
         l1[q] = L.cs[1][g];
         lv[q] = in;
@@ -487,7 +511,6 @@ __device__ inline void cg_down_tile2(const Level<T> &L, const Geo &gc, const CgV
         const TR sn = (TR)fma(beta, (double)lo[q], (double)lw[q]);
         tile.sB[i] = (T)residual((double)lr[q], (double)sn) * fv;
         tile.sI[i] = li[q] * fv;
-        tile.sS[i] = ls[q] * fv;
         tile.sC0[i] = l0[q] * (m0[q] ? (T)1 : (T)0);
         tile.sC1[i] = l1[q] * (m1[q] ? (T)1 : (T)0);
     }
@@ -509,7 +532,7 @@ __device__ inline void cg_down_tile2(const Level<T> &L, const Geo &gc, const CgV
         for (int q = 0; q < NT / kWave; ++q) t += wr[q];
         part_rr[tile_id] = t;
     }
-    down_passes2<T, NT>(tile, L, gc, xs, bc, tx, ty);
+    down_passes2<T, NT, false>(tile, L, gc, xs, bc, tx, ty);
 }
 
 // One tile of the way up that ends the preconditioner of a CG iteration:

@@ -100,7 +100,7 @@ def test_small_level_cycle_forms(n, per, precision):
     assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
 
 
-# post-smoothing of a 3D level in one pass: ragged tiles in x and y, chunks of 4,
+# way down and post-smoothing of a 3D level in one pass each: ragged tiles in x and y, chunks of 4,
 # 8, 16 and (past 1024 blocks of 16 planes) 32 planes, a single column of tiles
 # in x, walls on each axis
 @pytest.mark.parametrize("n,per", [((36, 20, 40), (True, False, True)), ((40, 24, 96), (False, True, False)),
