@@ -30,7 +30,6 @@
 // that consumes them.  PCG scalars live on the device; every iteration
 // kernel returns at once when the device "done" flag is set, so the host
 // launches iterations in chunks and checks the flag once per chunk.
-#include <cstdlib>
 #include <type_traits>
 
 #include "mgdev.h"
@@ -775,7 +774,9 @@ __global__ void __launch_bounds__(kT3Threads) k_down3_tile(Level<T> L, Geo gc, c
     }
 }
 
-template <typename T, typename TB>
+// !PRO: the symmetric sweep from zero that ends a truncated cycle (red b / d,
+// black, red) instead of the way up.
+template <typename T, typename TB, bool PRO = true>
 __global__ void __launch_bounds__(kT3Threads) k_up3_tile(Level<T> L, Geo gc, const T *__restrict__ xc,
                                                          const TB *__restrict__ b, const T *__restrict__ xpre,
                                                          T *__restrict__ x, int ntx, int nty, int ntiles,
@@ -798,9 +799,15 @@ __global__ void __launch_bounds__(kT3Threads) k_up3_tile(Level<T> L, Geo gc, con
     bool ok2;
     tile_pair<E2, 2>(tid < N2 ? tid : 0, 0, x2, y2, z2);
     const int c2 = tile_cell<2>(g, f0, x2, y2, z2, ia2, ok2);
-    const R xp = (R)xpre[c2];
+    R rx, rd = (R)0;
     TilePro<T> P;
-    pro_load<T>(gc, xc, ia2, P);
+    if (PRO) {
+        rx = (R)xpre[c2];
+        pro_load<T>(gc, xc, ia2, P);
+    } else {
+        rx = (R)b[c2];
+        rd = (R)L.invd[c2];
+    }
     int x1, y1, z1, ia1[3];
     bool ok1;
     tile_pair<E1, 1>(tid < N1 ? tid : 0, 1, x1, y1, z1);
@@ -816,7 +823,7 @@ __global__ void __launch_bounds__(kT3Threads) k_up3_tile(Level<T> L, Geo gc, con
     TileSt<T> S0;
     tile_load<T, TB, false>(L, b, c0, ia0, S0);
     if (tid < N2) {
-        const T v = (T)(xp + pro_value<T>(P));
+        const T v = (T)(PRO ? rx + pro_value<T>(P) : rx * rd);
         se[x2 + E2 * (y2 + E2 * z2)] = ok2 ? v : (T)0;
     }
     __syncthreads();
@@ -841,30 +848,31 @@ __global__ void __launch_bounds__(kT3Threads) k_up3_tile(Level<T> L, Geo gc, con
 //   !PRO  red start = b / d (the symmetric sweep from zero that ends a
 //         truncated cycle)
 // A block owns kUX x kUY cells of every plane of its z chunk.  Its waves split
-// by role, each two planes behind the one before: the first form the red
-// start values with a halo of two cells, the next the black values with a
-// halo of one, the last the red values of the owned cells, and store the
-// pair.  Values pass through rings of four planes in LDS, stored by x-pair
-// (one red and one black cell; the red one is at x = 2 m + parity), so one
-// barrier per plane is enough, and every role loads the next plane's operands
-// before it works on this one's.  The stored x may not be the one read
-// (neighbouring blocks still read their halos): the way down leaves the
-// pre-smoothed x in the level's r array.
+// by role: the first form the red start values with a halo of two cells, the
+// others, two planes behind, the black values with a halo of one and then the
+// red values of the plane below and store that plane.  Values pass through
+// rings of planes in LDS, stored by x-pair (one red and one black cell; the red
+// one is at x = 2 m + parity), so one barrier per plane is enough, and every
+// role loads operands two planes before it works on them.  The lanes of a wave
+// of the second role have rows of one parity, so which cell of a pair is red
+// is known at compile time and one load per pair serves the black and the red
+// value (a load of every second cell touches as many cache lines); the black
+// cells above and below a red one are in the lane's own pair.
+// The stored x may not be the one read (neighbouring blocks still read their
+// halos): the way down leaves the pre-smoothed x in the level's r array.
 // Per-cell arithmetic and order are those of prolong_at / presmooth_cell and
 // gs_color_cell (a neighbour past a wall enters as 0 with weight 0).
-// What bounds it is memory: x, b, 1 / d and three coefficients are read once
-// (b, 1 / d and coefficients of the halo twice, from the caches) and x is
-// written once, 56 B per cell in FP64, where three passes moved 129.
-// Measured against the three passes (prolongation, black, red), the second on
-// the same inputs: 128^3 FP64 46.6 us -> 24.5, FP32 29.6 -> 16.9; 96^3 FP64
-// 26.5 -> 15.6, FP32 19.1 -> 11.2; 80^3 FP64 19.4 -> 13.1.  128^3 FP64 moves
-// 117 MB, 24.6 us at the rate of a large copy; the smaller levels are bound
-// by the cache lines the stride-2 loads touch and by the halo.  A tile of 16
-// rows reads less halo and is level at 128^3 (23.8) but leaves CUs idle below
-// (96^3 16.8, 80^3 14.3); 512^3: 438 ms per solve with it, 423 with 8.
+// x, b, 1 / d and three coefficients are read once and x is written once, 56 B
+// per cell in FP64, where three passes (prolongation, black, red) moved 129.
+// Measured against these: 128^3 FP64 46.6 us -> 24.9, FP32 29.6 -> 20; 96^3 FP64
+// 26.5 -> 16.0, FP32 19.1 -> 14.6; 80^3 FP64 19.4 -> 14.8; 512^3 4.0 ms -> 1.95.
+// 128^3 FP64 moves 117 MB, 24.6 us at the rate of a large copy; 512^3 fetches
+// 1.6 times its bytes (halos that have left the L2) at 5.9 TB/s; smaller levels
+// are bound by the rounds of steps.  With the black and the red values in roles
+// of their own, each loading its half of every pair: 128^3 FP64 32.2, 96^3 22.1.
 // ---------------------------------------------------------------------------
-constexpr int kUX = 32, kUY = 8, kUM = kUX / 2 + 2;   // owned cells; pairs per row with one more on each side
-constexpr int kUPlanes = 16, kUBlocks = 256;   // planes of a chunk; CUs
+constexpr int kUX = 32, kUY = 16, kUM = kUX / 2 + 2;   // owned cells; pairs per row with one more on each side
+constexpr int kCUs = 256;
 
 // LDS of one plane is written before and read after: the barrier alone, without
 // waiting for the loads in flight
@@ -884,48 +892,40 @@ __device__ inline T plane_at(const T *plane, unsigned off) {
     return *(const T *)((const char *)plane + off);
 }
 
-// The cells of one lane of the black or red role: byte offsets in a plane of
-// the cell and of its upper x and y neighbours (the cell itself where there is
-// none), by parity of the step.
-struct SweepAt {
-    unsigned c[2], hx[2], hy[2];
+template <typename T>
+__device__ inline Pair2<T> pair_at(const T *plane, unsigned off) {
+    return *(const Pair2<T> *)((const char *)plane + off);
+}
+
+// A lane of the role that works on pairs of ROWS rows (halo H in y, one pair in
+// x) of the tile at (x0, y0): waves 0 .. wHalf - 1 hold the even rows, the next
+// wHalf the odd ones.
+template <int ROWS, int H>
+struct PairLane {
+    static constexpr int half = ROWS / 2 * kUM, wHalf = (half + kWave - 1) / kWave, waves = 2 * wHalf;
+    int rp, ly, m;        // row parity, row, pair in the row
+    bool on, own, ok;     // has a pair; of the owned cells; inside the grid
+    unsigned c, n, h;     // cell indices in a plane: the pair, the cell above it in x, the pair above in y
+    template <typename G>
+    __device__ inline PairLane(const G &g, int wave, int lane, int x0, int y0) {
+        rp = wave / wHalf;
+        const int u = (wave - rp * wHalf) * kWave + lane;
+        on = u < half;
+        const int row = on ? u / kUM : 0;
+        m = (on ? u : 0) - row * kUM;
+        ly = 2 * row + rp;
+        const int ex = x0 - 2 + 2 * m, ey = y0 - H + ly;
+        int gx, gy;
+        ok = wrap_axis(ex, g.n[0], g.per[0], gx) & wrap_axis(ey, g.n[1], g.per[1], gy);
+        gx &= ~1;
+        own = on && m >= 1 && m <= kUX / 2 && ly >= H && ly < ROWS - H && ex < g.n[0] && ey < g.n[1];
+        c = (unsigned)(gx + g.n[0] * gy);
+        // (nothing above at a wall: the coefficient multiplies 0 and may be any)
+        const int hx = nb_hi(g, (int)c + 1, gx + 1, 0), hy = nb_hi(g, (int)c, gy, 1);
+        n = hx >= 0 ? (unsigned)hx : c + 1;
+        h = hy >= 0 ? (unsigned)hy : c;
+    }
 };
-template <typename T>
-__device__ inline void sweep_at(const Geo &g, int gx, int gy, int p, SweepAt &A) {
-    const int c = gx + g.n[0] * gy;
-    const int hx = nb_hi(g, c, gx, 0), hy = nb_hi(g, c, gy, 1);
-    A.c[p] = (unsigned)c * sizeof(T);
-    A.hx[p] = (unsigned)(hx >= 0 ? hx : c) * sizeof(T);
-    A.hy[p] = (unsigned)(hy >= 0 ? hy : c) * sizeof(T);
-}
-// Operands of a Gauss-Seidel value: b, 1 / d and the face coefficients x low,
-// x high, .., z high.  The coefficient of a face past a wall may be any: the
-// value it multiplies is 0.
-template <typename T>
-struct SweepOps {
-    T b, invd, w[6];
-};
-template <typename T, typename TB>
-__device__ inline void sweep_load(const Level<T> &L, const TB *b, const SweepAt &A, int p, int gz, SweepOps<T> &o) {
-    static_assert(sizeof(T) == sizeof(TB), "offsets in bytes of both");
-    const int nxy = L.g.n[0] * L.g.n[1];
-    const long long z = (long long)gz * nxy, zh = (long long)(gz + 1 < L.g.n[2] ? gz + 1 : (L.g.per[2] ? 0 : gz)) * nxy;
-    o.b = (T)plane_at(b + z, A.c[p]);
-    o.invd = plane_at(L.invd + z, A.c[p]);
-    o.w[0] = plane_at(L.cs[0] + z, A.c[p]);
-    o.w[1] = plane_at(L.cs[0] + z, A.hx[p]);
-    o.w[2] = plane_at(L.cs[1] + z, A.c[p]);
-    o.w[3] = plane_at(L.cs[1] + z, A.hy[p]);
-    o.w[4] = plane_at(L.cs[2] + z, A.c[p]);
-    o.w[5] = plane_at(L.cs[2] + zh, A.c[p]);
-}
-template <typename T>
-__device__ inline T sweep_gs(const SweepOps<T> &o, const T (&v)[6]) {
-    T acc = 0.0;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) acc = fmar(o.w[i], v[i], acc);
-    return (o.b + acc) * o.invd;
-}
 
 // One role of the pass: body(s, K, o) for the steps from FIRST on, in whole
 // groups of four until `last` is past, a barrier after every one of `total`
@@ -946,6 +946,7 @@ __device__ __forceinline__ void sweep_role(int last, int total, LOAD load, BODY 
     auto step = [&](int s, auto J, O &o) {
         constexpr int k = (FIRST + decltype(J)::value) & 3;
         body(s, std::integral_constant<int, k>(), o);
+        __builtin_amdgcn_sched_barrier(0);   // (loads moved up into the body need a third set of registers)
         load(s + 2, std::integral_constant<int, (k & 1)>(), o);
         lds_barrier();
     };
@@ -959,27 +960,29 @@ __device__ __forceinline__ void sweep_role(int last, int total, LOAD load, BODY 
     for (; s < total; ++s) lds_barrier();
 }
 
-// Pairs per plane of the red start / black / owned values, coarse cells per
-// plane that the red start reads, first wave of the black / red role, threads.
+// Pairs per plane of the red start / black values, coarse cells per plane that
+// the red start reads, waves of the first role, threads.
 struct SweepShape {
-    static constexpr int E = (kUY + 4) * kUM, B = (kUY + 2) * kUM, R = kUX / 2 * kUY;
+    static constexpr int rows = kUY + 2, E = (kUY + 4) * kUM, B = rows * kUM;
     static constexpr int CX = kUX / 2 + 4, CY = kUY / 2 + 4, C = CX * CY;
-    static constexpr int wB = (E + kWave - 1) / kWave, wR = wB + (B + kWave - 1) / kWave, nR = (R + kWave - 1) / kWave;
-    static constexpr int threads = (wR + nR) * kWave;
+    using Lane = PairLane<rows, 1>;
+    static constexpr int wB = (E + kWave - 1) / kWave, nB = Lane::waves;
+    static constexpr int threads = (wB + nB) * kWave;
 };
 
 // r.z, sum z, sum r of a thread's pair, and the block's partials of them (u:
-// thread among those that own cells, whole waves)
+// thread of the second role)
 template <typename TR, typename T>
 __device__ inline void sweep_dots(const Pair2<TR> &r, const Pair2<T> &z, double &arz, double &az, double &ar) {
+#pragma clang fp contract(off)   // z as stored: not fused with the product it comes from
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-        arz += (double)r.v[e] * (double)z.v[e];
+        arz = fmar((double)r.v[e], (double)z.v[e], arz);
         az += (double)z.v[e];
         ar += (double)r.v[e];
     }
 }
-__device__ inline void sweep_partials(double arz, double az, double ar, int u, double (*ws)[SweepShape::nR],
+__device__ inline void sweep_partials(double arz, double az, double ar, int u, double (*ws)[SweepShape::nB],
                                       double *p0, double *p1, double *p2) {
     arz = wave_sum(arz);
     az = wave_sum(az);
@@ -992,7 +995,7 @@ __device__ inline void sweep_partials(double arz, double az, double ar, int u, d
     lds_barrier();
     if (u == 0) {
         arz = az = ar = 0.0;
-        for (int k = 0; k < SweepShape::nR; ++k) {
+        for (int k = 0; k < SweepShape::nB; ++k) {
             arz += ws[0][k];
             az += ws[1][k];
             ar += ws[2][k];
@@ -1013,17 +1016,17 @@ __global__ void __launch_bounds__(SweepShape::threads) k_sweep3(Level<T> L, cons
     using Sh = SweepShape;
     const int tile = xcd_block();
     if (tile >= ntiles || *done) return;
-    __shared__ T E[4][Sh::E], B[4][Sh::B], C[4][PRO ? Sh::C : 1];
-    __shared__ double ws[3][Sh::nR];
+    static_assert(sizeof(T) == sizeof(TB), "offsets in bytes of both");
+    __shared__ T E[4][Sh::E], B[2][Sh::B], C[4][PRO ? Sh::C : 1];
+    __shared__ double ws[3][Sh::nB];
     static_assert(Sh::C <= Sh::wB * kWave, "one coarse cell per lane of the first role");
     const Geo &g = L.g;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
     const int col = tile % ncol, z0 = (tile / ncol) * zc, z1 = z0 + zc < nz ? z0 + zc : nz;
     const int x0 = (col % ntx) * kUX, y0 = (col / ntx) * kUY;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    // the red role is four planes behind the first; every role ends its group
-    // of four within `total` steps
-    const int steps = z1 - z0 + 6, total = steps + 4;
+    const long long nxy = (long long)nx * ny;
+    const int n = z1 - z0, total = n + 8;   // every role ends its group of four within these steps
     if (wave < Sh::wB) {
         // red start of plane z0 - 2 + s, into E[s & 3]
         const int u = (int)threadIdx.x;
@@ -1084,7 +1087,7 @@ __global__ void __launch_bounds__(SweepShape::threads) k_sweep3(Level<T> L, cons
             T a, b;
         };
         sweep_role<0, Ops>(
-            steps - 3, total,
+            n + 3, total,
             [&](int s, auto P, Ops &o) {
                 constexpr int p = decltype(P)::value;
                 int gz;
@@ -1125,93 +1128,111 @@ __global__ void __launch_bounds__(SweepShape::threads) k_sweep3(Level<T> L, cons
         if (DOTS) lds_barrier();
         return;
     }
-    if (wave < Sh::wR) {
-        // black values of plane z0 - 4 + s into B[s & 3]; the red start around
-        // plane z0 - 4 + s is in E[s - 3 .. s - 1]
-        const int u = (int)threadIdx.x - Sh::wB * kWave;
-        const bool on = u < Sh::B;
-        const int ly = on ? u / kUM : 0, m = (on ? u : 0) - ly * kUM;
-        int gy;
-        const bool oky = wrap_axis(y0 - 1 + ly, ny, g.per[1], gy);
-        if (PRO) lds_barrier();
-        const int q = (ly + 1) * kUM + m;   // the pair in a plane of E
-        const int ql = m > 0 ? q - 1 : q, qh = m < kUM - 1 ? q + 1 : q;   // (the outermost pairs' outer cells are not used)
-        bool ok[2];
-        int xl[2], xh[2];
-        SweepAt A;
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int par = (y0 - 1 + ly + z0 + p) & 1;
-            int gx;
-            ok[p] = wrap_axis(x0 - 2 + 2 * m + 1 - par, nx, g.per[0], gx) && oky;
-            sweep_at<T>(g, gx, gy, p, A);
-            xl[p] = par ? ql : q;
-            xh[p] = par ? q : qh;
-        }
-        sweep_role<3, SweepOps<T>>(
-            steps - 2, total,
-            [&](int s, auto P, SweepOps<T> &o) {
-                int gz;
-                (void)wrap_axis(z0 - 4 + s, nz, g.per[2], gz);
-                sweep_load(L, b, A, decltype(P)::value, gz, o);
-            },
-            [&](int s, auto K, const SweepOps<T> &o) {
-                constexpr int k = decltype(K)::value, p = k & 1;
-                int gz;
-                const bool okz = wrap_axis(z0 - 4 + s, nz, g.per[2], gz);
-                const T *e0 = E[(k + 2) & 3], *em = E[(k + 1) & 3], *ep = E[(k + 3) & 3];
-                const T v[6] = {e0[xl[p]], e0[xh[p]], e0[q - kUM], e0[q + kUM], em[q], ep[q]};
-                const T val = sweep_gs(o, v);
-                if (on) B[k][u] = okz && ok[p] ? val : (T)0;
-            });
-        if (DOTS) lds_barrier();
-        return;
-    }
-    // red values of the owned cells of plane z0 - 6 + s, and the stores; the
-    // black values around it are in B[s - 3 .. s - 1]
-    const int u0 = (int)threadIdx.x - Sh::wR * kWave, u = u0 < Sh::R ? u0 : 0;
-    const int ly = u / (kUX / 2), m = u - ly * (kUX / 2);
-    const int gy = y0 + ly, ex = x0 + 2 * m;
-    const bool own = u0 < Sh::R && ex < nx && gy < ny;
-    const int cy = own ? gy : 0, cx = own ? ex : 0;
-    const int q = (ly + 1) * kUM + m + 1;   // the pair in a plane of B
+    // black values of plane z0 - 4 + s into B[s & 1] (the red start around it is
+    // in E[s - 3 .. s - 1]); red values of the plane below, whose black values
+    // are in B[s - 1], and its store
+    const typename Sh::Lane P(g, wave - Sh::wB, (int)threadIdx.x & (kWave - 1), x0, y0);
+    const int q = (P.ly + 1) * kUM + P.m, qb = P.ly * kUM + P.m;
+    // (the outermost pairs' and rows' outer neighbours are not used)
+    const int ql = P.m > 0 ? q - 1 : q, qh = P.m < kUM - 1 ? q + 1 : q;
+    const int xl = P.m > 0 ? qb - 1 : qb, xh = P.m < kUM - 1 ? qb + 1 : qb;
+    const int yl = P.ly > 0 ? qb - kUM : qb, yh = P.ly < Sh::rows - 1 ? qb + kUM : qb;
+    const unsigned off = P.c * (unsigned)sizeof(T), offn = P.n * (unsigned)sizeof(T), offh = P.h * (unsigned)sizeof(T);
+    constexpr bool same = std::is_same<T, TR>::value;   // r is b
     double arz = 0.0, az = 0.0, ar = 0.0;
-    int par[2], xl[2], xh[2];
-    SweepAt A;
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        par[p] = (gy + z0 + p) & 1;
-        sweep_at<T>(g, cx + (own ? par[p] : 0), cy, p, A);
-        xl[p] = par[p] ? q : q - 1;
-        xh[p] = par[p] ? q + 1 : q;
-    }
     if (PRO) lds_barrier();
-    const unsigned pair = (unsigned)(cx + nx * cy);
     struct Ops {
-        SweepOps<T> g;
-        Pair2<TR> r;
+        Pair2<T> b, d, c0, c1, h1, c2;   // c2: of the plane above
+        T n;
+        Pair2<TR> r;                     // of the plane below
     };
-    sweep_role<6, Ops>(
-        steps - 1, total,
-        [&](int s, auto P, Ops &o) {
-            const int zz = z0 - 6 + s < nz ? z0 - 6 + s : nz - 1;
-            sweep_load(L, b, A, decltype(P)::value, zz, o.g);
-            if (DOTS) o.r = *(const Pair2<TR> *)((const char *)(r + (long long)zz * nx * ny) + pair * sizeof(TR));
-        },
-        [&](int s, auto K, const Ops &o) {
-            constexpr int k = decltype(K)::value, p = k & 1;
-            const T *b0 = B[(k + 2) & 3], *bm = B[(k + 1) & 3], *bp = B[(k + 3) & 3];
-            const T v[6] = {b0[xl[p]], b0[xh[p]], b0[q - kUM], b0[q + kUM], bm[q], bp[q]};
-            const T red = sweep_gs(o.g, v), mine = par[p] ? v[0] : v[1];
-            if (own && s < steps) {
-                Pair2<T> t;
-                t.v[0] = par[p] ? mine : red;
-                t.v[1] = par[p] ? red : mine;
-                *(Pair2<T> *)((char *)(x + (long long)(z0 - 6 + s) * nx * ny) + pair * sizeof(T)) = t;
-                if (DOTS) sweep_dots(o.r, t, arz, az, ar);
-            }
-        });
-    if (DOTS) sweep_partials(arz, az, ar, u0, ws, p0 + tile, p1 + tile, p2 + tile);
+    auto run = [&](auto RP) {
+        constexpr int rpar = decltype(RP)::value;
+        asm volatile("; rows of parity %0" ::"n"(rpar));   // keeps the two parities' loads apart
+        // of the plane below: b, the red cell's 1 / d and coefficients but the
+        // upper one, the black value; the black value below that
+        Pair2<T> kb;
+        T kd = 0.0, kw[5], v1 = 0.0, v2 = 0.0;
+        kb.v[0] = kb.v[1] = (T)0;
+#pragma unroll
+        for (int i = 0; i < 5; ++i) kw[i] = (T)0;
+        int gf;
+        (void)wrap_axis(z0 - 1, nz, g.per[2], gf);
+        Pair2<T> c2 = pair_at(L.cs[2] + gf * nxy, off);
+        sweep_role<3, Ops>(
+            n + 4, total,
+            [&](int s, auto, Ops &o) {
+                int gz, gh;
+                (void)wrap_axis(z0 - 4 + s, nz, g.per[2], gz);
+                (void)wrap_axis(z0 - 3 + s, nz, g.per[2], gh);
+                const long long z = gz * nxy;
+                o.b = pair_at((const T *)(const void *)b + z, off);
+                o.d = pair_at(L.invd + z, off);
+                o.c0 = pair_at(L.cs[0] + z, off);
+                o.n = plane_at(L.cs[0] + z, offn);
+                o.c1 = pair_at(L.cs[1] + z, off);
+                o.h1 = pair_at(L.cs[1] + z, offh);
+                o.c2 = pair_at(L.cs[2] + gh * nxy, off);
+                if (DOTS && !same) {
+                    const int zr = z0 - 5 + s < z0 ? z0 : (z0 - 5 + s < nz ? z0 - 5 + s : nz - 1);
+                    o.r = pair_at(r + zr * nxy, P.c * (unsigned)sizeof(TR));
+                }
+            },
+            [&](int s, auto K, const Ops &o) {
+                constexpr int k = decltype(K)::value, blk = (rpar + k) & 1, red = 1 - blk;
+                const int p = z0 - 4 + s;
+                int gz;
+                const bool okz = wrap_axis(p, nz, g.per[2], gz);
+                T val;
+                {
+                    const T *e0 = E[(k + 2) & 3], *em = E[(k + 1) & 3], *ep = E[(k + 3) & 3];
+                    const T v[6] = {blk ? e0[q] : e0[ql], blk ? e0[qh] : e0[q], e0[q - kUM], e0[q + kUM], em[q], ep[q]};
+                    const T w[6] = {o.c0.v[blk], blk ? o.n : o.c0.v[1], o.c1.v[blk], o.h1.v[blk], c2.v[blk], o.c2.v[blk]};
+                    T acc = 0.0;
+#pragma unroll
+                    for (int i = 0; i < 6; ++i) acc = fmar(w[i], v[i], acc);
+                    val = (o.b.v[blk] + acc) * o.d.v[blk];
+                    val = okz && P.ok ? val : (T)0;
+                    if (P.on) B[k & 1][qb] = val;
+                }
+                {
+                    // (the plane below has its red and black cells the other way round)
+                    const T *a = B[(k + 1) & 1];
+                    const T v[6] = {blk ? v1 : a[xl], blk ? a[xh] : v1, a[yl], a[yh], v2, val};
+                    T acc = 0.0;
+#pragma unroll
+                    for (int i = 0; i < 5; ++i) acc = fmar(kw[i], v[i], acc);
+                    acc = fmar(c2.v[blk], v[5], acc);
+                    Pair2<T> t;
+                    t.v[blk] = (kb.v[blk] + acc) * kd;
+                    t.v[red] = v1;
+                    if (P.own && p > z0 && p <= z1) {
+                        *(Pair2<T> *)((char *)(x + (p - 1) * nxy) + off) = t;
+                        if (DOTS) {
+                            if constexpr (same)
+                                sweep_dots(kb, t, arz, az, ar);
+                            else
+                                sweep_dots(o.r, t, arz, az, ar);
+                        }
+                    }
+                }
+                kb = o.b;
+                kd = o.d.v[red];
+                kw[0] = o.c0.v[red];
+                kw[1] = red ? o.n : o.c0.v[1];
+                kw[2] = o.c1.v[red];
+                kw[3] = o.h1.v[red];
+                kw[4] = c2.v[red];
+                c2 = o.c2;
+                v2 = v1;
+                v1 = val;
+            });
+    };
+    if (P.rp)
+        run(std::integral_constant<int, 1>());
+    else
+        run(std::integral_constant<int, 0>());
+    if (DOTS) sweep_partials(arz, az, ar, (int)threadIdx.x - Sh::wB * kWave, ws, p0 + tile, p1 + tile, p2 + tile);
 }
 
 // The same partials in the same order as a pass of its own, for a level 0
@@ -1219,7 +1240,7 @@ __global__ void __launch_bounds__(SweepShape::threads) k_sweep3(Level<T> L, cons
 // pair of cells of its column, marching along z.  Both forms of the cycle then
 // give the same bits.
 template <typename T, typename TZ>
-__global__ void __launch_bounds__(SweepShape::nR * kWave) k_pcg_rz3(Geo g, const T *__restrict__ r,
+__global__ void __launch_bounds__(SweepShape::nB * kWave) k_pcg_rz3(Geo g, const T *__restrict__ r,
                                                                     const TZ *__restrict__ z,
                                                                     const Scal *__restrict__ sc,
                                                                     double *__restrict__ p0, double *__restrict__ p1,
@@ -1227,18 +1248,17 @@ __global__ void __launch_bounds__(SweepShape::nR * kWave) k_pcg_rz3(Geo g, const
                                                                     int ntiles) {
     const int tile = xcd_block();
     if (tile >= ntiles || sc->done) return;
-    __shared__ double ws[3][SweepShape::nR];
-    const int nx = g.n[0], nxy = nx * g.n[1];
+    __shared__ double ws[3][SweepShape::nB];
+    const int nxy = g.n[0] * g.n[1];
     const int col = tile % ncol, z0 = (tile / ncol) * zc, z1 = z0 + zc < g.n[2] ? z0 + zc : g.n[2];
-    const int ly = (int)threadIdx.x / (kUX / 2), m = (int)threadIdx.x - ly * (kUX / 2);
-    const int ex = (col % ntx) * kUX + 2 * m, gy = (col / ntx) * kUY + ly;
+    const SweepShape::Lane P(g, __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), (int)threadIdx.x & (kWave - 1),
+                             (col % ntx) * kUX, (col / ntx) * kUY);
     double arz = 0.0, az = 0.0, ar = 0.0;
-    if (ex < nx && gy < g.n[1]) {
-        const int c = ex + nx * gy;
+    if (P.own) {
 #pragma unroll 4
         for (int kz = z0; kz < z1; ++kz) {
-            const Pair2<T> rc = *(const Pair2<T> *)(r + c + (long long)kz * nxy);
-            const Pair2<TZ> zv = *(const Pair2<TZ> *)(z + c + (long long)kz * nxy);
+            const Pair2<T> rc = *(const Pair2<T> *)(r + P.c + (long long)kz * nxy);
+            const Pair2<TZ> zv = *(const Pair2<TZ> *)(z + P.c + (long long)kz * nxy);
             sweep_dots(rc, zv, arz, az, ar);
         }
     }
@@ -1252,7 +1272,7 @@ __global__ void __launch_bounds__(SweepShape::nR * kWave) k_pcg_rz3(Geo g, const
 // black neighbours' x over the face coefficients (d x = b cancels), so only
 // red residuals are formed, s is not read, and the restriction takes the 32
 // red of its 64 taps.
-// Columns of kUX x kDY cells march along z as in k_sweep3, with three roles:
+// Columns of kUX x kUY cells march along z as in k_sweep3, with three roles:
 // red values b / d (halo of 3 cells), black values and, two planes behind, the
 // red residuals (halos of 2 and 1), and one wave with a coarse cell per lane,
 // which adds a plane of residuals per step to the two coarse planes it
@@ -1269,13 +1289,12 @@ __global__ void __launch_bounds__(SweepShape::nR * kWave) k_pcg_rz3(Geo g, const
 // which the roles trail.  8 rows per column instead of 16: 96^3 level and 128^3
 // 10 % slower, 512^3 solve 377 ms against 350.
 // ---------------------------------------------------------------------------
-constexpr int kDY = 16;
 struct DownShape {
-    static constexpr int DM = kUX / 2 + 4, D = (kDY + 6) * DM;   // pairs of the red values: per row, per plane
-    static constexpr int rows = kDY + 4, X = rows * kUM;         // black values and residuals
-    static constexpr int half = rows / 2 * kUM, wHalf = (half + kWave - 1) / kWave;   // lanes, waves of one row parity
-    static constexpr int wX = (D + kWave - 1) / kWave, wC = wX + 2 * wHalf;
-    static constexpr int wN = kUX / 2 * kDY / 2 / kWave;   // a coarse cell per lane
+    static constexpr int DM = kUX / 2 + 4, D = (kUY + 6) * DM;   // pairs of the red values: per row, per plane
+    static constexpr int rows = kUY + 4, X = rows * kUM;         // black values and residuals
+    using Lane = PairLane<rows, 2>;
+    static constexpr int wX = (D + kWave - 1) / kWave, wC = wX + Lane::waves;
+    static constexpr int wN = kUX / 2 * kUY / 2 / kWave;   // a coarse cell per lane
     static constexpr int threads = (wC + wN) * kWave;
 };
 
@@ -1293,7 +1312,7 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
     const long long nxy = (long long)nx * ny;
     const int col = tile % ncol, z0 = (tile / ncol) * zc, z1 = z0 + zc < nz ? z0 + zc : nz, n = z1 - z0;
-    const int x0 = (col % ntx) * kUX, y0 = (col / ntx) * kDY;
+    const int x0 = (col % ntx) * kUX, y0 = (col / ntx) * kUY;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = (int)threadIdx.x & (kWave - 1);
     const int total = n + 11;   // every role ends its group of four within these steps
     if (wave < Sh::wX) {
@@ -1332,16 +1351,10 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
         // it are in D[s - 3 .. s - 1]); red residuals of the plane below into
         // R[s & 1] (its black values are in X[s - 1]; the black cells above and
         // below a red one are in this lane's pair)
-        const int w = wave - Sh::wX, rp = w / Sh::wHalf, u = (w - rp * Sh::wHalf) * kWave + lane;
-        const bool on = u < Sh::half;
-        const int row = on ? u / kUM : 0, m = (on ? u : 0) - row * kUM, ly = 2 * row + rp;
-        int gx, gy;
-        const bool ok = wrap_axis(x0 - 2 + 2 * m, nx, g.per[0], gx) & wrap_axis(y0 - 2 + ly, ny, g.per[1], gy);
-        gx &= ~1;
-        const int c = gx + nx * gy, hx = nb_hi(g, c + 1, gx + 1, 0), hy = nb_hi(g, c, gy, 1);
-        const unsigned off = (unsigned)c * sizeof(T), offn = (unsigned)(hx >= 0 ? hx : c + 1) * sizeof(T),
-                       offh = (unsigned)(hy >= 0 ? hy : c) * sizeof(T);
-        const bool own = on && m >= 1 && m <= kUX / 2 && ly >= 2 && ly < kDY + 2 && x0 - 2 + 2 * m < nx && y0 - 2 + ly < ny;
+        const typename Sh::Lane P(g, wave - Sh::wX, lane, x0, y0);
+        const bool on = P.on, ok = P.ok, own = P.own;
+        const int ly = P.ly, m = P.m;
+        const unsigned off = P.c * (unsigned)sizeof(T), offn = P.n * (unsigned)sizeof(T), offh = P.h * (unsigned)sizeof(T);
         const int q = (ly + 1) * Sh::DM + m + 1, qx = ly * kUM + m;
         // (the outermost pairs' and rows' outer neighbours are not used)
         const int xl = m > 0 ? qx - 1 : qx, xh = m < kUM - 1 ? qx + 1 : qx;
@@ -1350,9 +1363,9 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
             T b, d, n;
             Pair2<T> c0, c1, h1, c2;   // c2: of the plane above
         };
-        auto pair_at = [](const T *plane, unsigned o) { return *(const Pair2<T> *)((const char *)plane + o); };
         auto run = [&](auto RP) {
             constexpr int rpar = decltype(RP)::value;
+        asm volatile("; rows of parity %0" ::"n"(rpar));   // keeps the two parities' loads apart
             // of the plane below: the red cell's coefficients but the upper one,
             // the black value; the black value below that
             T keep[5], v1 = 0.0, v2 = 0.0;
@@ -1421,7 +1434,7 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
                     v1 = val;
                 });
         };
-        if (rp)
+        if (P.rp)
             run(std::integral_constant<int, 1>());
         else
             run(std::integral_constant<int, 0>());
@@ -1472,37 +1485,27 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
         });
 }
 
-// Columns, planes per block (a multiple of 4) and blocks of the way down.  A CU
-// holds one block (15 waves of 118 registers in FP64), so the pass takes
-// ceil(blocks / CUs) rounds of a chunk's planes and the 11 steps by which
-// the roles trail: the planes that make this least (FP64 96^3 level, 8 planes,
-// 216 blocks: 17 us, 4 planes, 432 blocks: 22; 128^3, 16 planes, 256 blocks: 23,
-// 32 planes: 33).
-static int down3_grid(const Geo &g, int &ntx, int &ncol, int &zc, int &ntiles) {
+// Columns, planes per block (a multiple of 4) and blocks of these passes.  A CU
+// holds one block (12 or 15 waves of up to 128 registers), so a pass takes
+// ceil(blocks / CUs) rounds of a chunk's planes and the steps by which its
+// roles trail: the planes that make this least (k_down3 FP64 on 96^3, 8 planes,
+// 216 blocks: 17 us, 4 planes, 432 blocks: 22; on 128^3, 16 planes, 256 blocks:
+// 24, 32 planes: 33).  max_blocks: more planes where the blocks outnumber the
+// partials of r.z.
+constexpr int kSweepTrail = 8, kDownTrail = 11;
+static int march3_grid(const Geo &g, int trail, int max_blocks, int &ntx, int &ncol, int &zc, int &ntiles) {
     ntx = (g.n[0] + kUX - 1) / kUX;
-    ncol = ntx * ((g.n[1] + kDY - 1) / kDY);
+    ncol = ntx * ((g.n[1] + kUY - 1) / kUY);
     auto blocks = [&](int z) { return ncol * ((g.n[2] + z - 1) / z); };
-    auto steps = [&](int z) { return (long long)((blocks(z) + kUBlocks - 1) / kUBlocks) * (z + 11); };
+    auto steps = [&](int z) { return (long long)((blocks(z) + kCUs - 1) / kCUs) * (z + trail); };
     zc = 4;
     for (int z = 8; z / 2 < g.n[2]; z *= 2)
-        if (steps(z) < steps(zc)) zc = z;
+        if (steps(z) < steps(zc) || (max_blocks && blocks(zc) > max_blocks)) zc = z;
     ntiles = blocks(zc);
     return ntiles > 8 ? (ntiles + 7) & ~7 : ntiles;
 }
-
-// Columns, planes per block (a multiple of 4) and blocks of that pass: 16
-// planes, fewer where that leaves a CU without a block (80^3 FP64 13.1 us with
-// 8 planes, 20.8 with 16), more where the blocks would outnumber the partials
-// of r.z.
 static int sweep3_grid(const Geo &g, int &ntx, int &ncol, int &zc, int &ntiles) {
-    ntx = (g.n[0] + kUX - 1) / kUX;
-    ncol = ntx * ((g.n[1] + kUY - 1) / kUY);
-    zc = kUPlanes;
-    auto blocks = [&] { return ncol * ((g.n[2] + zc - 1) / zc); };
-    while (zc > 4 && blocks() < kUBlocks) zc /= 2;
-    while (blocks() > kRedBlocks && zc < g.n[2]) zc *= 2;
-    ntiles = blocks();
-    return ntiles > 8 ? (ntiles + 7) & ~7 : ntiles;
+    return march3_grid(g, kSweepTrail, kRedBlocks, ntx, ncol, zc, ntiles);
 }
 
 // Whether level l of a 3D slot runs the tile passes: above the
@@ -1941,7 +1944,7 @@ static void vcycle_down(Slot<T> &S, int l, const TB *b, T *x, const int *done, h
     if constexpr (DIM == 3) {
         // b, invd, cs in; pre-smoothed x (to r: the way up reads it there while it writes x) and the coarse b out
         int ntx, ncol, zc, ntiles;
-        const int grid = down3_grid(lv.g, ntx, ncol, zc, ntiles);
+        const int grid = march3_grid(lv.g, kDownTrail, 0, ntx, ncol, zc, ntiles);
         TLAUNCH(K_MG_DOWN, (sizeof(TB) + W * (2 + DIM)) * N + W * Nc, (k_down3<T, TB>), dim3(grid),
                 dim3(DownShape::threads), st, lv, b, S.lev[l + 1].g, lv.r, S.lev[l + 1].b, ntx, ncol, zc, ntiles, done);
     }
@@ -2035,7 +2038,16 @@ static void vcycle_d(Slot<T> &S, const TB *b0, T *x0, const int *done, hipStream
         }
         vcycle_down<T, TB, DIM, TR>(S, 0, b0, x0, done, st, cg);
         for (int l = 1; l < lt; ++l) vcycle_down<T, T, DIM>(S, l, S.lev[l].b, S.lev[l].x, done, st);
-        sgs(S.lev[lt], (const T *)S.lev[lt].b, S.lev[lt].x, nullptr);
+        if (DIM == 3 && tile3_level(S, lt)) {
+            // (32^3 FP64 5.9 us against 8.6 in k_sweep3, whose 16 blocks march)
+            Level<T> &L = S.lev[lt];
+            int ntx, nty, ntiles;
+            const int grid = tile3_grid(S.lev[lt + 1].g, ntx, nty, ntiles);
+            TLAUNCH(K_SMOOTH, W * (4 + DIM) * L.g.N, (k_up3_tile<T, T, false>), dim3(grid), dim3(kT3Threads), st, L,
+                    S.lev[lt + 1].g, (const T *)nullptr, (const T *)L.b, (const T *)nullptr, L.x, ntx, nty, ntiles, done);
+        } else {
+            sgs(S.lev[lt], (const T *)S.lev[lt].b, S.lev[lt].x, nullptr);
+        }
         for (int l = lt - 1; l >= 1; --l) vcycle_up<T, T, DIM>(S, l, S.lev[l].b, S.lev[l].x, done, st);
         vcycle_up<T, TB, DIM, TR>(S, 0, b0, x0, done, st, cg, rz);
         return;
@@ -2182,7 +2194,7 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
             int ntx, ncol, zc, ntiles;
             const int grid = sweep3_grid(g, ntx, ncol, zc, ntiles);
             if (kind == OP_SLOT && SP.lsb > 0 && ntiles <= kRedBlocks) {   // (level 0 above the small levels: even extents)
-                TLAUNCH(K_PCG_DOT, (W + WP) * N, (k_pcg_rz3<T, TP>), dim3(grid), dim3(SweepShape::nR * kWave), st, g,
+                TLAUNCH(K_PCG_DOT, (W + WP) * N, (k_pcg_rz3<T, TP>), dim3(grid), dim3(SweepShape::nB * kWave), st, g,
                         (const T *)v.r, (const TP *)v.z, (const Scal *)sc, red.rz0, red.rz1, red.rz2, ntx, ncol, zc,
                         ntiles);
                 nrz = ntiles;
