@@ -115,10 +115,9 @@ int spectral_init(Spectral &S, double h, std::string &err) {
 void spectral_release(Spectral &S) { S.on = 0; }
 
 // ---------------------------------------------------------------------------
-// axis transforms: C(m, n) = sum_k A(m, k) B(k, n) per batch entry, FP64
-// FMAs on 64 x 64 output tiles of a 256-thread workgroup (4 x 4 outputs per
-// thread, k in chunks of 16 staged in LDS).  Operands are addressed by
-// element strides, so one kernel covers every axis and both directions.
+// axis transforms: C(m, n) = sum_k A(m, k) B(k, n) per batch entry, FP64, on
+// output tiles of a 256-thread workgroup.  Operands are addressed by element
+// strides, so one kernel covers every axis and both directions.
 // ---------------------------------------------------------------------------
 struct AxOp {
     const double *p;            // base of batch entry 0
@@ -137,176 +136,111 @@ struct AxOut {
 
 constexpr int kGThreads = 256;
 
-// TS x TS output tile (TS = 64 or 32): a 16 x 16 thread grid, each thread
-// (TS / 16)^2 outputs.  k runs in chunks of KC = 2048 / TS staged in LDS;
-// the loads of the next chunk are in flight while the current one is used.
-template <int TS>
-__global__ void __launch_bounds__(kGThreads) k_axis_gemm(int M, int N, int K, AxOp A, AxOp B, AxOut C) {
-    constexpr int R = TS / 16, KC = 2048 / TS, PT = TS * KC / kGThreads;   // staged values per thread
-    __shared__ double As[KC][TS + 1], Bs[KC][TS + 1];
-    const int bz = (int)blockIdx.z;
-    const double *a = A.at(bz), *bp = B.at(bz);
-    double *c = C.at(bz);
-    const int m0 = (int)blockIdx.y * TS, n0 = (int)blockIdx.x * TS;
-    const int tid = (int)threadIdx.x, tm = tid / 16, tn = tid % 16;
-    // staging positions: the index that is contiguous in memory runs
-    // fastest across the threads
-    auto a_pos = [&](int e, int &mm, int &kk) {
-        if (A.s1 == 1) {
-            kk = e % KC;
-            mm = e / KC;
-        } else {
-            mm = e % TS;
-            kk = e / TS;
-        }
-    };
-    auto b_pos = [&](int e, int &nn, int &kk) {
-        if (B.s1 == 1) {
-            nn = e % TS;
-            kk = e / TS;
-        } else {
-            kk = e % KC;
-            nn = e / KC;
-        }
-    };
-    double ra[PT], rb[PT];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int r = 0; r < PT; ++r) {
-            int mm, kk, nn, kb;
-            a_pos(tid + kGThreads * r, mm, kk);
-            b_pos(tid + kGThreads * r, nn, kb);
-            const int gm = m0 + mm, gk = k0 + kk, gn = n0 + nn, gkb = k0 + kb;
-            ra[r] = (gm < M && gk < K) ? a[(long long)gm * A.s0 + (long long)gk * A.s1] : 0.0;
-            rb[r] = (gn < N && gkb < K) ? bp[(long long)gkb * B.s0 + (long long)gn * B.s1] : 0.0;
-        }
-    };
-    double acc[R][R];
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < R; ++j) acc[i][j] = 0.0;
-    fetch(0);
-    for (int k0 = 0; k0 < K; k0 += KC) {
-#pragma unroll
-        for (int r = 0; r < PT; ++r) {
-            int mm, kk, nn, kb;
-            a_pos(tid + kGThreads * r, mm, kk);
-            b_pos(tid + kGThreads * r, nn, kb);
-            As[kk][mm] = ra[r];
-            Bs[kb][nn] = rb[r];
-        }
-        __syncthreads();
-        if (k0 + KC < K) fetch(k0 + KC);   // in flight during the products below
-        const int kn = K - k0 < KC ? K - k0 : KC;
-#pragma unroll 4
-        for (int kk = 0; kk < kn; ++kk) {
-            double av[R], bv[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) av[i] = As[kk][tm + 16 * i];
-#pragma unroll
-            for (int j = 0; j < R; ++j) bv[j] = Bs[kk][tn + 16 * j];
-#pragma unroll
-            for (int i = 0; i < R; ++i)
-#pragma unroll
-                for (int j = 0; j < R; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int gm = m0 + tm + 16 * i, gn = n0 + tn + 16 * j;
-            if (gm < M && gn < N) c[(long long)gm * C.s0 + (long long)gn * C.s1] = acc[i][j];
-        }
-}
-
-// 64 x 64 output tile on the FP64 matrix cores: the four waves of the
-// workgroup form a 2 x 2 grid of 32 x 32 blocks, each four 16 x 16 x 4 MFMA
-// accumulators.  Staging and chunks (KC = 32) as in k_axis_gemm<64>.
+// TS x TS output tile (TS = 64 or 32) on the FP64 matrix cores: the four waves
+// of the workgroup form a 2 x 2 grid of blocks, each (TS / 32)^2 accumulators
+// of the 16 x 16 x 4 MFMA.  k runs in chunks of KC staged in LDS; the loads of
+// the next chunk are in flight while the current one is used.
 // Operand layout of the FP64 16 x 16 x 4 MFMA: lane l supplies A(l % 16,
 // l / 16) and B(l / 16, l % 16); element v of its accumulator is
-// C(4 v + l / 16, l % 16).  Values staged past M, N or K are zero, so every
-// chunk runs all of its k.
+// C(4 v + l / 16, l % 16).  Values staged past M, N or K are zero, so a step of
+// four may reach past K.
+// The unit is as fast as FP64 vector code here; what it saves is LDS: a wave
+// reads two values per lane for 2048 flops, where a 2 x 2 block per lane of a
+// vector kernel read four for 512, and waited for them.  768 x 768 x 768: 81 us
+// with that kernel on 32-wide tiles, 35 here (40 with the staged addresses and
+// edge checks formed anew for every chunk; 12 at the unit's rate: 2.25 tiles
+// per CU, a barrier pair per chunk); 64 x 64 per plane of 64^3 7.3 -> 4.7; 96^3,
+// 64-wide, 14 -> 13; ensemble 95 -> 81.  Loads two chunks ahead: no gain.
+// Rows are TS + 17 apart: the four rows of a read and the stores that run
+// along k both spread over the banks.
 typedef double dbl4 __attribute__((ext_vector_type(4)));
-constexpr int kMfmaKC = 32;   // k per staged chunk
 
-template <int KC>
-__global__ void __launch_bounds__(kGThreads) k_axis_mfma64(int M, int N, int K, AxOp A, AxOp B, AxOut C) {
-    constexpr int TS = 64, PT = TS * KC / kGThreads;
-    __shared__ double As[KC][TS + 1], Bs[KC][TS + 1];
+template <int TS>
+__global__ void __launch_bounds__(kGThreads) k_axis_mfma(int M, int N, int K, AxOp A, AxOp B, AxOut C) {
+    constexpr int KC = 2048 / TS, PT = TS * KC / kGThreads, NB = TS / 32, LD = TS + 17;
+    __shared__ double As[KC][LD], Bs[KC][LD];
     const int bz = (int)blockIdx.z;
     const double *a = A.at(bz), *bp = B.at(bz);
     double *c = C.at(bz);
     const int m0 = (int)blockIdx.y * TS, n0 = (int)blockIdx.x * TS;
     const int tid = (int)threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32, li = lane & 15, lk = lane >> 4;
-    auto a_pos = [&](int e, int &mm, int &kk) {
-        if (A.s1 == 1) {
-            kk = e % KC;
-            mm = e / KC;
-        } else {
-            mm = e % TS;
-            kk = e / TS;
-        }
+    const int wm = (w >> 1) * (TS / 2), wn = (w & 1) * (TS / 2), li = lane & 15, lk = lane >> 4;
+    // Staged element e of an operand whose k index has stride s1: (row or
+    // column, k), the index that is contiguous in memory running fastest
+    // across the threads.  Rows and columns past the edge repeat the last one
+    // (their outputs are not stored); k past K enters as 0.
+    auto pos = [](int e, bool kfast, int &i, int &kk) {
+        kk = kfast ? e % KC : e / TS;
+        i = kfast ? e / KC : e % TS;
     };
-    auto b_pos = [&](int e, int &nn, int &kk) {
-        if (B.s1 == 1) {
-            nn = e % TS;
-            kk = e / TS;
-        } else {
-            kk = e % KC;
-            nn = e / KC;
-        }
-    };
+    const bool ka = A.s1 == 1, kb = B.s1 != 1;
+    const double *pa[PT], *pb[PT];   // advanced from chunk to chunk: indices and checks once per tile
+    int da[PT], db[PT], qa[PT], qb[PT];
+#pragma unroll
+    for (int r = 0; r < PT; ++r) {
+        int i;
+        pos(tid + kGThreads * r, ka, i, qa[r]);
+        da[r] = qa[r] * LD + i;
+        pa[r] = a + (long long)(m0 + i < M ? m0 + i : M - 1) * A.s0 + (long long)qa[r] * A.s1;
+        pos(tid + kGThreads * r, kb, i, qb[r]);
+        db[r] = qb[r] * LD + i;
+        pb[r] = bp + (long long)(n0 + i < N ? n0 + i : N - 1) * B.s1 + (long long)qb[r] * B.s0;
+    }
     double ra[PT], rb[PT];
     auto fetch = [&](int k0) {
+        if (k0 + KC <= K) {
+#pragma unroll
+            for (int r = 0; r < PT; ++r) {
+                ra[r] = *pa[r];
+                rb[r] = *pb[r];
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < PT; ++r) {
+                ra[r] = k0 + qa[r] < K ? *pa[r] : 0.0;
+                rb[r] = k0 + qb[r] < K ? *pb[r] : 0.0;
+            }
+        }
 #pragma unroll
         for (int r = 0; r < PT; ++r) {
-            int mm, kk, nn, kb;
-            a_pos(tid + kGThreads * r, mm, kk);
-            b_pos(tid + kGThreads * r, nn, kb);
-            const int gm = m0 + mm, gk = k0 + kk, gn = n0 + nn, gkb = k0 + kb;
-            ra[r] = (gm < M && gk < K) ? a[(long long)gm * A.s0 + (long long)gk * A.s1] : 0.0;
-            rb[r] = (gn < N && gkb < K) ? bp[(long long)gkb * B.s0 + (long long)gn * B.s1] : 0.0;
+            pa[r] += (long long)KC * A.s1;
+            pb[r] += (long long)KC * B.s0;
         }
     };
-    dbl4 acc[2][2];
+    dbl4 acc[NB][NB];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
+        for (int j = 0; j < NB; ++j) acc[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
     fetch(0);
     for (int k0 = 0; k0 < K; k0 += KC) {
 #pragma unroll
         for (int r = 0; r < PT; ++r) {
-            int mm, kk, nn, kb;
-            a_pos(tid + kGThreads * r, mm, kk);
-            b_pos(tid + kGThreads * r, nn, kb);
-            As[kk][mm] = ra[r];
-            Bs[kb][nn] = rb[r];
+            (&As[0][0])[da[r]] = ra[r];
+            (&Bs[0][0])[db[r]] = rb[r];
         }
         __syncthreads();
         if (k0 + KC < K) fetch(k0 + KC);   // in flight during the products below
+        const int kn = K - k0;
 #pragma unroll
         for (int k4 = 0; k4 < KC; k4 += 4) {
-            double av[2], bv[2];
+            if (k4 >= kn) break;
+            double av[NB], bv[NB];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) av[i] = As[k4 + lk][wm + 16 * i + li];
+            for (int i = 0; i < NB; ++i) av[i] = As[k4 + lk][wm + 16 * i + li];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) bv[j] = Bs[k4 + lk][wn + 16 * j + li];
+            for (int j = 0; j < NB; ++j) bv[j] = Bs[k4 + lk][wn + 16 * j + li];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int gm = m0 + wm + 16 * i + 4 * v + lk, gn = n0 + wn + 16 * j + li;
@@ -318,7 +252,7 @@ __global__ void __launch_bounds__(kGThreads) k_axis_mfma64(int M, int N, int K, 
 // g computes the 4 x 4 block of rows t / 4 + 4 i and columns t % 4 + 4 j over
 // the k of each chunk with k mod 16 = g (half an LDS read per FMA, where one
 // output per thread takes two), then the 16 partial blocks are summed in
-// group order.  Staging and chunks (KC = 128) as in k_axis_gemm.
+// group order.  Staging and chunks (KC = 128) as in k_axis_mfma.
 __global__ void __launch_bounds__(kGThreads) k_axis_gemm16s(int M, int N, int K, AxOp A, AxOp B, AxOut C) {
     constexpr int TS = 16, KC = 2048 / TS, PT = TS * KC / kGThreads, G = kGThreads / 16;
     static_assert(2 * KC * (TS + 1) >= G * TS * TS, "partial sums reuse the staging LDS");
@@ -406,17 +340,18 @@ __global__ void __launch_bounds__(kGThreads) k_axis_gemm16s(int M, int N, int K,
     if (gm < M && gn < N) c[(long long)gm * C.s0 + (long long)gn * C.s1] = v;
 }
 
-// The widest of 64, 32, 16 output tiles that still gives every CU a
-// workgroup (the smaller tiles trade operand reuse for parallelism; the
-// 16-wide ones split k to keep some)
+// The widest of 64, 32, 16 output tiles that still gives every CU a workgroup
+// (the smaller tiles trade operand reuse for parallelism; the 16-wide ones
+// split k to keep some).  512 problems of the ensemble, 42 us at 64, 54 at 32;
+// 96^2 x 96 x 96, where 64 pads, 14 us at either.
 static void axis_gemm(int M, int N, int K, const AxOp &A, const AxOp &B, const AxOut &C, int batch, hipStream_t st) {
     auto tiles = [&](int t) { return (long long)((M + t - 1) / t) * ((N + t - 1) / t) * batch; };
     if (tiles(64) >= 256)
-        hipLaunchKernelGGL(k_axis_mfma64<kMfmaKC>, dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(kGThreads), 0, st, M,
-                           N, K, A, B, C);
+        hipLaunchKernelGGL(k_axis_mfma<64>, dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(kGThreads), 0, st, M, N, K,
+                           A, B, C);
     else if (tiles(32) >= 256)
-        hipLaunchKernelGGL(k_axis_gemm<32>, dim3((N + 31) / 32, (M + 31) / 32, batch), dim3(kGThreads), 0, st, M, N,
-                           K, A, B, C);
+        hipLaunchKernelGGL(k_axis_mfma<32>, dim3((N + 31) / 32, (M + 31) / 32, batch), dim3(kGThreads), 0, st, M, N, K,
+                           A, B, C);
     else
         hipLaunchKernelGGL(k_axis_gemm16s, dim3((N + 15) / 16, (M + 15) / 16, batch), dim3(kGThreads), 0, st, M, N, K,
                            A, B, C);

@@ -7,9 +7,12 @@ and the V-cycle-preconditioned operator has a condition number of a few
 units per decade of density contrast, so the field comes back to 1e-9 as in
 the pressure parity tests.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
+import workloads as W
 from oracle import MACGrid
 
 pytestmark = pytest.mark.gpu
@@ -110,3 +113,25 @@ def test_small_level_cycle_forms(n, per, precision):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_post_sweep_forms(n, per, precision):
     assert solve_error(n, per, ratio=0.01, precision=precision, tile_cells=0) <= 1e-9
+
+
+# axis transforms of the direct Cahn-Hilliard solve on 32-wide matrix-core
+# tiles: a ragged last tile and k below one chunk (40), k of one chunk and a
+# part (72), several chunks with a ragged last one (544).  Bar: MG-PCG stops at
+# 1e-10 per solve, as in the parity test of the direct solve.
+@pytest.mark.parametrize("n,bc", [((40, 72, 72), ("periodic", "wall", "periodic")), ((576, 544), ("wall", "periodic"))])
+def test_axis_transform_forms(n, bc):
+    P = _lib()
+    prob = W.spinodal(n[0], steps=2, bc=(W.PERIODIC,) * len(n))
+    prob = dataclasses.replace(prob, n=n, bc=tuple({"periodic": W.PERIODIC, "wall": W.WALL}[b] for b in bc))
+    out = []
+    for solver in (P.CHNS_CH_DIRECT, P.CHNS_CH_PCG):
+        print("CH solver", n, solver, flush=True)
+        g = P.grid_for_problem(prob)
+        g.set_option(P.CHNS_OPT_CH_SOLVER, solver)
+        st = g.new_state(W.initial_state(prob))
+        stats = g.step(st, 2)
+        out.append((st["phi"].cpu().numpy(), stats["iters_ch"]))
+    (a, ia), (b, ib) = out
+    assert ia == 1 and ib > 1
+    assert float(np.abs(a - b).max() / np.abs(b).max()) < 1e-8
