@@ -1282,11 +1282,12 @@ __global__ void __launch_bounds__(SweepShape::nB * kWave) k_pcg_rz3(Geo g, const
 // touches as many cache lines).
 // b, 1 / d and three coefficients are read and x written once: 48 B per cell in
 // FP64 where pre-smoothing, residual and restriction moved 121.  Measured
-// against these three: 128^3 FP64 43.7 us -> 24.7, FP32 29.8 -> 18.3; 96^3 FP64
-// 34.3 -> 16.8; 512^3 3.37 ms -> 2.0.  What bounds it is, at 512^3, memory (the
-// least bytes take 1.35 ms), and below the cache lines a CU can look up (halos
-// of 3, 2 and 1 cells make it load 1.7 times the owned cells) and the steps by
-// which the roles trail.  8 rows per column instead of 16: 96^3 level and 128^3
+// against these three: 128^3 FP64 43.7 us -> 21.3, FP32 29.8 -> 14.9; 96^3 FP64
+// 34.3 -> 14.2; 512^3 3.37 ms -> 1.82.  What bounds it is, at 512^3, memory (the
+// least bytes take 1.35 ms; halo lines that have left the L2 make it fetch 1.7
+// times them), and below the cache lines a CU can look up (halos of 3, 2 and
+// 1 cells) and the steps by which the roles trail.  b and 1 / d go to the second
+// role through LDS: with loads of its own, 128^3 24.7, 96^3 15.7, 512^3 2.06.  8 rows per column instead of 16: 96^3 level and 128^3
 // 10 % slower, 512^3 solve 377 ms against 350.
 // ---------------------------------------------------------------------------
 struct DownShape {
@@ -1308,6 +1309,7 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
     if (tile >= ntiles || *done) return;
     static_assert(sizeof(T) == sizeof(TB), "offsets in bytes of both");
     __shared__ T D[4][Sh::D], X[2][Sh::X], R[2][Sh::X];
+    __shared__ Pair2<T> F[4][2][Sh::D];   // b, 1 / d of the pairs of D
     const Geo &g = L.g;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
     const long long nxy = (long long)nx * ny;
@@ -1316,33 +1318,39 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = (int)threadIdx.x & (kWave - 1);
     const int total = n + 11;   // every role ends its group of four within these steps
     if (wave < Sh::wX) {
-        // red b / d of plane z0 - 3 + s, into D[s & 3]
+        // red b / d of plane z0 - 3 + s, into D[s & 3]; b and 1 / d of both
+        // cells for the second role, which would fetch the lines again two
+        // planes later
         const int u = (int)threadIdx.x;
         const bool on = u < Sh::D;
         const int ly = on ? u / Sh::DM : 0, m = (on ? u : 0) - ly * Sh::DM;
         int gx, gy;
         const bool ok = wrap_axis(x0 - 4 + 2 * m, nx, g.per[0], gx) & wrap_axis(y0 - 3 + ly, ny, g.per[1], gy);
         gx &= ~1;
-        unsigned off[2];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) off[p] = (unsigned)(gx + ((ly + p) & 1) + nx * gy) * sizeof(T);   // (y0 - 3 + ly + z0 - 3 + s even: red at 0)
+        const unsigned off = (unsigned)(gx + nx * gy) * sizeof(T);
         struct Ops {
-            T a, d;
+            Pair2<T> a, d;
         };
         sweep_role<0, Ops>(
             n + 5, total,
-            [&](int s, auto P, Ops &o) {
+            [&](int s, auto, Ops &o) {
                 int gz;
                 (void)wrap_axis(z0 - 3 + s, nz, g.per[2], gz);
                 const long long z = gz * nxy;
-                o.a = (T)plane_at(b + z, off[decltype(P)::value]);
-                o.d = plane_at(L.invd + z, off[decltype(P)::value]);
+                o.a = pair_at((const T *)(const void *)b + z, off);
+                o.d = pair_at(L.invd + z, off);
             },
             [&](int s, auto K, const Ops &o) {
                 int gz;
                 const bool okz = wrap_axis(z0 - 3 + s, nz, g.per[2], gz);
-                const T v = o.a * o.d;
-                if (on) D[decltype(K)::value][u] = okz && ok ? v : (T)0;
+                constexpr int k = decltype(K)::value;
+                const bool hi = (ly + k) & 1;   // the red cell of the pair (y0 - 3 + ly + z0 - 3 + s even: the lower one)
+                const T v = (hi ? o.a.v[1] : o.a.v[0]) * (hi ? o.d.v[1] : o.d.v[0]);
+                if (on) {
+                    D[k][u] = okz && ok ? v : (T)0;
+                    F[k][0][u] = o.a;
+                    F[k][1][u] = o.d;
+                }
             });
         return;
     }
@@ -1360,7 +1368,7 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
         const int xl = m > 0 ? qx - 1 : qx, xh = m < kUM - 1 ? qx + 1 : qx;
         const int yl = ly > 0 ? qx - kUM : qx, yh = ly < Sh::rows - 1 ? qx + kUM : qx;
         struct Ops {
-            T b, d, n;
+            T n;
             Pair2<T> c0, c1, h1, c2;   // c2: of the plane above
         };
         auto run = [&](auto RP) {
@@ -1376,14 +1384,11 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
             Pair2<T> c2 = pair_at(L.cs[2] + gf * nxy, off);
             sweep_role<3, Ops>(
                 n + 6, total,
-                [&](int s, auto P, Ops &o) {
-                    constexpr int blk = (rpar + decltype(P)::value) & 1;   // the black cell of the pair
+                [&](int s, auto, Ops &o) {
                     int gz, gh;
                     (void)wrap_axis(z0 - 5 + s, nz, g.per[2], gz);
                     (void)wrap_axis(z0 - 4 + s, nz, g.per[2], gh);
                     const long long z = gz * nxy;
-                    o.b = (T)plane_at(b + z, off + blk * (unsigned)sizeof(T));
-                    o.d = plane_at(L.invd + z, off + blk * (unsigned)sizeof(T));
                     o.c0 = pair_at(L.cs[0] + z, off);
                     o.n = plane_at(L.cs[0] + z, offn);
                     o.c1 = pair_at(L.cs[1] + z, off);
@@ -1391,7 +1396,7 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
                     o.c2 = pair_at(L.cs[2] + gh * nxy, off);
                 },
                 [&](int s, auto K, const Ops &o) {
-                    constexpr int k = decltype(K)::value, blk = (rpar + k) & 1, red = 1 - blk;
+                    constexpr int k = decltype(K)::value, blk = (rpar + k) & 1, red = 1 - blk;   // the pair's black and red cell
                     const int p = z0 - 5 + s;
                     int gz;
                     const bool okz = wrap_axis(p, nz, g.per[2], gz);
@@ -1404,7 +1409,7 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
                         T acc = 0.0;
 #pragma unroll
                         for (int i = 0; i < 6; ++i) acc = fmar(wt[i], v[i], acc);
-                        val = (o.b + acc) * o.d;
+                        val = (F[(k + 2) & 3][0][q].v[blk] + acc) * F[(k + 2) & 3][1][q].v[blk];
                         val = okz && ok ? val : (T)0;
                         if (on) X[k & 1][qx] = val;
                         if (own && p >= z0 && p < z1) {
@@ -1488,9 +1493,9 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
 // Columns, planes per block (a multiple of 4) and blocks of these passes.  A CU
 // holds one block (12 or 15 waves of up to 128 registers), so a pass takes
 // ceil(blocks / CUs) rounds of a chunk's planes and the steps by which its
-// roles trail: the planes that make this least (k_down3 FP64 on 96^3, 8 planes,
-// 216 blocks: 17 us, 4 planes, 432 blocks: 22; on 128^3, 16 planes, 256 blocks:
-// 24, 32 planes: 33).  max_blocks: more planes where the blocks outnumber the
+// roles trail: the planes that make this least (k_down3 FP64, of an
+// earlier form, on 96^3, 8 planes, 216 blocks: 17 us, 4 planes, 432 blocks: 22;
+// on 128^3, 16 planes, 256 blocks: 24, 32 planes: 33).  max_blocks: more planes where the blocks outnumber the
 // partials of r.z.
 constexpr int kSweepTrail = 8, kDownTrail = 11;
 static int march3_grid(const Geo &g, int trail, int max_blocks, int &ntx, int &ncol, int &zc, int &ntiles) {
