@@ -503,22 +503,23 @@ int chns_set_wall_velocity(struct chns_grid *g, int axis, int side, int componen
  *   CHNS_OPT_PICARD_ITERATIONS  Picard iterations per Crank-Nicolson step
  *                               (default 3).
  *   CHNS_OPT_MARCH_SWEEP_CELLS  3D multigrid levels with at least this many
- *                               cells run their smoothing and residual
- *                               sweeps marching along z with the stencil's
- *                               planes in LDS, and the CG apply of a pressure
- *                               solve on such a grid forms its face
- *                               coefficients from the cell density instead
- *                               of reading them (default 16777216: levels
- *                               whose arrays outgrow the 256 MB Infinity
- *                               Cache); >= 1.  Either form computes the same
- *                               per-cell arithmetic, bit for bit.
+ *                               cells run the passes that march along z,
+ *                               whatever CHNS_OPT_TILE_CYCLE_CELLS says, and
+ *                               the CG apply of a pressure solve on such a
+ *                               grid forms its face coefficients from the
+ *                               cell density instead of reading them (default
+ *                               16777216: levels whose arrays outgrow the
+ *                               256 MB Infinity Cache); >= 1.  Either form
+ *                               computes the same per-cell arithmetic, bit
+ *                               for bit.
  *   CHNS_OPT_TILE_CYCLE_CELLS   3D multigrid levels with at most this many
  *                               cells (below the march-sweep size, above the
  *                               part solved in one workgroup) run each side
  *                               of the V-cycle as one launch over 8^3-cell
  *                               tiles that recompute their halos in LDS
- *                               instead of three grid-wide launches (default
- *                               262144: 64^3 cells and below; 0: never).
+ *                               instead of columns that march along z
+ *                               (default 262144: 64^3 cells and below; 0:
+ *                               never).
  *                               Same per-cell arithmetic, bit for bit.
  *   CHNS_OPT_TIME_GUESS         1 (default): the S7 and S8 solves of a split
  *                               step start from their solutions of the

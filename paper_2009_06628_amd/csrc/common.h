@@ -203,9 +203,9 @@ struct Slot {
     int lsb;        // first level handled by the single-workgroup kernel
     int ltrunc;     // 3D: the V-cycle ends at this grid level with a symmetric
                     // Gauss-Seidel solve (-1: full cycle down to the coarsest)
-    long long march_cells;   // 3D levels with at least this many cells sweep marching along z
+    long long march_cells;   // 3D levels with at least this many cells never run the tile passes
     long long tile_cells;    // 3D levels with at most this many cells (above the single-workgroup
-                             // part, below march_cells) run one tile pass per side of the cycle
+                             // part, below march_cells) run tile passes, the others march along z
     const double *rho;       // pressure slots: cell densities whose face averages give the level-0
     double rho_ih2;          // coefficients 1/(rho_f h^2) (rho_ih2 = the 1/h^2 they were formed with);
                              // the 3D CG apply forms them on the fly on grids of at least march_cells
