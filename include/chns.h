@@ -518,8 +518,7 @@ int chns_set_wall_velocity(struct chns_grid *g, int axis, int side, int componen
  *                               of the V-cycle as one launch over 8^3-cell
  *                               tiles that recompute their halos in LDS
  *                               instead of columns that march along z
- *                               (default 262144: 64^3 cells and below; 0:
- *                               never).
+ *                               (default 131072: below 64^3 cells; 0: never).
  *                               Same per-cell arithmetic, bit for bit.
  *   CHNS_OPT_TIME_GUESS         1 (default): the S7 and S8 solves of a split
  *                               step start from their solutions of the

@@ -221,8 +221,10 @@ struct Slot {
 // Cache (256^3 cells and up).
 constexpr long long kMarchSweepCells = 1LL << 24;
 // Default of Slot::tile_cells: the levels whose sweeps cost less than their
-// launches (64^3 cells and below).
-constexpr long long kTileCycleCells = 1LL << 18;
+// launches.  On 64^3 the marching passes are faster by now (drop step FP64 1862
+// us with the tile passes there, 1713 without; cavity 1317 / 1218), on 48^3
+// the tile passes (96^3 drop step 3038 us with them there, 3480 without).
+constexpr long long kTileCycleCells = 1LL << 17;
 
 // Reduction scratch shared by all solves of a handle.
 struct Red {
