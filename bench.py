@@ -148,7 +148,7 @@ KERNEL_CLASSES = {
                   "k_velocity_guess", "k_cn_mom_setup"),
     "p_setup": ("k_p_setup", "k_p_setup3", "k_p_coef_rho", "k_pressure_guess"),
     "project": ("k_project", "k_project3", "k_cn_project", "k_cn_finish"),
-    "mg_setup": ("k_coarsen", "k_conv_coef", "k_fill_ch", "k_invd", "k_setup_block"),
+    "mg_setup": ("k_coarsen", "k_conv_coef", "k_fill_ch", "k_invd", "k_setup_block", "k_gj_step"),
     "pcg_init": ("k_pcg_init_slot", "k_pcg_init_zero", "k_pcg_init_ch", "k_pcg_fin_init", "k_round_vec",
                  "k_ch_lap_plain", "k_cn_zero"),
     "mean": ("k_sum", "k_sub_mean"),

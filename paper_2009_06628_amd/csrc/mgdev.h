@@ -1036,9 +1036,10 @@ __device__ inline void coarse_matrix_block(const Level<T> &C, int singular, doub
 // Set-up of the small levels in one workgroup: coarsen from level
 // max(l0,1) - 1 downwards, inverse diagonals, then the coarsest inverse
 // (in LDS when it has at most kLdsInverse cells, else in S.aug).  Ends with
-// a workgroup barrier.
+// a workgroup barrier.  mat (when given): the coarsest matrix is left there and
+// not inverted.
 template <typename T, int DIM>
-__device__ inline void setup_block_dev(const Slot<T> &S, int l0, SetupLds &sh) {
+__device__ inline void setup_block_dev(const Slot<T> &S, int l0, SetupLds &sh, double *mat = nullptr) {
     const int L = S.nlev;
     if (l0 == 0) {
         BLOCK_LOOP(S.lev[0].g.N) invd_cell<T, DIM>(S.lev[0], c);
@@ -1052,8 +1053,9 @@ __device__ inline void setup_block_dev(const Slot<T> &S, int l0, SetupLds &sh) {
     }
     // dense coarsest operator
     const int n = (int)S.lev[L - 1].g.N;
-    double *M = n <= kLdsInverse ? sh.A : S.aug;
+    double *M = mat ? mat : (n <= kLdsInverse ? sh.A : S.aug);
     coarse_matrix_block<T, DIM>(S.lev[L - 1], S.singular, M, sh.red);
+    if (mat) return;
     gauss_jordan_inplace(M, n, sh.f, &sh.piv);
     for (int e = threadIdx.x; e < n * n; e += blockDim.x) S.Ainv[e] = M[e];
     __syncthreads();
@@ -1078,10 +1080,10 @@ struct SetupLdsLev {
     T lev[(1 + DIM) * kSetupLdsCells];
 };
 template <typename T, int DIM>
-__device__ inline void setup_lds_dev(const Slot<T> &S, int l0, SetupLdsLev<T, DIM> &sh) {
+__device__ inline void setup_lds_dev(const Slot<T> &S, int l0, SetupLdsLev<T, DIM> &sh, double *mat = nullptr) {
     const int L = S.nlev, n = (int)S.lev[L - 1].g.N;
     if (n > kLdsInverse || L < 2 || S.lev[l0 > 1 ? l0 : 1].g.N > 2 * kSBThreads) {
-        setup_block_dev<T, DIM>(S, l0, sh.base);
+        setup_block_dev<T, DIM>(S, l0, sh.base, mat);
         return;
     }
     if (l0 == 0) BLOCK_LOOP(S.lev[0].g.N) invd_cell<T, DIM>(S.lev[0], c);

@@ -135,3 +135,13 @@ def test_axis_transform_forms(n, bc):
     (a, ia), (b, ib) = out
     assert ia == 1 and ib > 1
     assert float(np.abs(a - b).max() / np.abs(b).max()) < 1e-8
+
+
+# coarsest levels inverted by block steps of 16 pivots: 66 and 72 cells (a part
+# of a block left over; an odd number of blocks), 255, 306, 448 and 486 cells
+@pytest.mark.parametrize("n,per", [((88, 48), (True, False)), ((72, 64), (False, False)), ((34, 30), (True, True)),
+                                   ((144, 136), (False, True)), ((56, 64, 64), (False, False, True)),
+                                   ((36, 36, 24), (True, True, True))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_coarse_inverse_block_forms(n, per, precision):
+    assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
