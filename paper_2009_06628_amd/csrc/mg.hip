@@ -383,15 +383,18 @@ __device__ inline bool iter_start(Scal *sc, const double *__restrict__ p0, const
 }
 
 // p_new = (z - zmean) + beta p_old (beta = 0: p_new = z - zmean);
-// q = A p_new (slot operator); partial p.q
-template <typename T, typename TZ, int DIM>
+// q = A p_new (slot operator); partial p.q.  RHO (3D pressure operator): the
+// face coefficients formed from the cell densities with the set-up's
+// expression instead of read, as in k_pcg_apply3_march below.
+template <typename T, typename TZ, int DIM, bool RHO>
 __global__ void __launch_bounds__(kBlock) k_pcg_apply_slot(Level<T> L, const TZ *__restrict__ z,
                                                            const T *__restrict__ pold, T *__restrict__ pnew,
                                                            T *__restrict__ q, Scal *sc, double *__restrict__ part,
                                                            const double *__restrict__ rz0,
                                                            const double *__restrict__ rz1,
                                                            const double *__restrict__ rz2, int nrz, int k,
-                                                           int singular, T *__restrict__ rpend) {
+                                                           int singular, T *__restrict__ rpend,
+                                                           const double *__restrict__ rho, double rho_ih2) {
     if (sc->done) return;
     __shared__ double lds[kBlock / kWave];
     const double alpha_prev = rpend ? sc->alpha : 0.0;   // read before iter_start
@@ -416,7 +419,8 @@ __global__ void __launch_bounds__(kBlock) k_pcg_apply_slot(Level<T> L, const TZ 
             const int hi = nb_hi(L.g, c, ia[b], b);
             const int l = lo >= 0 ? lo : c, h = hi >= 0 ? hi : c;
             const double vl = pv(l), vh = pv(h);
-            const double wl = (double)L.cs[b][c], wh = (double)L.cs[b][h];
+            const double wl = RHO ? 1.0 / (0.5 * (rho[c] + rho[l])) * rho_ih2 : (double)L.cs[b][c];
+            const double wh = RHO ? 1.0 / (0.5 * (rho[h] + rho[c])) * rho_ih2 : (double)L.cs[b][h];
             qc += (lo >= 0 ? wl : 0.0) * (pc - vl);
             qc += (hi >= 0 ? wh : 0.0) * (pc - vh);
         }
@@ -2310,10 +2314,12 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
     struct {
         int nb = 0, ncolx = 0, ncol = 0, zc = 0;
     } march;
+    bool dens = false;   // coefficients from the density (Slot::rho)
     if (DIM == 3 && kind == OP_SLOT) {
         const Geo &g0 = L0.g;
         march.ncolx = (g0.n[0] + kMX - 1) / kMX;
         march.ncol = march.ncolx * ((g0.n[1] + kMY - 1) / kMY);
+        dens = march.ncol <= kMaxBlocks && SA.rho && g0.N >= SA.march_cells;
         if (march.ncol <= kMaxBlocks && g0.N >= kMarchApplyCells) {   // else the grid-stride apply
             march.zc = kMarchPlanes;
             while (march.zc > 1 && march.ncol * ((g0.n[2] + march.zc - 1) / march.zc) < kMarchApplyBlocks)
@@ -2339,7 +2345,7 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
             // fused: it also stores the previous iteration's residual
             T *rpend = fuse && k > 0 ? v.r : nullptr;
             const double WRP = rpend ? 2.0 * W : 0.0;   // r read and written
-            if (kind == OP_SLOT && march.nb && SA.rho && g.N >= SA.march_cells) {
+            if (kind == OP_SLOT && march.nb && dens) {
                 // rho, p_old read; p_new, q written; z in its precision
                 TLAUNCH(K_PCG_APPLY, 8.0 * N + 3.0 * W * N + WP * N, (k_pcg_apply3_march<T, TP, true>),
                         dim3(march.nb), dim3(kBlock), st, L0, (const TP *)v.z, (const T *)pold, pnew, v.q, sc,
@@ -2350,10 +2356,18 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
                         dim3(kBlock), st, L0, (const TP *)v.z, (const T *)pold, pnew, v.q, sc, red.part0,
                         (const double *)red.rz0, (const double *)red.rz1, (const double *)red.rz2, nrz, k, singular,
                         march.ncolx, march.ncol, march.zc, (const double *)nullptr, 0.0);
+            } else if (kind == OP_SLOT && dens) {
+                // a threshold set below kMarchApplyCells: same bits as the stored coefficients give
+                if constexpr (DIM == 3)
+                    LAUNCHR(K_PCG_APPLY, 8.0 * N + 3.0 * W * N + WP * N, (k_pcg_apply_slot<T, TP, DIM, true>), N, st,
+                            L0, (const TP *)v.z, (const T *)pold, pnew, v.q, sc, red.part0, (const double *)red.rz0,
+                            (const double *)red.rz1, (const double *)red.rz2, nrz, k, singular, (T *)nullptr, SA.rho,
+                            SA.rho_ih2);
             } else if (kind == OP_SLOT) {
-                LAUNCHR(K_PCG_APPLY, W * (4 + DIM) * N + WP * N + WRP * N, (k_pcg_apply_slot<T, TP, DIM>), N, st,
-                        L0, (const TP *)v.z, (const T *)pold, pnew, v.q, sc, red.part0, (const double *)red.rz0,
-                        (const double *)red.rz1, (const double *)red.rz2, nrz, k, singular, rpend);
+                LAUNCHR(K_PCG_APPLY, W * (4 + DIM) * N + WP * N + WRP * N, (k_pcg_apply_slot<T, TP, DIM, false>), N,
+                        st, L0, (const TP *)v.z, (const T *)pold, pnew, v.q, sc, red.part0, (const double *)red.rz0,
+                        (const double *)red.rz1, (const double *)red.rz2, nrz, k, singular, rpend,
+                        (const double *)nullptr, 0.0);
             } else {
                 LAUNCHR(K_PCG_APPLY, W * 3 * N + WP * N + WRP * N, (k_pcg_ch_lap<T, TP, DIM>), N, st, g, ch.ih2,
                         (const TP *)v.z, (const T *)pold, pnew, v.t, sc, (const double *)red.rz0, nrz, k, rpend,

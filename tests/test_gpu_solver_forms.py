@@ -145,3 +145,31 @@ def test_axis_transform_forms(n, bc):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_coarse_inverse_block_forms(n, per, precision):
     assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
+
+
+# the CG apply that forms the pressure coefficients from the density
+# (CHNS_OPT_MARCH_SWEEP_CELLS at or below the grid's cells): the timing record
+# shows that it ran (density, p_old and z read, p_new and q written), and the
+# solution has the bits of the stored coefficients.  Grids below 2^19 cells (one
+# cell per thread) and above (marching), ragged tiles, walls.
+@pytest.mark.parametrize("n,per", [((32, 16, 24), (True, True, False)), ((36, 20, 40), (False, False, True)),
+                                   ((80, 112, 64), (False, True, False)), ((80, 96, 80), (True, False, True))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_density_form_of_the_cg_apply(n, per, precision):
+    P = _lib()
+    g, rho, x, rhs = manufactured(n, per, 0.01, 5)
+    sols = []
+    for cells in (1 << 24, 1):
+        h = P.create_grid(n, g.h, ["periodic" if q else "wall" for q in per], precision=precision)
+        h.set_option(P.CHNS_OPT_MARCH_SWEEP_CELLS, cells)
+        h.set_timing(True)
+        p = dev(np.zeros(g.shape))
+        out = h.solve_pressure(dev(rho), dev(rhs), p, rtol=1e-13, max_iter=300)
+        apply = [t for t in h.get_timing() if t["name"] == "pcg_apply"][0]
+        print("density form", n, precision, cells, out, apply, flush=True)
+        assert out["rc"] == 0
+        if cells == 1:
+            assert apply["bytes"] == apply["launches"] * (32 + (4 if precision else 8)) * x.size
+        sols.append(p)
+    assert torch.equal(sols[0], sols[1])
+    assert float(np.abs(sols[1].cpu().numpy() - x).max() / np.abs(x).max()) <= 1e-9
