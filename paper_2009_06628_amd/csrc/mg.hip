@@ -1979,7 +1979,8 @@ static void sweep3(const Level<T> &L, const TB *b, const T *xpre, const Geo &gc,
     // b, 1 / d, cs, (x and e) in; x out
     const double bytes = sizeof(T) * (5 + (PRO ? 1 : 0)) * N + sizeof(TB) * N + (PRO ? sizeof(T) * (double)gc.N : 0.0);
     if (rz && ntiles <= kRedBlocks) {
-        TLAUNCH(K_SMOOTH, bytes + sizeof(TR) * N, (k_sweep3<T, TB, PRO, true, TR>), dim3(grid),
+        const double r_bytes = std::is_same<T, TR>::value ? 0.0 : sizeof(TR) * N;   // (of one type: r is b)
+        TLAUNCH(K_SMOOTH, bytes + r_bytes, (k_sweep3<T, TB, PRO, true, TR>), dim3(grid),
                 dim3(SweepShape::threads), st, L, b, xpre, gc, xc, x, ntx, ncol, zc, ntiles, done, rz->r, rz->p0,
                 rz->p1, rz->p2);
         *rz->nparts = ntiles;
@@ -2001,8 +2002,8 @@ static void vcycle_down(Slot<T> &S, int l, const TB *b, T *x, const int *done, h
         tile_grid2(lv.g, ntx, ntiles, grid);
         if (cg && cg->down_upd) {
             constexpr double WR = sizeof(TR);
-            // r, q, p, x in, x out; invd, s, cs in; x, bc out
-            const double bytes = 5.0 * WR * N + W * (3 + DIM) * N + W * Nc;
+            // r, q, p, x in, x out; invd, cs in; x, bc out
+            const double bytes = 5.0 * WR * N + W * (2 + DIM) * N + W * Nc;
             TLAUNCH(K_MG_DOWN, bytes, (k_down_tile2_cg<T, TR>), dim3(grid), dim3(kTileThreads), st, lv,
                     S.lev[l + 1].g, cg->r, cg->q, cg->p, cg->x, lv.r, S.lev[l + 1].b, ntx, ntiles, cg->sc,
                     cg->part_pq, cg->npq, cg->part_rr);
@@ -2010,7 +2011,7 @@ static void vcycle_down(Slot<T> &S, int l, const TB *b, T *x, const int *done, h
                     ntiles);
             return;
         }
-        const double bytes = (sizeof(TB) + W * (3 + DIM)) * N + W * Nc;   // b, invd, s, cs in; x, bc out
+        const double bytes = (sizeof(TB) + W * (2 + DIM)) * N + W * Nc;   // b, invd, cs in; x, bc out
         TLAUNCH(K_MG_DOWN, bytes, (k_down_tile2<T, TB>), dim3(grid), dim3(kTileThreads), st, lv, S.lev[l + 1].g, b,
                 lv.r, S.lev[l + 1].b, ntx, ntiles, done);
         return;
@@ -2125,7 +2126,8 @@ static void vcycle_d(Slot<T> &S, const TB *b0, T *x0, const int *done, hipStream
             Level<T> &L = S.lev[lt];
             int ntx, nty, ntiles;
             const int grid = tile3_grid(S.lev[lt + 1].g, ntx, nty, ntiles);
-            TLAUNCH(K_SMOOTH, W * (4 + DIM) * L.g.N, (k_up3_tile<T, T, false>), dim3(grid), dim3(kT3Threads), st, L,
+            // b, invd, cs in; x out
+            TLAUNCH(K_SMOOTH, W * (3 + DIM) * L.g.N, (k_up3_tile<T, T, false>), dim3(grid), dim3(kT3Threads), st, L,
                     S.lev[lt + 1].g, (const T *)nullptr, (const T *)L.b, (const T *)nullptr, L.x, ntx, nty, ntiles, done);
         } else {
             sgs(S.lev[lt], (const T *)S.lev[lt].b, S.lev[lt].x, nullptr);
@@ -2210,17 +2212,18 @@ static void cg_cycle2(Slot<TP> &SP, const Level<TR> &A, const TP *b0, TP *z, con
         vcycle_down<TP, TP, 2>(SP, 0, b0, z, done, st);
     } else {
         const CgVec2<TR> cv{R[k & 1], Sv[k & 1], v.az, R[(k + 1) & 1], Sv[(k + 1) & 1], v.p0, x};
-        // r, s, w, p, x, z in; r, s, p, x out; invd, s, cs in; x, bc out
-        TLAUNCH(K_MG_DOWN, (9.0 * WR + W) * N + W * 5 * N + W * Nc, (k_cg_down_tile2<TP, TR>), dim3(grid),
+        // r, s, w, p, x, z in; r, s, p, x out; invd, cs in; x, bc out
+        TLAUNCH(K_MG_DOWN, (9.0 * WR + W) * N + W * 4 * N + W * Nc, (k_cg_down_tile2<TP, TR>), dim3(grid),
                 dim3(kTileThreads), st, lv, gc, cv, (const TP *)z, lv.r, SP.lev[1].b, ntx, ntiles, k, SP.singular,
                 red.scal, pt, red.part1);
     }
     for (int l = 1; l < SP.lsb; ++l) vcycle_down<TP, TP, 2>(SP, l, SP.lev[l].b, SP.lev[l].x, done, st);
     vcycle_small<TP, TP, 2>(SP, b0, z, done, st, red.scal, (const double *)red.part1, k < 0 ? 0 : ntiles);
     for (int l = SP.lsb - 1; l >= 1; --l) vcycle_up<TP, TP, 2>(SP, l, SP.lev[l].b, SP.lev[l].x, done, st);
-    // r, x, invd, cs, xc in; z, w out; the CG's own s, cs where they differ
-    TLAUNCH(K_MG_UP, 2.0 * WR * N + W * 5 * N + W * Nc + (W < WR ? 3.0 * WR * N : 0.0), (k_cg_up_tile2<TP, TR>),
-            dim3(grid), dim3(kTileThreads), st, lv, gc, (const TP *)SP.lev[1].x, (const TR *)R[(k + 1) & 1],
+    // r, x, invd, cs, xc in; z, w out; the CG's own cs where they differ, and its s
+    const double own = (W < WR ? 2.0 : 0.0) + (SP.singular ? 0.0 : 1.0);
+    TLAUNCH(K_MG_UP, (2.0 + own) * WR * N + W * 5 * N + W * Nc, (k_cg_up_tile2<TP, TR>), dim3(grid),
+            dim3(kTileThreads), st, lv, gc, (const TP *)SP.lev[1].x, (const TR *)R[(k + 1) & 1],
             (const TP *)lv.r, z, v.az, A, ntx, ntiles, SP.singular, pt, done);
 }
 
@@ -2329,6 +2332,8 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
             march.nb = march.ncol * ((g0.n[2] + march.zc - 1) / march.zc);
         }
     }
+    // of an apply with stored coefficients: p_old, p_new, q, cs and, unless the operator is singular, s
+    const double WA = W * (3 + DIM + (singular ? 0 : 1));
     int launched = 0;
     int chunk = predict < 1 ? 1 : predict;
     for (;;) {
@@ -2352,7 +2357,7 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
                         red.part0, (const double *)red.rz0, (const double *)red.rz1, (const double *)red.rz2, nrz, k,
                         singular, march.ncolx, march.ncol, march.zc, SA.rho, SA.rho_ih2);
             } else if (kind == OP_SLOT && march.nb) {
-                TLAUNCH(K_PCG_APPLY, W * (4 + DIM) * N + WP * N, (k_pcg_apply3_march<T, TP, false>), dim3(march.nb),
+                TLAUNCH(K_PCG_APPLY, WA * N + WP * N, (k_pcg_apply3_march<T, TP, false>), dim3(march.nb),
                         dim3(kBlock), st, L0, (const TP *)v.z, (const T *)pold, pnew, v.q, sc, red.part0,
                         (const double *)red.rz0, (const double *)red.rz1, (const double *)red.rz2, nrz, k, singular,
                         march.ncolx, march.ncol, march.zc, (const double *)nullptr, 0.0);
@@ -2364,7 +2369,7 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
                             (const double *)red.rz1, (const double *)red.rz2, nrz, k, singular, (T *)nullptr, SA.rho,
                             SA.rho_ih2);
             } else if (kind == OP_SLOT) {
-                LAUNCHR(K_PCG_APPLY, W * (4 + DIM) * N + WP * N + WRP * N, (k_pcg_apply_slot<T, TP, DIM, false>), N,
+                LAUNCHR(K_PCG_APPLY, WA * N + WP * N + WRP * N, (k_pcg_apply_slot<T, TP, DIM, false>), N,
                         st, L0, (const TP *)v.z, (const T *)pold, pnew, v.q, sc, red.part0, (const double *)red.rz0,
                         (const double *)red.rz1, (const double *)red.rz2, nrz, k, singular, rpend,
                         (const double *)nullptr, 0.0);

@@ -173,3 +173,64 @@ def test_density_form_of_the_cg_apply(n, per, precision):
         sols.append(p)
     assert torch.equal(sols[0], sols[1])
     assert float(np.abs(sols[1].cpu().numpy() - x).max() / np.abs(x).max()) <= 1e-9
+
+
+# bytes of the timing record: each array a launch reads or writes once (w bytes
+# per value of the hierarchy, 8 in the CG), over all launches of a class
+def timed_solve(n, precision, **option):
+    P = _lib()
+    g, rho, x, rhs = manufactured(n, (True,) * len(n), 0.1, 6)
+    h = P.create_grid(n, g.h, ["periodic"] * len(n), precision=precision)
+    for name, value in option.items():
+        h.set_option(getattr(P, name), value)
+    h.set_timing(True)
+    out = h.solve_pressure(dev(rho), dev(rhs), dev(np.zeros(g.shape)), rtol=1e-10)
+    assert out["rc"] == 0
+    rec = {t["name"]: (t["launches"], t["bytes"]) for t in h.get_timing()}
+    print("bytes", n, precision, option, rec, flush=True)
+    return rec
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_timing_bytes_2d(precision):
+    """128^2: two tiled levels and 32^2 below them."""
+    rec = timed_solve((128, 128), precision)
+    w, n0, n1, n2 = (4 if precision else 8), 128 ** 2, 64 ** 2, 32 ** 2
+    cycles = rec["mg_down"][0] // 2
+    assert rec["mg_down"][0] == 2 * cycles == rec["mg_up"][0]
+    # b, 1/d, two cs in, x and the coarse b out; with the update: r, s, w, p, x in, r, s, p, x out and z for b
+    assert rec["mg_down"][1] == (5 * w * n0 + w * n1) + (cycles - 1) * ((9 * 8 + 5 * w) * n0 + w * n1) \
+        + cycles * (5 * w * n1 + w * n2)
+    # level 0: r in, w out, x, 1/d, two cs and the coarse x in, z out, the operator's own cs where they are others
+    assert rec["mg_up"][1] == cycles * ((2 * 8 + (2 * 8 if precision else 0) + 5 * w) * n0 + w * n1) \
+        + cycles * (6 * w * n1 + w * n2)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_timing_bytes_3d(precision):
+    """32^3: two levels marching along z and 8^3 below them."""
+    rec = timed_solve((32, 32, 32), precision, CHNS_OPT_TILE_CYCLE_CELLS=0)
+    w, n0, n1, n2 = (4 if precision else 8), 32 ** 3, 16 ** 3, 8 ** 3
+    cycles = rec["mg_down"][0] // 2
+    assert rec["mg_down"][0] == 2 * cycles == rec["smooth"][0]
+    # b, 1/d, three cs in, x and the coarse b out
+    assert rec["mg_down"][1] == cycles * (6 * w * n0 + w * n1 + 6 * w * n1 + w * n2)
+    # x as well in, and r for r.z where it is not b
+    assert rec["smooth"][1] == cycles * ((7 * w + (8 if precision else 0)) * n0 + w * n1 + 7 * w * n1 + w * n2)
+    # z, p_old, three cs in, p_new, q out (s of a singular operator is not read)
+    assert rec["pcg_apply"][1] == rec["pcg_apply"][0] * (6 * 8 + w) * n0
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_timing_bytes_truncated_cycle(precision):
+    """Momentum cycles of 32^3 that end on 16^3 with a symmetric sweep (Re = 50,
+    the only launches of the class): b, 1/d, three cs in, x out."""
+    P = _lib()
+    prob = W.drop3d(32, steps=1, Re=50.0)
+    h = P.grid_for_problem(prob, precision)
+    st = h.new_state(W.initial_state(prob))
+    h.set_timing(True)
+    h.step(st, 1)
+    rec = {t["name"]: (t["launches"], t["bytes"]) for t in h.get_timing()}
+    print("bytes truncated", precision, rec, flush=True)
+    assert rec["smooth"][1] == rec["smooth"][0] * 6 * (4 if precision else 8) * 16 ** 3
