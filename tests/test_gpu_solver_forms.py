@@ -13,7 +13,8 @@ import numpy as np
 import pytest
 
 import workloads as W
-from oracle import MACGrid
+from oracle import MACGrid, Params
+from oracle import chns as O
 
 pytestmark = pytest.mark.gpu
 
@@ -234,3 +235,44 @@ def test_timing_bytes_truncated_cycle(precision):
     rec = {t["name"]: (t["launches"], t["bytes"]) for t in h.get_timing()}
     print("bytes truncated", precision, rec, flush=True)
     assert rec["smooth"][1] == rec["smooth"][0] * 6 * (4 if precision else 8) * 16 ** 3
+
+
+# momentum solves of a 2D grid past 2048 level-0 tiles (2176), where the update,
+# the sums and the operator apply, with the diagonal shift of its rows, are
+# launches of their own.  The predicted velocity u* must satisfy the oracle's
+# momentum rows.  Bar: the solver stops at a relative residual of rtol_mom on the
+# recurred residual; applying A costs a relative 1e-16 of its largest terms,
+# which add up to about 100 times b here (4 eta / (Re h^2) against rho / dt), a few
+# times per iteration, so 1e-12 on top of twice the tolerance.
+@pytest.mark.parametrize("precision", [0, 1])
+def test_momentum_past_the_one_reduction_form(precision):
+    P = _lib()
+    n = (1088, 1024)
+    tol = W.PRECISION_FORM_TOLERANCES if precision else {}
+    prob = W.Problem("walls", n, 1.0 / n[0], (W.WALL, W.WALL), W.static_drop(n[0], **tol).props, 1, "drop",
+                     {"centre": (0.5, 0.45), "radius": 0.25, "velocity": "stream", "vseed": 3, "vamp": 0.05})
+    assert (n[0] // 32) * (n[1] // 16) > 2048
+    ini = W.initial_state(prob)
+    h = P.grid_for_problem(prob, precision)
+    st, rec = h.new_state(ini), h.new_record()
+    h.step_record(st, rec)
+    torch.cuda.synchronize()
+    # the right-hand side and rows of the oracle's predictor, from the step's own phi and mu
+    g, prm = MACGrid(prob.n, prob.h, prob.periodic), Params.from_props(prob.props)
+    alpha, beta, gamma, xi = O.coefficients(prm)
+    phi, u = ini["phi"], ini["u"]
+    phi_new, mu = rec["phi_new"].cpu().numpy(), rec["mu"].cpu().numpy()
+    gmu = [g.grad(mu, a) for a in range(2)]
+    m = [np.where(g.wall_face_mask(a), 0.0, g.avg(alpha * phi + beta, a) * u[a] - (alpha / prm.Cn) * gmu[a] / prm.Pe)
+         for a in range(2)]
+    rho_old, rho_new = alpha * O.pullback(phi) + beta, alpha * O.pullback(phi_new) + beta
+    eta = gamma * O.pullback(phi_new) + xi
+    for a in range(2):
+        rhs = 0.5 * (g.avg(rho_new, a) + g.avg(rho_old, a)) / prm.dt * u[a] - O.skew_advection(g, m, u[a], a)
+        rhs = rhs - (1.0 / (prm.We * prm.Cn)) * g.avg(phi, a) * gmu[a]
+        A, unk = O.momentum_matrix(g, a, g.avg(rho_new, a) / prm.dt, eta, prm.Re)
+        us = rec["ustar"][a].cpu().numpy()
+        res = float(np.linalg.norm(rhs[unk] - A @ us[unk]) / np.linalg.norm(rhs[unk]))
+        print("momentum residual", precision, a, "%.2e" % res, "change", float(np.abs(us - u[a]).max()), flush=True)
+        assert res <= 2.0 * prob.props.rtol_mom + 1e-12
+        assert not us[~unk].any()
