@@ -895,9 +895,6 @@ namespace chns {
 
 int tiled_build(chns_batch *b, int tile_cells) {
     if (tile_cells < kTileBlock || tile_cells % kTileBlock) return set_error(CHNS_EINVAL, "bad tile size");
-    if (b->prec == CHNS_FP64) {
-    } else {
-    }
     for (int l = 0; l < kMaxLev; ++l) {
         std::vector<BTile> v;
         if (l < b->nlev_max) {

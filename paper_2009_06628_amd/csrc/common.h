@@ -163,13 +163,6 @@ __device__ inline double block_sum_all(double v, double *lds) {
     return r;
 }
 
-// Sum of nparts partials in a fixed order (block-wide); result in thread 0.
-__device__ inline double sum_partials(const double *part, int nparts, double *lds) {
-    double v = 0.0;
-    for (int k = threadIdx.x; k < nparts; k += blockDim.x) v += ((volatile const double *)part)[k];
-    return block_sum(v, lds);
-}
-
 // ---------------------------------------------------------------------------
 // PCG scalar block (device memory)
 // ---------------------------------------------------------------------------
@@ -240,7 +233,7 @@ struct Red {
 // ---------------------------------------------------------------------------
 enum KClass {
     K_CH_RHS = 0, K_MU, K_PHI_UPDATE, K_MOM_SETUP, K_P_SETUP, K_PROJECT,
-    K_SMOOTH, K_RESIDUAL, K_RESTRICT, K_PROLONG, K_COARSE_SOLVE, K_MG_SETUP,
+    K_SMOOTH, K_COARSE_SOLVE, K_MG_SETUP,
     K_PCG_APPLY, K_PCG_UPDATE, K_PCG_DOT, K_PCG_INIT, K_MEAN, K_DIAG, K_ADJOINT, K_MG_DOWN, K_MG_UP,
     K_CH_SPECTRAL, K_NCLASS
 };

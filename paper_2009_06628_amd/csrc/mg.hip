@@ -1911,7 +1911,7 @@ static void mg_setup_d(Slot<T> &S, hipStream_t st, bool invd0) {
     for (int l = lsb; l < S.nlev; ++l) bytes += W * (2 + 2 * DIM) * S.lev[l].g.N;
     bytes += 8.0 * S.ncoarse * S.ncoarse;
     const int n = S.ncoarse, nb = (n + kGjB - 1) / kGjB;
-    if (n <= kLdsInverse || !S.aug) {
+    if (n <= kLdsInverse) {
         LAUNCH1(K_MG_SETUP, bytes, (k_setup_block<T, DIM>), kSBThreads, st, S, lsb, (double *)nullptr);
         return;
     }
