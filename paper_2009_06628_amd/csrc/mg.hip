@@ -2188,10 +2188,15 @@ static void precond_cg_d(Slot<TP> &SP, OpKind kind, const TP *r, TP *z, TP *w, c
 }
 
 // Tiles up to which a 2D solve takes the form with one reduction point per
-// iteration: every tile of its way down sums four partials per tile (64 KB
-// of L2 reads per tile at the limit; at 1152 tiles, 768^2, the step still
-// gains: 2133 -> 2051 us).
-constexpr int kCgTiles = 2048;
+// iteration.  Every tile of its way down sums four partials per tile, which
+// grows with the square of the tiles, and both tile passes stage a wider halo;
+// what it saves, two launches and a pass over p and q, grows with the tiles.
+// Against launches of their own for apply, update and sums, walled drops, FP64 /
+// FP32 hierarchy, pressure solve and whole step: 1152 tiles (768^2) 4 / 3 % and
+// 2 / 1 % faster, 1280 (1024 x 640) 4 / 4 and 3 / 2 %, 1408 (1024 x 704) 0 / 1 and
+// -1 / 0 %, 1536 (1024 x 768) -1 / 0 and 0 / 0 %, 1792 (1024 x 896) 0 / 0 and
+// -2 / -1 %, 2048 (1024^2) -4 / -3 and -5 / -4 % (step 3059 against 3231 us).
+constexpr int kCgTiles = 1408;
 
 // The preconditioner of iteration k of such a solve, and the update before
 // it (k < 0: the first one, from the initial residual b0; no update): level 0

@@ -276,3 +276,12 @@ def test_momentum_past_the_one_reduction_form(precision):
         print("momentum residual", precision, a, "%.2e" % res, "change", float(np.abs(us - u[a]).max()), flush=True)
         assert res <= 2.0 * prob.props.rtol_mom + 1e-12
         assert not us[~unk].any()
+
+
+# the most tiles of the one-reduction form (1408) and the first grid of these
+# widths past it (1536), where apply, update and sums are launches of their own
+@pytest.mark.parametrize("n,per", [((1024, 704), (False, True)), ((704, 1024), (True, False)),
+                                   ((1024, 768), (False, False))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_one_reduction_limit(n, per, precision):
+    assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
