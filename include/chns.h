@@ -447,9 +447,10 @@ int chns_get_timing(struct chns_grid *g, chns_kernel_timing *out, int max, int *
 /* ---- pressure solve without allocation ---------------------------------
  * For callers that cannot allocate device memory (code under stream
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
- * stand-alone S8 solve of chns_solve_pressure (same operator, kernels,
- * arguments and results), on a grid given by its description instead of a
- * handle, with no workspace argument.  Its multigrid hierarchy, CG vectors
+ * stand-alone S8 solve of chns_solve_pressure (same operator and arguments,
+ * results equal to rounding: a 2D solve sums its CG scalars in another
+ * order), on a grid given by its description instead of a handle, with no
+ * workspace argument.  Its multigrid hierarchy, CG vectors
  * and reduction scratch live in a device array of the library of
  * CHNS_NOALLOC_SCRATCH_BYTES bytes, which every GPU the library runs on
  * holds until the process ends; the call allocates nothing (no hipMalloc,

@@ -213,10 +213,15 @@ struct Slot {
 // Default of Slot::march_cells: levels whose arrays outgrow the Infinity
 // Cache (256^3 cells and up).
 constexpr long long kMarchSweepCells = 1LL << 24;
-// Default of Slot::tile_cells: the levels whose sweeps cost less than their
-// launches.  On 64^3 the marching passes are faster by now (drop step FP64 1862
-// us with the tile passes there, 1713 without; cavity 1317 / 1218), on 48^3
-// the tile passes (96^3 drop step 3038 us with them there, 3480 without).
+// Default of Slot::tile_cells: levels whose columns are too few for the chip (48^3
+// marches as 72 blocks of 4 planes, which trail by 8 to 11 steps, on 256 CUs;
+// tiles recompute more, but are 216 blocks without a march).  Whole pressure solves, us, FP64 / FP32 hierarchy,
+// tile passes on level 0 against marching ones: 48 x 48 x 40 1268 / 945 against
+// 1307 / 952, 48^3 1068 / 763 against 1095 / 784, 64 x 48 x 40 (122880 cells) 1427 /
+// 1014 against 1466 / 1019; past the line 64 x 48 x 48 (147456) 1462 / 999 against
+// 1394 / 933, 64 x 64 x 48 1500 / 1022 against 1430 / 959, 64^3 1537 / 1055 against
+// 1447 / 985.  (56^3, which fills three quarters of its columns, 3254 / 1886
+// against 3209 / 2032.)
 constexpr long long kTileCycleCells = 1LL << 17;
 
 // Reduction scratch shared by all solves of a handle.

@@ -13,8 +13,9 @@
 //   * coarse levels  re-discretised: s averaged over children, face
 //                    coefficients averaged over the fine faces of a coarse
 //                    face and divided by 4 (spacing doubles);
-//   * coarsest       explicit FP64 inverse (Gauss-Jordan in one workgroup)
-//                    with a rank-one shift tau 1 1^T for the singular
+//   * coarsest       explicit FP64 inverse (Gauss-Jordan, in one workgroup
+//                    up to kLdsInverse cells, else by block steps of the
+//                    whole chip) with a rank-one shift tau 1 1^T for the singular
 //                    pressure operator.
 // Launch structure (a launch costs a few microseconds whatever its size):
 //   * 2D levels above kSBCells cells: two tile kernels per level, one for
@@ -41,9 +42,7 @@ namespace chns {
 
 static int sb_cells() { return kSBCells; }
 
-// ---------------------------------------------------------------------------
-// grid-wide V-cycle kernels (one pass each)
-// ---------------------------------------------------------------------------
+// Grid-stride loop over cells, XCD-contiguous
 #define GRID_LOOP(N) \
     for (int c = xcd_block() * (int)blockDim.x + (int)threadIdx.x; c < (int)(N); c += (int)(gridDim.x * blockDim.x))
 
@@ -580,9 +579,9 @@ __global__ void __launch_bounds__(kBlock) k_pcg_apply3_march(Level<T> L, const T
 // 3D V-cycle passes on cubic tiles (levels of at most Slot::tile_cells cells
 // above the single-workgroup part): ONE launch per level on the way down
 // (zero-guess pre-smoothing, residual, restriction) and one on the way up
-// (prolongation, black sweep, red sweep), where the grid-wide form takes
-// three dependent launches each -- on these levels a launch costs more than
-// its sweep.  A workgroup owns a kTF^3 block of fine cells (kTC^3 coarse
+// (prolongation, black sweep, red sweep), as the columns below have, without
+// their march: on these levels a chain of planes takes longer than recomputing
+// halos (kTileCycleCells).  A workgroup owns a kTF^3 block of fine cells (kTC^3 coarse
 // cells) and recomputes into LDS what its cells' stencils reach in the
 // neighbouring tiles:
 //   down: b / d of the red cells on a halo of 3, x on a halo of 2, the
@@ -590,14 +589,14 @@ __global__ void __launch_bounds__(kBlock) k_pcg_apply3_march(Level<T> L, const T
 //         taps; that of a black cell is 0);
 //   up:   red x + P e on a halo of 2, the black GS values on a halo of 1,
 //         then the red GS values of the owned cells.
-// Each value is formed with the arithmetic and order of the grid-wide
+// Each value is formed with the arithmetic and order of the per-cell
 // bodies (presmooth_cell, apply_at, restrict_cell, prolong_at,
 // gs_color_cell), so both forms give the same bits.  The pre-smoothed x of
 // the owned cells goes to the level's r array (the residual stays in LDS)
 // and the way up reads it there, writing the smoothed x: a workgroup writes
 // its cells while its neighbours still read their halo values.  Positions
 // past a wall hold 0 and enter only with weight 0, as a missing neighbour
-// does in the grid-wide bodies (the zero product added to a sum that starts
+// does in the per-cell bodies (the zero product added to a sum that starts
 // at +0 leaves it unchanged).
 // ---------------------------------------------------------------------------
 constexpr int kTF = 8, kTC = kTF / 2;   // fine / coarse cells per tile edge
@@ -929,8 +928,9 @@ __global__ void __launch_bounds__(kT3Threads) k_up3_tile(Level<T> L, Geo gc, con
 // gs_color_cell (a neighbour past a wall enters as 0 with weight 0).
 // x, b, 1 / d and three coefficients are read once and x is written once, 56 B
 // per cell in FP64, where three passes (prolongation, black, red) moved 129.
-// Measured against these: 128^3 FP64 46.6 us -> 24.9, FP32 29.6 -> 20; 96^3 FP64
-// 26.5 -> 16.0, FP32 19.1 -> 14.6; 80^3 FP64 19.4 -> 14.8; 512^3 4.0 ms -> 1.95.
+// Measured against these, with r.z, alone on the chip (a pressure solve): 128^3
+// FP64 46.6 us -> 24.9, FP32 29.6 -> 20; 96^3 FP64 26.5 -> 16.4, FP32 19.1 -> 14.5;
+// 80^3 FP64 19.4 -> 15.2; 512^3 4.0 ms -> 1.95.
 // 128^3 FP64 moves 117 MB, 24.6 us at the rate of a large copy; 512^3 fetches
 // 1.6 times its bytes (halos that have left the L2) at 5.9 TB/s; smaller levels
 // are bound by the rounds of steps.  With the black and the red values in roles
@@ -1303,7 +1303,9 @@ __global__ void __launch_bounds__(SweepShape::threads) k_sweep3(Level<T> L, cons
 // The same partials in the same order as a pass of its own, for a level 0
 // that runs the tile passes: one block per block of the sweep, one thread per
 // pair of cells of its column, marching along z.  Both forms of the cycle then
-// give the same bits.
+// give the same bits.  Its few blocks cost nothing against k_pcg_rz (their
+// partials are what the next kernel sums): whole pressure solves with it and with
+// k_pcg_rz, FP64, 16^3 638 and 662 us, 32^3 923 and 948, 48^3 1047 and 1075.
 template <typename T, typename TZ>
 __global__ void __launch_bounds__(SweepShape::nB * kWave) k_pcg_rz3(Geo g, const T *__restrict__ r,
                                                                     const TZ *__restrict__ z,
@@ -1339,9 +1341,9 @@ __global__ void __launch_bounds__(SweepShape::nB * kWave) k_pcg_rz3(Geo g, const
 // red of its 64 taps.
 // Columns of kUX x kUY cells march along z as in k_sweep3, with three roles:
 // red values b / d (halo of 3 cells), black values and, two planes behind, the
-// red residuals (halos of 2 and 1), and one wave with a coarse cell per lane,
-// which adds a plane of residuals per step to the two coarse planes it
-// belongs to.  The lanes of a wave of the second role have rows of one parity,
+// red residuals (halos of 2 and 1), and two waves with a coarse cell per lane,
+// which add a plane of residuals per step to the two coarse planes it
+// contributes to.  The lanes of a wave of the second role have rows of one parity,
 // so which cell of a pair is red is known at compile time and both cells'
 // coefficients come from one load per pair (a load of every second cell
 // touches as many cache lines).
@@ -1352,8 +1354,9 @@ __global__ void __launch_bounds__(SweepShape::nB * kWave) k_pcg_rz3(Geo g, const
 // least bytes take 1.35 ms; halo lines that have left the L2 make it fetch 1.7
 // times them), and below the cache lines a CU can look up (halos of 3, 2 and
 // 1 cells) and the steps by which the roles trail.  b and 1 / d go to the second
-// role through LDS: with loads of its own, 128^3 24.7, 96^3 15.7, 512^3 2.06.  8 rows per column instead of 16: 96^3 level and 128^3
-// 10 % slower, 512^3 solve 377 ms against 350.
+// role through LDS: with loads of its own, 128^3 24.7, 96^3 15.7, 512^3 2.06.
+// 8 rows per column instead of 16: 96^3 level and 128^3 10 % slower, 512^3 solve
+// 377 ms against 350.
 // ---------------------------------------------------------------------------
 struct DownShape {
     static constexpr int DM = kUX / 2 + 4, D = (kUY + 6) * DM;   // pairs of the red values: per row, per plane
@@ -1558,10 +1561,12 @@ __global__ void __launch_bounds__(DownShape::threads) k_down3(Level<T> L, const 
 // Columns, planes per block (a multiple of 4) and blocks of these passes.  A CU
 // holds one block (12 or 15 waves of up to 128 registers), so a pass takes
 // ceil(blocks / CUs) rounds of a chunk's planes and the steps by which its
-// roles trail: the planes that make this least (k_down3 FP64, of an
-// earlier form, on 96^3, 8 planes, 216 blocks: 17 us, 4 planes, 432 blocks: 22;
-// on 128^3, 16 planes, 256 blocks: 24, 32 planes: 33).  max_blocks: more planes where the blocks outnumber the
-// partials of r.z.
+// roles trail: the planes that make this least.  Whole FP64 pressure solves with
+// 4, 8, 16, 32 and 64 planes on every level: 64^3 1.45, 1.59, 1.77, 2.15, 2.96 ms;
+// 96^3 2.43, 2.23, 2.41, 2.82, 3.67; 128^3 5.24, 4.66, 4.56, 5.53, 7.80 (the rule,
+// level by level, 4.14); 192^3 20.0, 17.3, 16.4, 16.1, 17.3 (14.3); 256^3 57.7, 48.6,
+// 43.0, 40.0, 43.5 (34.9).  max_blocks: more planes where the blocks outnumber
+// the partials of r.z.
 constexpr int kSweepTrail = 8, kDownTrail = 11;
 static int march3_grid(const Geo &g, int trail, int max_blocks, int &ntx, int &ncol, int &zc, int &ntiles) {
     ntx = (g.n[0] + kUX - 1) / kUX;
@@ -2294,8 +2299,9 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
         LAUNCHR(K_PCG_DOT, (W + WP) * N, (k_pcg_rz<T, TP>), N, st, N, (const T *)v.r, (const TP *)v.z,
                 (const Scal *)sc, red.rz0, red.rz1, red.rz2, singular);
     };
-    // 2D with tiled level 0: the update and the r.z partials ride on the
-    // level-0 tile passes (one partial per tile), and the residual store
+    // 2D with tiled level 0 of at most kRedBlocks tiles, the Cahn-Hilliard
+    // operator or no vector for A z: the update and the r.z partials ride on
+    // the level-0 tile passes (one partial per tile), and the residual store
     // moves to the next operator apply
     int ntiles0 = 0;
     if (DIM == 2 && SP.lsb > 0) {

@@ -2,7 +2,10 @@
 // chns_solve_pressure for callers that cannot allocate device memory.  Its
 // hierarchy, CG vectors and reduction scratch live in one file-scope device
 // array (`scratch`) of fixed size, which every GPU the library runs on holds
-// until the process ends.  The kernels are those of chns_solve_pressure.
+// until the process ends.  The kernels are those of chns_solve_pressure in 3D; in
+// 2D the CG keeps two reduction points per iteration (k_down_tile2_cg,
+// k_up_tile2_cg and an apply): the form with one needs another vector, and the
+// grids that fit the array would shrink by it.
 #include <cstring>
 #include <mutex>
 #include <string>

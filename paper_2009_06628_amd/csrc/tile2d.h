@@ -384,10 +384,10 @@ __device__ inline void up_tile2(const Level<T> &L, const Geo &gc, const T *__res
 // way down forms beta, alpha, p = z + beta p, s = w + beta s (= A p),
 // x += alpha p and r -= alpha s before it smooths.  The iterates are those of
 // the usual order in exact arithmetic; what goes is the launch of the
-// operator apply (5.4 us at 128 x 256, 6.9 us at 256 x 512, FP64), which on
-// these grids costs its latency, against 0.3 us more in each of the two tile
-// passes; the end of the iteration moves from a launch of its own (4.1 us)
-// into the single-workgroup coarse kernel.  Residuals and solutions agree
+// operator apply (5.7 us at 128 x 256, 6.8 us at 256 x 512, FP64), which on
+// these grids costs its latency, against a longer way down (6.7 -> 7.4 us, 7.0
+// -> 8.1) and way up (5.9 -> 6.5, 6.2 -> 6.8); the end of the iteration moves
+// from a launch of its own (4.0 us) into the single-workgroup coarse kernel.  Residuals and solutions agree
 // with the two-reduction form to rounding (density ratio 1000, 256 x 512:
 // the same iteration counts, true residuals within 1 %).
 // ---------------------------------------------------------------------------
