@@ -187,17 +187,19 @@ __global__ void __launch_bounds__(kSBThreads) k_vcycle_block(Slot<T> S, int l0, 
 }
 
 // End of a CG iteration: r.r, the iteration count and the stop flags (thread
-// 0; v: the scalars as they were)
+// 0; v: the scalars as they were, or *sc itself, so read before sc is written)
 __device__ inline void pcg_fin_rr_dev(Scal *sc, const Scal &v, double rr) {
     if (threadIdx.x != 0) return;
+    const int iter = v.iter + 1, max_iter = v.max_iter;
+    const double lim = v.rtol2 * v.bb;
     sc->rr = rr;
-    sc->iter = v.iter + 1;
+    sc->iter = iter;
     if (!isfinite(rr)) {
         sc->nonfinite = 1;
         sc->done = 1;
-    } else if (rr <= v.rtol2 * v.bb) {
+    } else if (rr <= lim) {
         sc->done = 1;
-    } else if (v.iter + 1 >= v.max_iter) {
+    } else if (iter >= max_iter) {
         sc->unconverged = 1;
         sc->done = 1;
     }

@@ -285,3 +285,34 @@ def test_momentum_past_the_one_reduction_form(precision):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_one_reduction_limit(n, per, precision):
     assert solve_error(n, per, ratio=0.01, precision=precision) <= 1e-9
+
+
+# max_iter is the number of CG iterations a solve may take in every form: 2D with
+# one reduction point, 2D with launches of their own, 3D, and the allocation-free
+# solve (2D with two reduction points).  Stopped early it reports all of them;
+# given exactly the iterations it needs it converges.
+@pytest.mark.parametrize("n,alloc", [((64, 64), True), ((1024, 768), True), ((32, 32, 32), True), ((64, 64, 64), True),
+                                     ((128, 64), False), ((24, 24, 24), False)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_max_iter_counts_every_iteration(n, alloc, precision):
+    P = _lib()
+    g, rho, x, rhs = manufactured(n, (True,) * len(n), 0.1, 7)
+    rho, rhs, bc = dev(rho), dev(rhs), ["periodic"] * len(n)
+    h = P.create_grid(n, g.h, bc, precision=precision) if alloc else None
+
+    def solve(max_iter):
+        p = dev(np.zeros(g.shape))
+        if alloc:
+            out = h.solve_pressure(rho, rhs, p, rtol=1e-10, max_iter=max_iter)
+        else:
+            out = P.solve_pressure_noalloc(n, g.h, bc, rho, rhs, p, rtol=1e-10, max_iter=max_iter, precision=precision)
+        print("max_iter", n, alloc, precision, max_iter, out, flush=True)
+        return out
+
+    need = solve(300)
+    assert need["rc"] == P.CHNS_OK and need["iters"] > 6
+    for m in (1, 2, 5, need["iters"] - 1):
+        out = solve(m)
+        assert out["rc"] == P.CHNS_ENOCONV and out["iters"] == m
+    out = solve(need["iters"])
+    assert out["rc"] == P.CHNS_OK and out["iters"] == need["iters"]
