@@ -383,7 +383,12 @@ __device__ inline void up_tile2(const Level<T> &L, const Geo &gc, const T *__res
 // w = A z, so both inner products r.z and w.z are taken there, and the next
 // way down forms beta, alpha, p = z + beta p, s = w + beta s (= A p),
 // x += alpha p and r -= alpha s before it smooths.  The iterates are those of
-// the usual order in exact arithmetic; what goes is the launch of the
+// the usual order in exact arithmetic.  On a singular operator the update also
+// takes the mean of r off: the recurrence of s collects rounding, so the sum of r
+// drifts from 0, and what cannot be solved for stays in r (1024 x 640, density
+// ratio 1e4: r stalled at 2e-11 of b; of 360 solves to 1e-13 at ratios of 1e3 to
+// 1e5, 512^2 to 1024 x 640, 141 did not end, 43 with two reductions, none now).
+// What goes is the launch of the
 // operator apply (5.7 us at 128 x 256, 6.8 us at 256 x 512, FP64), which on
 // these grids costs its latency, against a longer way down (6.7 -> 7.4 us, 7.0
 // -> 8.1) and way up (5.9 -> 6.5, 6.2 -> 6.8); the end of the iteration moves
@@ -486,7 +491,7 @@ __device__ inline void cg_down_tile2(const Level<T> &L, const Geo &gc, const CgV
     tile_sum4_all<NT>(sum, ws);
     // a singular operator's z is projected onto its range (mean removed); A z
     // does not see the constant
-    const double zm = singular ? sum[2] / (double)L.g.N : 0.0;
+    const double zm = singular ? sum[2] / (double)L.g.N : 0.0, rm = singular ? sum[3] / (double)L.g.N : 0.0;
     const double rz = sum[0] - zm * sum[3];
     const double beta = (k == 0 || prev_rz == 0.0) ? 0.0 : rz / prev_rz;
     const double back = (k == 0 || prev_al == 0.0) ? 0.0 : beta * rz / prev_al;
@@ -503,7 +508,7 @@ __device__ inline void cg_down_tile2(const Level<T> &L, const Geo &gc, const CgV
         }
     }
     if (!ok) return;
-    auto residual = [&](double r, double s) { return (TR)fma(-alpha, s, r); };
+    auto residual = [&](double r, double s) { return (TR)fma(-alpha, s, r - rm); };
 #pragma unroll
     for (int q = 0; q < KL; ++q) {
         const int i0 = tid + q * NT, i = i0 < NL ? i0 : NL - 1;
