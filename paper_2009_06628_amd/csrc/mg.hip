@@ -933,8 +933,8 @@ __global__ void __launch_bounds__(kT3Threads) k_up3_tile(Level<T> L, Geo gc, con
 // Measured against these, with r.z, alone on the chip (a pressure solve): 128^3
 // FP64 46.6 us -> 24.9, FP32 29.6 -> 20; 96^3 FP64 26.5 -> 16.4, FP32 19.1 -> 14.5;
 // 80^3 FP64 19.4 -> 15.2; 512^3 4.0 ms -> 1.95.
-// 128^3 FP64 moves 117 MB, 24.6 us at the rate of a large copy; 512^3 fetches
-// 1.6 times its bytes (halos that have left the L2) at 5.9 TB/s; smaller levels
+// 128^3 FP64 moves 117 MB, 24.6 us at the rate of a large copy; 512^3 moves
+// 1.6 times its bytes (halos that have left the L2) at 5.7 TB/s; smaller levels
 // are bound by the rounds of steps.  With the black and the red values in roles
 // of their own, each loading its half of every pair: 128^3 FP64 32.2, 96^3 22.1.
 // ---------------------------------------------------------------------------

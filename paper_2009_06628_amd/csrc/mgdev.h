@@ -406,10 +406,10 @@ __device__ inline void vcycle_block_dev(const Slot<T> &S, int l0, const TB *__re
 // Faces on walls hold 0 on these levels (coarsen_cell), so every axis is
 // indexed as periodic: the wrapped neighbour of a cell on a wall enters with
 // weight 0, where the masked stencils add 0 for the missing neighbour.
-// Launch, FP64 (before: every level staged in LDS in x order, 1024 threads):
-// 256 x 512 (levels 2048, 512, 128, 32) 15.6 -> 13.7 us, 64^2 11.0 -> 9.9 us,
-// 96^3 (1728, 216, 27) 15.2 -> 11.8 us, 64^3 8.7 -> 7.1 us; bit for bit the
-// same.  What is left is the 41 dependent passes, 250 to 400 cycles each.
+// Launch in a pressure solve, FP64 (before: every level staged in LDS in x order,
+// 1024 threads): 256 x 512 (levels 2048, 512, 128, 32) 15.7 -> 14.0 us and 64^2
+// 11.6 -> 10.2, with the end of the CG iteration taken in; 96^3 (1728, 216, 27)
+// 16.7 -> 13.4, 64^3 9.6 -> 8.4; bit for bit the same.  What is left is the 41 dependent passes, 250 to 400 cycles each.
 constexpr int kVsThreads = 512;
 template <int DIM>
 constexpr int kVsLevels = DIM == 2 ? 3 : 2;   // levels swept: N > 64 on each, at most 2048 on the first
@@ -1069,8 +1069,8 @@ __device__ inline void setup_block_dev(const Slot<T> &S, int l0, SetupLds &sh, d
 // inverted in registers.  Falls back to setup_block_dev where that does not
 // apply (a larger coarsest level, or no level below the grid).
 // Whole set-up kernel, FP64, with the levels in memory and the matrix in LDS
-// before: 64^2 (n = 64) 89 -> 43 us, 256 x 512 (n = 32) 30 -> 23 us, 96^3
-// (n = 27) 38 -> 27 us, all bit for bit the same; 512 batched problems, FP32,
+// before: 64^2 (n = 64) 91 -> 44 us, 256 x 512 (n = 32) 29 -> 23 us, 96^3
+// (n = 27) 32 -> 25 us, all bit for bit the same; 512 batched problems, FP32,
 // 134 -> 56 us.
 constexpr int kSetupLdsCells = kSBThreads * 2 * 4 / 3 + 32;   // all levels from 2 kSBThreads cells down (2D; fewer in 3D)
 template <typename T, int DIM>

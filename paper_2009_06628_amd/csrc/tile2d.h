@@ -385,16 +385,16 @@ __device__ inline void up_tile2(const Level<T> &L, const Geo &gc, const T *__res
 // x += alpha p and r -= alpha s before it smooths.  The iterates are those of
 // the usual order in exact arithmetic.  On a singular operator the update also
 // takes the mean of r off: the recurrence of s collects rounding, so the sum of r
-// drifts from 0, and what cannot be solved for stays in r (1024 x 640, density
+// drifts from 0, and what cannot be solved for stays in r (768 x 512, density
 // ratio 1e4: r stalled at 2e-11 of b; of 360 solves to 1e-13 at ratios of 1e3 to
 // 1e5, 512^2 to 1024 x 640, 141 did not end, 43 with two reductions, none now).
-// What goes is the launch of the
-// operator apply (5.7 us at 128 x 256, 6.8 us at 256 x 512, FP64), which on
-// these grids costs its latency, against a longer way down (6.7 -> 7.4 us, 7.0
-// -> 8.1) and way up (5.9 -> 6.5, 6.2 -> 6.8); the end of the iteration moves
-// from a launch of its own (4.0 us) into the single-workgroup coarse kernel.  Residuals and solutions agree
-// with the two-reduction form to rounding (density ratio 1000, 256 x 512:
-// the same iteration counts, true residuals within 1 %).
+// What goes is the launch of the operator apply (5.7 us at 128 x 256, 6.8 us at
+// 256 x 512, FP64), which on these grids costs its latency, against a longer way
+// down (6.7 -> 7.4 us, 7.0 -> 8.1) and way up (5.9 -> 6.5, 6.2 -> 6.8); the end of
+// the iteration moves from a launch of its own (2.7 us) into the single-workgroup
+// coarse kernel.  Residuals and solutions agree with the two-reduction form to
+// rounding (224 solves of 64^2 to 1024 x 640, ratios 10 to 1e4: the same
+// iteration counts up to -6 and +2, true residuals 2 % larger on average).
 // ---------------------------------------------------------------------------
 // Sums of four per-thread values over a workgroup of NT threads, in every
 // thread (fixed order: waves by shuffles, then the waves in order).
