@@ -214,7 +214,8 @@ void layout(Bump &B, const Plan &P, chns_grid *g, int prec) {
     g->vp1 = B.take<double>(N);
     g->vq = B.take<double>(N);
     g->vt = B.take<double>(N);
-    g->vw = P.dim == 2 ? B.take<double>(N) : nullptr;
+    const bool one = one_reduction_grid(P.lev[0], P.dim);
+    g->vw = one ? B.take<double>(N) : nullptr;
     carve_slot(B, P, g->ch, 0);
     carve_slot(B, P, g->mom, 0);
     carve_slot(B, P, g->pres, 1);
@@ -257,7 +258,7 @@ void layout(Bump &B, const Plan &P, chns_grid *g, int prec) {
         M.vp1 = B.take<double>(N);
         M.vq = B.take<double>(N);
         M.vt = B.take<double>(N);
-        M.vw = P.dim == 2 ? B.take<double>(N) : nullptr;
+        M.vw = one ? B.take<double>(N) : nullptr;
         carve_slot(B, P, M.mom, 0);
         double *maug = nc > kLdsInverse ? B.take<double>((size_t)nc * nc) : nullptr;
         M.mom.aug = maug;

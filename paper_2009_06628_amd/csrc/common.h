@@ -304,7 +304,7 @@ struct MomCtx {
     Slot<double> mom;
     Slot<float> mom32;
     double *rhs;
-    double *vr, *vz, *vp0, *vp1, *vq, *vt, *vw;   // vw: 2D only
+    double *vr, *vz, *vp0, *vp1, *vq, *vt, *vw;   // vw: one_reduction_grid only
     float *f_z, *f_t, *f_r;
     Red red;
     hipStream_t stream;
@@ -352,7 +352,7 @@ struct chns_grid {
     double *phi_new2, *phihat2, *rch2;       // the second stored phase (nph == 3)
     double *mix3[5];                         // per-step mixture fields (nph == 3)
     double *mflux3[3];                       // per-step face mass fluxes (nph == 3)
-    double *vr, *vz, *vp0, *vp1, *vq, *vt, *vw;   // PCG vectors (vw: 2D only)
+    double *vr, *vz, *vp0, *vp1, *vq, *vt, *vw;   // PCG vectors (vw: one_reduction_grid only)
     chns::Slot<double> ch, mom, pres;
     // precision form (FP32 inner solves under FP64 refinement)
     int prec;

@@ -2204,6 +2204,12 @@ static void precond_cg_d(Slot<TP> &SP, OpKind kind, const TP *r, TP *z, TP *w, c
 // -1 / 0 %, 1536 (1024 x 768) -1 / 0 and 0 / 0 %, 1792 (1024 x 896) 0 / 0 and
 // -2 / -1 %, 2048 (1024^2) -4 / -3 and -5 / -4 % (step 3059 against 3231 us).
 constexpr int kCgTiles = 1408;
+bool one_reduction_grid(const Geo &g, int dim) {
+    int ntx, ntiles, grid;
+    if (dim != 2 || g.N <= kSBCells) return false;
+    tile_grid2(g, ntx, ntiles, grid);
+    return ntiles <= kCgTiles;
+}
 
 // The preconditioner of iteration k of such a solve, and the update before
 // it (k < 0: the first one, from the initial residual b0; no update): level 0
@@ -2312,7 +2318,7 @@ static hipError_t pcg_d(Slot<T> &SA, Slot<TP> &SP, OpKind kind, ChOp ch, const T
     }
     // one reduction point per iteration: the operator apply rides on the
     // preconditioner's last pass as well
-    const bool one = DIM == 2 && kind == OP_SLOT && SP.lsb > 0 && v.az && ntiles0 <= kCgTiles;
+    const bool one = kind == OP_SLOT && SP.lsb > 0 && v.az && one_reduction_grid(g, DIM);
     const bool fuse = !one && DIM == 2 && SP.lsb > 0 && ntiles0 <= kRedBlocks;
     if (fuse) nrz = ntiles0;
     L0Cg<T> cg{0, 0, 1, (const T *)v.r, (const T *)v.q, nullptr, x, sc, (const double *)red.part0, nb,

@@ -19,6 +19,9 @@ struct PcgVecs {
     T *w = nullptr;
 };
 
+// Whether solves on grid g take that form.
+bool one_reduction_grid(const Geo &g, int dim);
+
 // PCG vectors in precision T with the preconditioned vector z and the
 // preconditioner's scratch w in precision TP.
 template <typename T, typename TP>

@@ -121,3 +121,12 @@ def test_bench_refuses_more_than_one_gpu():
         assert r.returncode == 2
         assert "one GPU only" in r.stderr
         assert r.stdout == ""
+
+
+def test_workspace_carries_no_vector_that_no_solve_uses():
+    """A z of the one-reduction CG is carved only where solves take that form
+    (4096 x 128: 1024 tiles; 4096 x 256 has 2048): one array per velocity
+    component less per cell.  (No direct Cahn-Hilliard solve on these axes, so
+    all else is per cell or smaller on the larger grid.)"""
+    per_cell = [P.workspace_size((4096, m), 1.0 / 4096, ("periodic", "wall")) / (4096 * m) for m in (128, 256)]
+    assert per_cell[0] - per_cell[1] >= 16.0
